@@ -130,8 +130,8 @@ def chain_probe(P, synth, torch, half=1000, days=40, n_nodes=1, classes=1):
     class), so the chain walks the six-compartment model as the farm
     networks' herds do. With one node the chain is walked by a wavefront;
     from 8192 nodes on, the largest herd has a workgroup as on the farm
-    networks (the block walk fed by a second wavefront, and the workgroup walk
-    while the chain expects 4096 attempts or more)."""
+    networks (the workgroup walk while the chain expects 128 attempts or
+    more, then a wavefront's)."""
     import numpy as np
 
     def day_us(S0):
@@ -605,7 +605,7 @@ def main():
     # the serial critical path: each day's longest SSA chain at the
     # per-attempt time of a long chain walked as the day kernel walks the
     # largest herd (from 8192 nodes with one lane per node: its own workgroup,
-    # the workgroup walk for chains of 4096 expected attempts or more)
+    # the workgroup walk for chains of 128 expected attempts or more)
     hub_layout = p.n_nodes >= 8192 and p.n_rep == 1 and not best.get("tile_nodes")
     # the probe walks the workload's own rules: three S<->I classes on the
     # six-compartment networks, one on the synthetic model (its launches are
@@ -616,7 +616,7 @@ def main():
         if hub_layout:
             short = chain_probe(P, synth, torch, half=1000, n_nodes=8192, classes=classes)
             long_ = chain_probe(P, synth, torch, half=10000, days=20, n_nodes=8192, classes=classes)
-            per_day_us = np.where(most + 1 >= 4096, long_["us_per_attempt"], short["us_per_attempt"]) * (most + 1)
+            per_day_us = np.where(most + 1 >= 128, long_["us_per_attempt"], short["us_per_attempt"]) * (most + 1)
             probes = [short, long_]
         else:
             one = chain_probe(P, synth, torch, classes=classes)
@@ -631,7 +631,7 @@ def main():
                         cycles_per_attempt=[round(q["cycles_per_attempt"], 1) for q in probes],
                         chain_ms_per_step=round(chain_ms, 3), step_ms=round(step_ms, 3),
                         frac=round(chain_ms / step_ms, 4), probe=[q["probe"] for q in probes],
-                        rule="longest chains of 4096 attempts or more at the second probe's rate" if hub_layout else "")
+                        rule="longest chains of 128 attempts or more at the second probe's rate" if hub_layout else "")
     roofline["binding"] = ("serial SSA chain of the day's largest herd (critical_path.frac of the step), "
                            "not HBM")
     tag = {"sise3-37k": "sq_37k", "sise3-1m": "sq_1m", "sise3-37k-u10": "sq_u10",

@@ -223,6 +223,35 @@ struct PairRules {
             c.xd[2 * q + 1] = c.xd[2 * q + 1] - dq;
         }
     }
+    // The walks by many lanes describe a run of picks by the net number of
+    // individuals it returns to S in each class.
+    static constexpr int kFlows = NP;
+    __device__ static __forceinline__ void flows(int j, unsigned long long lanes, int (&n)[kFlows]) {
+#pragma unroll
+        for (int q = 0; q < NP; ++q)
+            n[q] = __popcll(__ballot(j == 2 * q + 1) & lanes) - __popcll(__ballot(j == 2 * q) & lanes);
+    }
+    // running sums of the rates in the state of c after the flows n
+    __device__ static __forceinline__ void cum_after(const Model &, const State &c, const int (&n)[kFlows],
+                                                     double (&cum)[NT]) {
+        double l = 0.0;
+#pragma unroll
+        for (int q = 0; q < NP; ++q) {
+            const double dS = (double)n[q];
+            l = l + c.cphi[2 * q] * (c.xd[2 * q] + dS);
+            cum[2 * q] = l;
+            l = l + c.cphi[2 * q + 1] * (c.xd[2 * q + 1] - dS);
+            cum[2 * q + 1] = l;
+        }
+    }
+    __device__ static __forceinline__ void advance(const Model &, State &c, const int (&n)[kFlows]) {
+#pragma unroll
+        for (int q = 0; q < NP; ++q) {
+            const double dS = (double)n[q];
+            c.xd[2 * q] = c.xd[2 * q] + dS;
+            c.xd[2 * q + 1] = c.xd[2 * q + 1] - dS;
+        }
+    }
     // j is the same in every lane (a scalar): only class j/2 changes, so only
     // the running sums from its first transition on are recomputed (the
     // earlier ones are unchanged, so the values equal a full recomputation).
@@ -247,7 +276,7 @@ struct PairRules {
 };
 
 // The single-chain walk for paired classes (defined below).
-template <int NP, bool FED = false>
+template <int NP>
 __device__ __forceinline__ void pairs_walk_block(const Model &m, Chain<2 * NP, 2 * NP> &c, uint32_t kbase,
                                                  uint32_t node, uint32_t day, uint32_t key0, uint32_t key1,
                                                  unsigned long long *status, int32_t r);
@@ -364,86 +393,6 @@ __device__ __forceinline__ int clock_by_scan(double clock, double tau, double *c
     return A;
 }
 
-// Value v[idx / 64] of lane idx % 64 (idx uniform over the wavefront).
-template <int W>
-__device__ __forceinline__ double part_at(const double (&v)[W], int idx) {
-    double out = 0.0;
-#pragma unroll
-    for (int w = 0; w < W; ++w)
-        if (idx / 64 == w) out = lane_f64(v[w], idx % 64);
-    return out;
-}
-
-// The clock of a round of the workgroup walk without the attempt-by-attempt
-// sum (the rule of clock_by_scan, carried past ties and binade ends). While the running
-// clock s stays in one binade [2^e, 2^(e+1)) every partial sum is an integer
-// multiple of its spacing h = 2^(e-52), and adding a waiting time rounds to
-// the nearest multiple: s + tau -> (s/h + rn(tau/h)) h. Those integers add
-// exactly (each partial sum that matters stays below 2^53), so prefix sums
-// over the round's attempts (attempt w * 64 + lane in tau[w]) give the
-// partial sums bit for bit up to the first attempt that either reaches
-// 2^(e+1) or lies exactly half-way between two multiples (ties round to even,
-// which depends on the partial sum). That attempt is added as the
-// attempt-by-attempt walk adds it, and the scan goes on from the next one in
-// the binade of the new sum; so does an attempt added to a clock of 0. The
-// first attempt whose sum is not below 1 ends the round. Returns the number of
-// attempts that fire and their clock, or -1 for a clock too small to scale
-// (the caller sums attempt by attempt). Every lane of the wavefront calls it.
-template <int W>
-__device__ __forceinline__ int clock_exact_scan(double clock, const double (&tau)[W], double *clock_out) {
-    const int lane = threadIdx.x & 63;
-    constexpr int N = 64 * W;
-    int done = 0;  // attempts before done fire; s is the clock after them
-    double s = clock;
-    for (int iter = 0; iter <= N; ++iter) {
-        if (done == N) break;
-        if (!(s > 0.0)) {
-            const double t0 = part_at<W>(tau, done);  // 0 + tau is tau
-            if (!(t0 < 1.0)) break;
-            s = t0;
-            ++done;
-            continue;
-        }
-        const long long cb = __double_as_longlong(s);
-        const int e = (int)((cb >> 52) & 0x7ff) - 1023;
-        if (e < -960) return -1;
-        const double up = __longlong_as_double((long long)(1023 + 52 - e) << 52);    // 2^(52-e)
-        const double down = __longlong_as_double((long long)(1023 - 52 + e) << 52);  // 2^(e-52)
-        const double S0 = s * up;                                                    // in [2^52, 2^53)
-        const double T = 0x1p53 - S0;
-        double P[W];
-        int special = N;  // first attempt past the binade or on a tie
-        double carry = 0.0;
-#pragma unroll
-        for (int w = 0; w < W; ++w) {
-            const bool live = 64 * w + lane >= done;
-            const double v = tau[w] * up;
-            const double fl = floor(v);
-            const double fr = v - fl;
-            P[w] = wave_prefix_sum(live ? (fr > 0.5 ? fl + 1.0 : fl) : 0.0) + carry;
-            carry = lane_f64(P[w], 63);
-            const unsigned long long odd = __ballot(live && (fr == 0.5 || !(P[w] < T)));
-            if (special == N && odd != 0ull) special = 64 * w + __ffsll((long long)odd) - 1;
-        }
-        const double before = special > done ? (S0 + part_at<W>(P, special - 1)) * down : s;
-        if (special == N) {
-            s = before;
-            done = N;
-            break;
-        }
-        const double s2 = before + part_at<W>(tau, special);
-        if (!(s2 < 1.0)) {
-            s = before;
-            done = special;
-            break;
-        }
-        s = s2;
-        done = special + 1;
-    }
-    *clock_out = s;
-    return done;
-}
-
 // One chain walked by the whole wavefront, 64 attempts per round, for paired
 // classes. Attempt kbase + i belongs to lane i; its draws do not depend on the
 // state, but the transition it picks (eq:sampling2) and its waiting time
@@ -464,51 +413,19 @@ __device__ __forceinline__ int clock_exact_scan(double clock, const double (&tau
 // Counts are exact integers in binary64 and the rates, running sums, targets
 // and waiting times are the same functions of the same state as in a walk
 // attempt by attempt, so the bits agree.
-// With FED, every thread of a workgroup calls it: wavefront 0 walks the chain
-// while wavefront 1 computes the next round's draws (Philox, -log rand, rand)
-// into LDS, one round ahead, with a workgroup barrier per round; the draws do
-// not depend on the state, so the walk is the same.
-template <int NP, bool FED>
+template <int NP>
 __device__ __forceinline__ void pairs_walk_block(const Model &m, Chain<2 * NP, 2 * NP> &c, uint32_t kbase,
                                                  uint32_t node, uint32_t day, uint32_t key0, uint32_t key1,
                                                  unsigned long long *status, int32_t r) {
     constexpr int NT = 2 * NP;
     __shared__ double sh_tau[kWaves][64];
-    __shared__ double sh_draw[2][2][64];  // fed walk: [buffer][E, U][attempt of the round]
-    __shared__ int sh_go;                 // fed walk: 0 once wavefront 0 has ended the chain
     const uint32_t lane = threadIdx.x & 63u;
     const int wave = threadIdx.x >> 6;
     const unsigned long long below = (1ull << lane) - 1ull;
-    [[maybe_unused]] int rnd = 0;
-    if constexpr (FED) {
-        auto produce = [&](uint32_t kb, int b) {
-            const Word4 o = philox4x32_10(Word4{kb + lane, node, day, 0u}, key0, key1);
-            sh_draw[b][0][lane] = minus_log(unit_open(o.a, o.b));
-            sh_draw[b][1][lane] = unit_open(o.c, o.d);
-        };
-        if (wave == 1) produce(kbase, 0);
-        if (threadIdx.x == 0) sh_go = 1;
-        __syncthreads();
-        if (wave != 0) {
-            // the producer (and two idle wavefronts): one barrier per round of
-            // wavefront 0, which clears sh_go before the barrier of its last
-            for (;; ++rnd) {
-                if (wave == 1) produce(kbase + 64u * (uint32_t)(rnd + 1), (rnd + 1) & 1);
-                __syncthreads();
-                if (!sh_go) return;
-            }
-        }
-    }
-    for (;; ++rnd) {
-        double E, U;
-        if constexpr (FED) {
-            E = sh_draw[rnd & 1][0][lane];
-            U = sh_draw[rnd & 1][1][lane];
-        } else {
-            const Word4 o = philox4x32_10(Word4{kbase + lane, node, day, 0u}, key0, key1);
-            E = minus_log(unit_open(o.a, o.b));
-            U = unit_open(o.c, o.d);
-        }
+    for (;;) {
+        const Word4 o = philox4x32_10(Word4{kbase + lane, node, day, 0u}, key0, key1);
+        const double E = minus_log(unit_open(o.a, o.b));
+        const double U = unit_open(o.c, o.d);
         // guess: every attempt sees the round's starting state
         int j = 0;
         {
@@ -611,41 +528,46 @@ __device__ __forceinline__ void pairs_walk_block(const Model &m, Chain<2 * NP, 2
         c.fired = c.fired + A;
         pairs_rates_full<NP>(c);
         if (limit && lane == 0) atomicMin(status, (STATUS_LIMIT_TAG << 32) | (unsigned long long)(uint32_t)r);
-        const bool done = limit || A < 64 || !(c.lam > 0.0);
-        if constexpr (FED) {
-            if (done && lane == 0) sh_go = 0;
-            __syncthreads();  // the producer's next round is in LDS; with sh_go = 0 the others leave
-        }
-        if (done) return;
+        if (limit || A < 64 || !(c.lam > 0.0)) return;
         kbase = kbase + 64;
     }
 }
 
-// One chain walked by the four wavefronts of a workgroup, 256 attempts per
-// round (attempt kbase + t for thread t), for paired classes: the scheme of
-// pairs_walk_block, with the picks of each wavefront (one ballot per
-// transition) shared in LDS so that an attempt counts the picks of every
-// attempt below it, and the clock of the 256 waiting times decided by
-// wavefront 0. Every thread of the workgroup calls it with the same state and
-// ends with the same state. It pays off for long chains only: a round starts
-// only while the window still expects min_attempts attempts
-// (lambda (1 - clock)), and a round whose picks do not settle within
+// One chain walked by all wavefronts of a workgroup, kBlock attempts per round
+// (attempt kbase + t for thread t): the scheme of pairs_walk_block, with the
+// picks of each wavefront shared in LDS as its flows (Rules::flows), so that
+// an attempt's state is the round's state after the flows of the wavefronts
+// below and of the lanes below in its own. One barrier per pass: a wavefront
+// publishes its flows together with whether its picks moved in the pass
+// before, and a pass that finds no wavefront moved ends the round.
+// The clock follows the rule of clock_by_scan, in every wavefront at once:
+// prefix sums within the wavefronts and the wavefronts' totals through LDS give
+// every partial sum of the binade; an attempt whose sum leaves the binade, or
+// that lies half-way between two multiples, is added as the serial walk adds
+// it, and the scan goes on behind it in the binade of the new sum. A chain's
+// first kHeadAttempts attempts, most of whose sums are the first in their
+// binade, are added one by one from LDS.
+// A round takes about 6,000 cycles, most of them the latency of dependent
+// binary64 arithmetic and of LDS (one wavefront a SIMD): 10 ns an attempt
+// against 13 with the clock decided by one wavefront while three waited and two
+// barriers a pass (37k network, u = 10, 120 days: 47.1 -> 30.4 ms).
+// Every thread of the workgroup calls it with the same state and ends with the
+// same state. A round starts only while the window still expects min_attempts
+// attempts (lambda (1 - clock)), and a round whose picks do not settle within
 // kGroupPasses passes is dropped. Returns whether the chain is done; if not,
 // the caller continues with the single-wavefront walk from attempt kbase and
 // state c, which are those at the start of a round.
 constexpr int kGroupPasses = 8;
+constexpr int kHeadAttempts = 16;
 
-template <int NP>
-__device__ bool pairs_walk_group(Chain<2 * NP, 2 * NP> &c, uint32_t &kbase, uint32_t node, uint32_t day,
-                                 uint32_t key0, uint32_t key1, unsigned long long *status, int32_t r,
-                                 double min_attempts) {
-    constexpr int NT = 2 * NP;
+template <class Rules>
+__device__ bool walk_group(const Model &m, typename Rules::State &c, uint32_t &kbase, uint32_t node, uint32_t day,
+                           uint32_t key0, uint32_t key1, unsigned long long *status, int32_t r, double min_attempts) {
+    constexpr int NT = Rules::NT, K = Rules::kFlows;
     constexpr int kRound = kBlock;
-    __shared__ unsigned long long sh_b[2][kWaves][NT];  // picks of each wavefront and pass, per transition
-    __shared__ int sh_moved[2][kWaves];
-    __shared__ double sh_tau[kRound];
-    __shared__ double sh_clock;
-    __shared__ int sh_fired;
+    __shared__ int32_t sh_flow[2][kWaves][K], sh_moved[2][kWaves];
+    __shared__ double sh_head[kHeadAttempts], sh_total[kWaves], sh_before, sh_at;
+    __shared__ int32_t sh_tie[kWaves], sh_special;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const unsigned long long below = (1ull << lane) - 1ull;
     int buf = 0;
@@ -654,6 +576,7 @@ __device__ bool pairs_walk_group(Chain<2 * NP, 2 * NP> &c, uint32_t &kbase, uint
         const Word4 o = philox4x32_10(Word4{kbase + (uint32_t)t, node, day, 0u}, key0, key1);
         const double E = minus_log(unit_open(o.a, o.b));
         const double U = unit_open(o.c, o.d);
+        // guess: every attempt sees the round's starting state
         int j = 0;
         {
             const double target = U * c.lam;
@@ -661,108 +584,139 @@ __device__ bool pairs_walk_group(Chain<2 * NP, 2 * NP> &c, uint32_t &kbase, uint
             for (int k = 0; k < NT; ++k) j += c.cum[k] < target ? 1 : 0;
         }
         double lam = c.lam;
-        bool settled = false;
+        bool settled = false, moved = true;
+        int all[K];
         for (int pass = 0; pass < kGroupPasses; ++pass) {
-            unsigned long long bk[NT];
-#pragma unroll
-            for (int k = 0; k < NT; ++k) bk[k] = __ballot(j == k);
+            int n[K];
+            Rules::flows(j, ~0ull, n);
             if (lane == 0) {
 #pragma unroll
-                for (int k = 0; k < NT; ++k) sh_b[buf][wave][k] = bk[k];
+                for (int k = 0; k < K; ++k) sh_flow[buf][wave][k] = n[k];
+                sh_moved[buf][wave] = moved ? 1 : 0;
             }
-            __syncthreads();
-            double l = 0.0, cum[NT];
-#pragma unroll
-            for (int q = 0; q < NP; ++q) {
-                int inf = (int)__popcll(bk[2 * q] & below), rec = (int)__popcll(bk[2 * q + 1] & below);
-                for (int w = 0; w < wave; ++w) {
-                    inf += (int)__popcll(sh_b[buf][w][2 * q]);
-                    rec += (int)__popcll(sh_b[buf][w][2 * q + 1]);
-                }
-                const double dS = (double)(rec - inf);
-                l = l + c.cphi[2 * q] * (c.xd[2 * q] + dS);
-                cum[2 * q] = l;
-                l = l + c.cphi[2 * q + 1] * (c.xd[2 * q + 1] - dS);
-                cum[2 * q + 1] = l;
-            }
-            const double target = U * l;
-            int jn = 0;
-#pragma unroll
-            for (int k = 0; k < NT; ++k) jn += cum[k] < target ? 1 : 0;
-            const bool moved = __ballot(jn != j) != 0ull;
-            j = jn;
-            lam = l;
-            if (lane == 0) sh_moved[buf][wave] = moved ? 1 : 0;
             __syncthreads();
             bool any = false;
+            Rules::flows(j, below, n);
 #pragma unroll
-            for (int w = 0; w < kWaves; ++w) any = any || sh_moved[buf][w] != 0;
+            for (int k = 0; k < K; ++k) all[k] = 0;
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) {
+                any = any || sh_moved[buf][w] != 0;
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    const int f = sh_flow[buf][w][k];
+                    all[k] += f;
+                    n[k] += w < wave ? f : 0;
+                }
+            }
             buf ^= 1;
-            if (!any) {
+            if (!any) {  // the picks are those the waiting rates lam were computed from
                 settled = true;
                 break;
             }
+            double cum[NT];
+            Rules::cum_after(m, c, n, cum);
+            lam = cum[NT - 1];
+            const double target = U * lam;
+            int jn = 0;
+#pragma unroll
+            for (int k = 0; k < NT; ++k) jn += cum[k] < target ? 1 : 0;
+            moved = __ballot(jn != j) != 0ull;
+            j = jn;
         }
         if (!settled) return false;  // the same in every thread; nothing of this round applied
-        const int last = buf ^ 1;  // the final picks' ballots
-        sh_tau[t] = E / lam;       // lambda = 0: tau = inf, never fires
-        __syncthreads();
-        if (wave == 0) {
-            double tw[kWaves];
-#pragma unroll
-            for (int w = 0; w < kWaves; ++w) tw[w] = sh_tau[64 * w + lane];
-            double clock;
-            int A = clock_exact_scan<kWaves>(c.clock, tw, &clock);
-            if (A < 0) {
-                // attempt by attempt, in order
-                double s = c.clock, mine[kWaves];
-#pragma unroll
-                for (int w = 0; w < kWaves; ++w) {
-                    mine[w] = 0.0;
-#pragma unroll 16
-                    for (int i = 0; i < 64; ++i) {
-                        s = s + sh_tau[64 * w + i];
-                        if (lane == i) mine[w] = s;
-                    }
+        const double tau = E / lam;  // lambda = 0: tau = inf, never fires
+        double s = c.clock;
+        int done = 0;        // attempts before done fire; s is the clock after them
+        bool ended = false;  // attempt done does not fire
+        if (!(s > 0.0)) {
+            if (t < kHeadAttempts) sh_head[t] = tau;
+            __syncthreads();
+            for (; done < kHeadAttempts; ++done) {
+                const double s2 = s + sh_head[done];
+                if (!(s2 < 1.0)) {
+                    ended = true;
+                    break;
                 }
-                A = 0;
-#pragma unroll
-                for (int w = 0; w < kWaves; ++w) A += (int)__popcll(__ballot(mine[w] < 1.0));
-                clock = c.clock;
-#pragma unroll
-                for (int w = 0; w < kWaves; ++w)
-                    if (A > 0 && (A - 1) / 64 == w) clock = lane_f64(mine[w], (A - 1) % 64);
-            }
-            if (lane == 0) {
-                sh_clock = clock;
-                sh_fired = A;
+                s = s2;
             }
         }
-        __syncthreads();
-        int A = sh_fired;
-        const double clock = sh_clock;
+        while (!ended && done < kRound) {
+            const int e = (int)((__double_as_longlong(s) >> 52) & 0x7ff) - 1023;
+            if (e < -960) return false;  // too small to scale; nothing of this round applied
+            const double up = __longlong_as_double((long long)(1023 + 52 - e) << 52);    // 2^(52-e)
+            const double down = __longlong_as_double((long long)(1023 - 52 + e) << 52);  // 2^(e-52)
+            const double S0 = s * up;                                                    // in [2^52, 2^53)
+            const double T = 0x1p53 - S0;
+            const bool live = t >= done;
+            const double v = tau * up;
+            const double fl = floor(v);
+            const double fr = v - fl;
+            const double P = wave_prefix_sum(live ? (fr > 0.5 ? fl + 1.0 : fl) : 0.0);
+            const bool tie = live && fr == 0.5;
+            const unsigned long long ties = __ballot(tie);
+            const double total = lane_f64(P, 63);
+            if (lane == 0) {
+                sh_total[wave] = total;
+                sh_tie[wave] = ties != 0ull ? 1 : 0;
+            }
+            __syncthreads();
+            double carry = 0.0, mine = 0.0;
+            int first = kWaves;  // the first wavefront with a sum past the binade or a tie
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) {
+                if (w == wave) mine = carry;
+                carry = carry + sh_total[w];
+                if (first == kWaves && (sh_tie[w] != 0 || !(carry < T))) first = w;
+            }
+            if (first == kWaves) {
+                s = (S0 + carry) * down;
+                done = kRound;
+                break;
+            }
+            if (wave == first) {
+                const double Pg = P + mine;
+                const int sp = __ffsll((long long)__ballot(tie || (live && !(Pg < T)))) - 1;
+                const double prior = sp > 0 ? lane_f64(Pg, max(sp, 1) - 1) : mine;
+                if (lane == sp) {
+                    sh_at = tau;
+                    sh_before = (S0 + prior) * down;
+                    sh_special = 64 * wave + sp;
+                }
+            }
+            __syncthreads();
+            const double s2 = sh_before + sh_at;
+            done = sh_special;
+            ended = !(s2 < 1.0);
+            s = ended ? sh_before : s2;
+            done += ended ? 0 : 1;
+        }
+        int A = done;
         bool limit = false;
         if (c.fired + A >= SIM_MAX_FIRED) {
             A = SIM_MAX_FIRED - c.fired;
             limit = true;
         }
+        if (A < kRound) {
+            const int nw = A - 64 * wave;
+            int n[K];
+            Rules::flows(j, nw >= 64 ? ~0ull : (nw > 0 ? ((1ull << nw) - 1ull) : 0ull), n);
+            if (lane == 0) {
 #pragma unroll
-        for (int q = 0; q < NP; ++q) {
-            int inf = 0, rec = 0;
-#pragma unroll
-            for (int w = 0; w < kWaves; ++w) {
-                const int nw = A - 64 * w;
-                const unsigned long long fired = nw >= 64 ? ~0ull : (nw > 0 ? ((1ull << nw) - 1ull) : 0ull);
-                inf += (int)__popcll(sh_b[last][w][2 * q] & fired);
-                rec += (int)__popcll(sh_b[last][w][2 * q + 1] & fired);
+                for (int k = 0; k < K; ++k) sh_flow[buf][wave][k] = n[k];
             }
-            const double d = (double)(rec - inf);
-            c.xd[2 * q] = c.xd[2 * q] + d;
-            c.xd[2 * q + 1] = c.xd[2 * q + 1] - d;
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                all[k] = 0;
+#pragma unroll
+                for (int w = 0; w < kWaves; ++w) all[k] += sh_flow[buf][w][k];
+            }
         }
-        if (A > 0 && !limit) c.clock = clock;
+        Rules::advance(m, c, all);
+        if (A > 0 && !limit) c.clock = s;
         c.fired = c.fired + A;
-        pairs_rates_full<NP>(c);
+        Rules::rates(m, c);
         if (limit) {
             if (t == 0) atomicMin(status, (STATUS_LIMIT_TAG << 32) | (unsigned long long)(uint32_t)r);
             return true;
@@ -1115,11 +1069,12 @@ __device__ void group_chain(const Model &m, typename Rules::State &c, bool live,
         u.fired = 0;
         uint32_t kb = 0;
         // a short chain, or the end of a long one, is walked by wavefront 0
-        // (thread 0 is in it) while wavefront 1 draws one round ahead
-        if (!pairs_walk_group<Rules::kPairs>(u, kb, sh_key[0], day, sh_key[1], sh_key[2], status, (int32_t)sh_key[3],
-                                             min_attempts))
-            pairs_walk_block<Rules::kPairs, true>(m, u, kb, sh_key[0], day, sh_key[1], sh_key[2], status,
-                                                  (int32_t)sh_key[3]);
+        // (thread 0 is in it)
+        if (!walk_group<Rules>(m, u, kb, sh_key[0], day, sh_key[1], sh_key[2], status, (int32_t)sh_key[3],
+                               min_attempts) &&
+            threadIdx.x < 64)
+            pairs_walk_block<Rules::kPairs>(m, u, kb, sh_key[0], day, sh_key[1], sh_key[2], status,
+                                            (int32_t)sh_key[3]);
         __builtin_amdgcn_s_setprio(0);
         if (threadIdx.x == 0) c = u;
     }

@@ -20,7 +20,7 @@ one lane per node (one trajectory per instance):
   group_herds        how many of the largest herds of a large instance get a
                      whole workgroup for their chains (0: default 4, negative: none);
   group_min_attempts how many attempts a chain must still expect in the day for
-                     the workgroup to walk it (0: default 4096);
+                     the workgroup to walk it (0: default 128);
   tile_nodes         nonzero: tiles of this many nodes instead, each wavefront
                      walking one node's chain with all its lanes;
 replicate tiles (several replicates per instance):
