@@ -136,23 +136,23 @@ typedef struct sim_device_opts {
     int32_t block;         /* threads per workgroup for node kernels: 0 or 256 (the kernels are built for 256) */
     int32_t launch;        /* SIM_LAUNCH_*: how days are issued */
     int32_t group_herds;   /* with one lane per node and per-day launches, the largest herds per instance of
-                              at least 8192 nodes whose chains a whole workgroup walks: 0 = default (4),
+                              at least 8192 nodes that get a workgroup to themselves: 0 = default (4),
                               negative = none, at most 16 */
     int32_t small_level;   /* per-day launches: event levels of at most this many (event, replicate) tasks
                               run several per launch in one workgroup: 0 = default (512) */
     int32_t tile_nodes;    /* replicate tiles (R > 1): node positions per tile of 64 replicate lanes, which the
                               tile's four wavefronts take one at a time: 0 = default (128), else a power of two in
-                              [4, 512]. With one replicate (R = 1) a nonzero value selects tiles as well: each
-                              wavefront then walks one node's chain at a time with all its lanes (for networks
-                              of few nodes with long chains); 0 keeps one lane per node */
+                              [4, 512]. With one replicate (R = 1) and per-day launches, the nodes of one
+                              workgroup: 0 = chosen by the network's size (4 to 1024), else a power of two in
+                              [4, 512]; the persistent launch runs one replicate in tiles if it is nonzero */
     int32_t heavy_herds;   /* replicate tiles with per-day launches: the largest herds per instance (at most one per
                               64 nodes) whose every (herd, replicate) chain gets a wavefront of its own: 0 = default
                               (64), negative = none, at most 256 */
     int32_t few_chains;    /* at most this many live chains of a wavefront, one of them still expecting many
                               attempts, are walked one after another by the whole wavefront: 0 = default (4),
                               negative = never, at most 64 */
-    int32_t group_min_attempts; /* one lane per node with per-day launches: a workgroup walks one herd's chain
-                              while it still expects this many attempts in the day: 0 = default (128) */
+    int32_t group_min_attempts; /* one lane per node with per-day launches: a chain that expects this many
+                              attempts in the day may be walked by its whole workgroup: 0 = default (256) */
     int32_t slot_lanes;    /* slot handles: replicate lanes per slot, 8, 16, 32 or 64 (0 = 64); n_slots times
                               slot_lanes must be a multiple of 64 */
 } sim_device_opts;

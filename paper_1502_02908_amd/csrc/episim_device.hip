@@ -32,7 +32,10 @@ namespace episim {
 namespace {
 
 constexpr int kBlock = 256;
-static_assert(kBlock == kLaneUnit, "a workgroup of one-lane-per-node kernels is one unit");
+static_assert(kBlock == kPersistUnit, "a workgroup of the persistent kernel's one-lane-per-node layout is one unit");
+constexpr int kDayBlock = 1024;  // workgroup of the one-lane-per-node day kernel
+constexpr int kDayWaves = kDayBlock / 64;
+static_assert(kDayWaves == 16, "the workgroup walk exchanges one value per lane of a row");
 constexpr int kMaxScratchDevices = 64;
 constexpr int kWaves = kBlock / 64;
 constexpr int kEvKindMask = 3;
@@ -116,13 +119,16 @@ __device__ __forceinline__ int32_t load_state(const int32_t *p) { return *p; }
 
 __device__ __forceinline__ void fresh_l1() { __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent"); }
 
+// The paired-class kernels (2 or 6 compartments and transitions) are built for
+// exactly their model; the generic ones for every model up to their size.
+constexpr bool exact_size(int n) { return n == 2 || n == 6; }
 template <int NC>
 __device__ __forceinline__ bool comp_on(const Model &m, int c) {
-    return NC != MAXC || c < m.nc;
+    return exact_size(NC) || c < m.nc;
 }
 template <int NT>
 __device__ __forceinline__ bool trans_on(const Model &m, int k) {
-    return NT != MAXT || k < m.nt;
+    return exact_size(NT) || k < m.nt;
 }
 
 // ---------------------------------------------------------------------------
@@ -144,28 +150,44 @@ struct Chain {
 };
 
 // Any stoichiometry (column k: -1 at reactant k, non-negative elsewhere).
+// Besides the counts a chain keeps the reactant counts of every transition,
+// xr[k] = X[reactant[k]] (and xr2[k] of the second reactant of a mass-action
+// rate), which the walks by many lanes update from the picks directly
+// (Model::react). Transitions past the model's have rate constant 0.
+template <int NC_, int NT_>
+struct GenericChain : Chain<NC_, NT_> {
+    double xr[NT_], xr2[NT_];
+};
+
 template <int NC_, int NT_>
 struct GenericRules {
     static constexpr int NC = NC_, NT = NT_;
-    static constexpr int kPairs = 0;
     static constexpr int kTileWaves = 2;  // waves per SIMD the replicate-tile kernel is built for
-    using State = Chain<NC, NT>;
+    using State = GenericChain<NC, NT>;
     __device__ static __forceinline__ double rate(const Model &m, const State &c, int k) {
-        double xr = 0.0, xr2 = 0.0;
-#pragma unroll
-        for (int cc = 0; cc < NC; ++cc) {
-            if (m.reactant[k] == cc) xr = c.xd[cc];
-            if (m.reactant2[k] == cc) xr2 = c.xd[cc];
-        }
-        const double w = c.cphi[k] * xr;
+        const double w = c.cphi[k] * c.xr[k];
         // a mass-action rate is also proportional to its second reactant
-        return m.reactant2[k] >= 0 ? w * xr2 : w;
+        return m.reactant2[k] >= 0 ? w * c.xr2[k] : w;
+    }
+    __device__ static __forceinline__ void reactants(const Model &m, State &c) {
+#pragma unroll
+        for (int k = 0; k < NT; ++k) {
+            double a = 0.0, b = 0.0;
+#pragma unroll
+            for (int cc = 0; cc < NC; ++cc) {
+                if (m.reactant[k] == cc) a = c.xd[cc];
+                if (m.reactant2[k] == cc) b = c.xd[cc];
+            }
+            c.xr[k] = a;
+            c.xr2[k] = b;
+        }
     }
     __device__ static __forceinline__ void rates(const Model &m, State &c) {
+        reactants(m, c);
         double lam = 0.0;
 #pragma unroll
         for (int k = 0; k < NT; ++k) {
-            if (trans_on<NT>(m, k)) lam = lam + rate(m, c, k);
+            lam = lam + rate(m, c, k);
             c.cum[k] = lam;
         }
         c.lam = lam;
@@ -179,10 +201,41 @@ struct GenericRules {
             }
         }
     }
-    // j is the same in every lane: apply it and recompute all rates
-    __device__ static __forceinline__ void apply_uniform(const Model &m, int j, State &c) {
-        apply(m, j, c);
-        rates(m, c);
+    // The walks by many lanes describe a run of picks by how often it holds
+    // each transition.
+    static constexpr int kFlows = NT;
+    __device__ static __forceinline__ void flows(int j, unsigned long long lanes, int (&n)[kFlows]) {
+#pragma unroll
+        for (int k = 0; k < NT; ++k) n[k] = __popcll(__ballot(j == k) & lanes);
+    }
+    // running sums of the rates in the state of c after the flows n (every
+    // product and sum of counts is an exact integer)
+    __device__ static __forceinline__ void cum_after(const Model &m, const State &c, const int (&n)[kFlows],
+                                                     double (&cum)[NT]) {
+        double l = 0.0;
+#pragma unroll
+        for (int k = 0; k < NT; ++k) {
+            double a = c.xr[k];
+#pragma unroll
+            for (int i = 0; i < NT; ++i) a = __builtin_fma(m.react[k][i], (double)n[i], a);
+            double w = c.cphi[k] * a;
+            if (m.reactant2[k] >= 0) {
+                double b = c.xr2[k];
+#pragma unroll
+                for (int i = 0; i < NT; ++i) b = __builtin_fma(m.react2[k][i], (double)n[i], b);
+                w = w * b;
+            }
+            l = l + w;
+            cum[k] = l;
+        }
+    }
+    __device__ static __forceinline__ void advance(const Model &m, State &c, const int (&n)[kFlows]) {
+#pragma unroll
+        for (int cc = 0; cc < NC; ++cc) {
+#pragma unroll
+            for (int k = 0; k < NT; ++k) c.xd[cc] = __builtin_fma((double)m.S[cc][k], (double)n[k], c.xd[cc]);
+        }
+        reactants(m, c);
     }
 };
 
@@ -193,7 +246,6 @@ struct GenericRules {
 template <int NP>
 struct PairRules {
     static constexpr int NC = 2 * NP, NT = 2 * NP;
-    static constexpr int kPairs = NP;
     // replicate tiles of paired classes are built for three waves per SIMD
     // (at most 168 VGPRs, with a 16-byte spill): the third wave hides the
     // latency of the chains' dependent binary64 arithmetic and of the state
@@ -204,6 +256,7 @@ struct PairRules {
     __device__ static __forceinline__ double rate(const Model &, const State &c, int k) {
         return c.cphi[k] * c.xd[k];
     }
+    __device__ static __forceinline__ void reactants(const Model &, State &) {}  // the counts themselves
     __device__ static __forceinline__ void rates(const Model &m, State &c) {
         double lam = 0.0;
 #pragma unroll
@@ -252,34 +305,7 @@ struct PairRules {
             c.xd[2 * q + 1] = c.xd[2 * q + 1] - dS;
         }
     }
-    // j is the same in every lane (a scalar): only class j/2 changes, so only
-    // the running sums from its first transition on are recomputed (the
-    // earlier ones are unchanged, so the values equal a full recomputation).
-    __device__ static __forceinline__ void apply_uniform(const Model &m, int j, State &c) {
-        const int p = j >> 1;
-        const double dS = (j & 1) ? 1.0 : -1.0;
-#pragma unroll
-        for (int q = 0; q < NP; ++q) {
-            if (q == p) {
-                c.xd[2 * q] = c.xd[2 * q] + dS;
-                c.xd[2 * q + 1] = c.xd[2 * q + 1] - dS;
-                double lam = q == 0 ? 0.0 : c.cum[2 * q - 1];
-#pragma unroll
-                for (int k = 2 * q; k < NT; ++k) {
-                    lam = lam + rate(m, c, k);
-                    c.cum[k] = lam;
-                }
-                c.lam = lam;
-            }
-        }
-    }
 };
-
-// The single-chain walk for paired classes (defined below).
-template <int NP>
-__device__ __forceinline__ void pairs_walk_block(const Model &m, Chain<2 * NP, 2 * NP> &c, uint32_t kbase,
-                                                 uint32_t node, uint32_t day, uint32_t key0, uint32_t key1,
-                                                 unsigned long long *status, int32_t r);
 
 // Inversion of eq:sampling2: the first transition with a positive rate whose
 // running sum reaches target. With target > 0 that is the number of running
@@ -299,17 +325,6 @@ __device__ __forceinline__ int invert(const Model &m, const typename Rules::Stat
             if (trans_on<NT>(m, k) && Rules::rate(m, c, k) > 0.0) j = k;
     }
     return j;
-}
-
-template <int NP>
-__device__ __forceinline__ void pairs_rates_full(Chain<2 * NP, 2 * NP> &c) {
-    double lam = 0.0;
-#pragma unroll
-    for (int k = 0; k < 2 * NP; ++k) {
-        lam = lam + c.cphi[k] * c.xd[k];
-        c.cum[k] = lam;
-    }
-    c.lam = lam;
 }
 
 // One attempt of the direct method with the draw (E, U) = (-log rand_1,
@@ -372,7 +387,9 @@ __device__ __forceinline__ double wave_prefix_sum(double v) {
 // has to be summed attempt by attempt, and so has a round in which a waiting
 // time lies exactly half-way between two multiples (ties round to even, which
 // depends on the partial sum) or whose clock is 0. Returns the number of
-// attempts that fire (-1: sum attempt by attempt) and their clock.
+// attempts that fire (-1: sum attempt by attempt) and their clock. (Going on
+// with another scan behind such an attempt is slower than the 64 additions:
+// each scan's result passes through scalar registers before the next.)
 __device__ __forceinline__ int clock_by_scan(double clock, double tau, double *clock_out) {
     const long long cb = __double_as_longlong(clock);
     const int e = (int)((cb >> 52) & 0x7ff) - 1023;
@@ -393,186 +410,308 @@ __device__ __forceinline__ int clock_by_scan(double clock, double tau, double *c
     return A;
 }
 
-// One chain walked by the whole wavefront, 64 attempts per round, for paired
-// classes. Attempt kbase + i belongs to lane i; its draws do not depend on the
-// state, but the transition it picks (eq:sampling2) and its waiting time
-// (eq:sampling) depend on the state the attempts before it leave. Each lane
-// first assumes the round's starting state, then recomputes its state from the
-// transitions the lanes below it picked (a ballot per transition and a count of
-// the set bits below the lane) and its own pick from that state, until no pick
-// changes. Lane i is settled after i + 1 passes whatever the guesses were, so
-// the result is the one attempt-by-attempt walk gives; with many individuals
-// the rates barely move and one or two passes settle every lane (and only the
-// lanes up to the first attempt surely past the window end need to). The
-// waiting times then follow in parallel, and the clock's partial sums, which
-// binary64 addition rounds one by one, come from an exact integer prefix sum
-// (clock_by_scan) or, where that does not apply, attempt by attempt. The
-// attempts whose sum stays below the window end fire; they form a prefix of
-// the lanes because the clock never decreases. Every lane holds the same
-// chain state.
-// Counts are exact integers in binary64 and the rates, running sums, targets
-// and waiting times are the same functions of the same state as in a walk
-// attempt by attempt, so the bits agree.
-template <int NP>
-__device__ __forceinline__ void pairs_walk_block(const Model &m, Chain<2 * NP, 2 * NP> &c, uint32_t kbase,
-                                                 uint32_t node, uint32_t day, uint32_t key0, uint32_t key1,
-                                                 unsigned long long *status, int32_t r) {
-    constexpr int NT = 2 * NP;
-    __shared__ double sh_tau[kWaves][64];
-    const uint32_t lane = threadIdx.x & 63u;
-    const int wave = threadIdx.x >> 6;
-    const unsigned long long below = (1ull << lane) - 1ull;
-    for (;;) {
-        const Word4 o = philox4x32_10(Word4{kbase + lane, node, day, 0u}, key0, key1);
-        const double E = minus_log(unit_open(o.a, o.b));
-        const double U = unit_open(o.c, o.d);
-        // guess: every attempt sees the round's starting state
-        int j = 0;
-        {
-            const double target = U * c.lam;
-#pragma unroll
-            for (int k = 0; k < NT; ++k) j += c.cum[k] < target ? 1 : 0;
-        }
-        double lam = c.lam;
-        int settle = 63;  // the attempts 0 .. settle need their final picks
-        for (int pass = 0; pass < 64; ++pass) {
-            double x[NT];
-#pragma unroll
-            for (int q = 0; q < NP; ++q) {
-                const int inf = __popcll(__ballot(j == 2 * q) & below);
-                const int rec = __popcll(__ballot(j == 2 * q + 1) & below);
-                const double dS = (double)(rec - inf);
-                x[2 * q] = c.xd[2 * q] + dS;
-                x[2 * q + 1] = c.xd[2 * q + 1] - dS;
-            }
-            double cum[NT];
-            double l = 0.0;
-#pragma unroll
-            for (int k = 0; k < NT; ++k) {
-                l = l + c.cphi[k] * x[k];
-                cum[k] = l;
-            }
-            // target > 0 whenever the attempt can fire: target = 0 needs
-            // lambda < 2^-1021, and then tau = E/lambda > 1 since E >= 2^-53
-            const double target = U * l;
-            int jn = 0;
-#pragma unroll
-            for (int k = 0; k < NT; ++k) jn += cum[k] < target ? 1 : 0;
-            const unsigned long long moved = __ballot(jn != j);
-            j = jn;
-            lam = l;
-            if (moved == 0ull) break;
-            if (pass == 0) continue;  // large herds settle in one or two passes without it
-            // An attempt whose clock surely lands past the window end stops
-            // the chain, so only the picks up to it have to settle. If none of
-            // them moved in this pass, they and their waiting times are those
-            // of the attempt-by-attempt walk (each was computed from the
-            // unchanged picks below it); the clock bound then comes from exact
-            // waiting times, and its margin is far above the rounding of the
-            // approximate prefix sum.
-            const double reach = c.clock + wave_prefix_sum(l > 0.0 ? E / l : __builtin_inf());
-            const unsigned long long over = __ballot(!(reach < 1.0 + 0x1p-30));
-            if (over != 0ull) {
-                const int a = __ffsll((long long)over) - 1;
-                if ((moved & (a >= 63 ? ~0ull : ((2ull << a) - 1ull))) == 0ull) {
-                    settle = a;
-                    break;
-                }
-            }
-        }
-        // lambda = 0: tau = inf, never fires; attempts past `settle` do not
-        // fire and may hold unsettled picks
-        const double tau = (int)lane > settle ? __builtin_inf() : E / lam;
-        double clock;
-        int A = clock_by_scan(c.clock, tau, &clock);
-        if (A < 0) {
-            // the clock, attempt by attempt. The waiting times go through LDS
-            // and come back as broadcast reads, which issue ahead of the
-            // dependent additions.
-            sh_tau[wave][lane] = tau;
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            double t = c.clock;
+// The clock of a wavefront's 64 attempts, attempt by attempt where the scan
+// does not apply: the waiting times go through LDS (64 values of this
+// wavefront) and come back as broadcast reads, which issue ahead of the
+// dependent additions.
+__device__ __forceinline__ int wave_clock(double s, double tau, double *sh_tau, double *clock_out) {
+    const int lane = threadIdx.x & 63;
+    int A = clock_by_scan(s, tau, clock_out);
+    if (A >= 0) return A;
+    sh_tau[lane] = tau;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    double t = s;
 #pragma unroll 16
-            for (int i = 0; i < 64; ++i) t = t + sh_tau[wave][i];
-            A = 64;
-            clock = t;
-            if (!(t < 1.0)) {
-                double s = c.clock, mine = 0.0;
+    for (int i = 0; i < 64; ++i) t = t + sh_tau[i];
+    A = 64;
+    if (!(t < 1.0)) {
+        double q = s, mine = 0.0;
 #pragma unroll 16
-                for (int i = 0; i < 64; ++i) {
-                    s = s + sh_tau[wave][i];
-                    if ((int)lane == i) mine = s;
-                }
-                A = __popcll(__ballot(mine < 1.0));
-                clock = A > 0 ? lane_f64(mine, A - 1) : c.clock;
-            }
-            __builtin_amdgcn_wave_barrier();  // the next round rewrites sh_tau
+        for (int i = 0; i < 64; ++i) {
+            q = q + sh_tau[i];
+            if (lane == i) mine = q;
         }
-        bool limit = false;
-        if (c.fired + A >= SIM_MAX_FIRED) {
-            A = SIM_MAX_FIRED - c.fired;
-            limit = true;
-        }
-        const unsigned long long fired = A >= 64 ? ~0ull : ((1ull << A) - 1ull);
-#pragma unroll
-        for (int q = 0; q < NP; ++q) {
-            const int inf = __popcll(__ballot(j == 2 * q) & fired);
-            const int rec = __popcll(__ballot(j == 2 * q + 1) & fired);
-            const double dS = (double)(rec - inf);
-            c.xd[2 * q] = c.xd[2 * q] + dS;
-            c.xd[2 * q + 1] = c.xd[2 * q + 1] - dS;
-        }
-        if (A > 0 && !limit) c.clock = clock;
-        c.fired = c.fired + A;
-        pairs_rates_full<NP>(c);
-        if (limit && lane == 0) atomicMin(status, (STATUS_LIMIT_TAG << 32) | (unsigned long long)(uint32_t)r);
-        if (limit || A < 64 || !(c.lam > 0.0)) return;
-        kbase = kbase + 64;
+        A = __popcll(__ballot(mine < 1.0));
+        t = A > 0 ? lane_f64(mine, A - 1) : s;
+    }
+    __builtin_amdgcn_wave_barrier();  // the next round rewrites sh_tau
+    *clock_out = t;
+    return A;
+}
+
+// Prefix sums over segments of G lanes (in any order of addition).
+template <int G>
+__device__ __forceinline__ double segment_prefix_sum(double v, int li) {
+    if constexpr (G == 64) {
+        return wave_prefix_sum(v);
+    } else {
+        static_assert(G == 8 || G == 16, "segments lie within rows of 16 lanes");
+        double u = dpp_f64<0x111, 0xf>(v);  // row_shr:1
+        v = v + (G == 16 || li >= 1 ? u : 0.0);
+        u = dpp_f64<0x112, 0xf>(v);  // row_shr:2
+        v = v + (G == 16 || li >= 2 ? u : 0.0);
+        u = dpp_f64<0x114, 0xf>(v);  // row_shr:4
+        v = v + (G == 16 || li >= 4 ? u : 0.0);
+        if constexpr (G == 16) v = v + dpp_f64<0x118, 0xf>(v);  // row_shr:8
+        return v;
     }
 }
 
-// One chain walked by all wavefronts of a workgroup, kBlock attempts per round
-// (attempt kbase + t for thread t): the scheme of pairs_walk_block, with the
-// picks of each wavefront shared in LDS as its flows (Rules::flows), so that
-// an attempt's state is the round's state after the flows of the wavefronts
-// below and of the lanes below in its own. One barrier per pass: a wavefront
-// publishes its flows together with whether its picks moved in the pass
-// before, and a pass that finds no wavefront moved ends the round.
+// The walks by several lanes. Attempt kbase + i of a chain belongs to lane i of
+// the chain's segment of G lanes (64: the whole wavefront; 16 or 8: as many
+// chains side by side as segments), G attempts a round. An attempt's draws do
+// not depend on the state, but the transition it picks (eq:sampling2) and its
+// waiting time (eq:sampling) depend on the state the attempts before it leave.
+// Each lane first assumes the round's starting state, then recomputes its
+// state from the transitions the lanes below it picked (Rules::flows: a ballot
+// per transition and a count of the set bits below the lane) and its own pick
+// from that state, until no pick changes. Lane i is settled after i + 1 passes
+// whatever the guesses were, so the result is the one attempt-by-attempt walk
+// gives; with many individuals the rates barely move and one or two passes
+// settle every lane (and only the lanes up to the first attempt surely past
+// the window end need to). The waiting times then follow in parallel. The
+// clock's partial sums, which binary64 addition rounds one by one, come from
+// exact integer prefix sums or attempt by attempt from LDS. The attempts whose sum stays below the window end fire;
+// they form a prefix of the lanes because the clock never decreases. Every lane
+// of a segment holds the same chain state.
+// Counts are exact integers in binary64 and the rates, running sums, targets
+// and waiting times are the same functions of the same state as in a walk
+// attempt by attempt, so the bits agree.
+struct Draw {
+    double E, U;  // -log rand_1, rand_2
+};
+
+__device__ __forceinline__ Draw draw_attempt(uint32_t k, uint32_t node, uint32_t day, uint32_t key0, uint32_t key1) {
+    const Word4 o = philox4x32_10(Word4{k, node, day, 0u}, key0, key1);
+    return Draw{minus_log(unit_open(o.a, o.b)), unit_open(o.c, o.d)};
+}
+
+// The pick of an attempt in the state of c after the flows n, and its lambda.
+template <class Rules>
+__device__ __forceinline__ int pick_after(const Model &m, const typename Rules::State &c, const int (&n)[Rules::kFlows],
+                                          double U, double *lam) {
+    double cum[Rules::NT];
+    Rules::cum_after(m, c, n, cum);
+    // target > 0 whenever the attempt can fire: target = 0 needs
+    // lambda < 2^-1021, and then tau = E/lambda > 1 since E >= 2^-53
+    const double target = U * cum[Rules::NT - 1];
+    int j = 0;
+#pragma unroll
+    for (int k = 0; k < Rules::NT; ++k) j += cum[k] < target ? 1 : 0;
+    *lam = cum[Rules::NT - 1];
+    return j;
+}
+
+// Passes over the picks j until those that can fire no longer change; returns
+// the last attempt of the segment with a settled pick.
+template <class Rules, int G>
+__device__ __forceinline__ int settle_picks(const Model &m, const typename Rules::State &c, Draw q, int first_pass,
+                                            int &j, double &lam) {
+    constexpr int K = Rules::kFlows;
+    const int lane = threadIdx.x & 63, li = lane & (G - 1), seg0 = lane - li;
+    const unsigned long long seg = G == 64 ? ~0ull : (((1ull << (G & 63)) - 1ull) << seg0);
+    const unsigned long long below = seg & ((1ull << lane) - 1ull);
+    for (int pass = first_pass; pass < 64; ++pass) {
+        int n[K];
+        Rules::flows(j, below, n);
+        const int jn = pick_after<Rules>(m, c, n, q.U, &lam);
+        const unsigned long long moved = __ballot(jn != j);
+        j = jn;
+        if (moved == 0ull) break;
+        if (pass == 0) continue;  // large herds settle in one or two passes without it
+        // An attempt whose clock surely lands past the window end stops the
+        // chain, so only the picks up to it have to settle. If none of them
+        // moved in this pass, they and their waiting times are those of the
+        // attempt-by-attempt walk (each was computed from the unchanged picks
+        // below it); the clock bound then comes from exact waiting times, and
+        // its margin is far above the rounding of the approximate prefix sum.
+        const double reach = c.clock + segment_prefix_sum<G>(lam > 0.0 ? q.E / lam : __builtin_inf(), li);
+        const unsigned long long over = __ballot(!(reach < 1.0 + 0x1p-30)) & seg;
+        const int a = over != 0ull ? __ffsll((long long)over) - 1 : seg0 + G - 1;
+        const unsigned long long upto = a >= 63 ? ~0ull : ((2ull << a) - 1ull);
+        if (__ballot((moved & seg & upto) != 0ull) == 0ull) return a - seg0;
+    }
+    return G - 1;
+}
+
+// The first A attempts of each segment fire, with picks j; their clock.
+// Returns whether the chain has reached SIM_MAX_FIRED (A is cut there).
+template <class Rules, int G>
+__device__ __forceinline__ bool fire_attempts(const Model &m, typename Rules::State &c, int j, int &A, double clock,
+                                              unsigned long long *status, int32_t r) {
+    const int lane = threadIdx.x & 63, li = lane & (G - 1), seg0 = lane - li;
+    bool limit = false;
+    if (c.fired + A >= SIM_MAX_FIRED) {
+        A = SIM_MAX_FIRED - c.fired;
+        limit = true;
+    }
+    int n[Rules::kFlows];
+    Rules::flows(j, (A >= 64 ? ~0ull : ((1ull << A) - 1ull)) << seg0, n);
+    Rules::advance(m, c, n);
+    if (A > 0 && !limit) c.clock = clock;
+    c.fired = c.fired + A;
+    if (limit && li == 0) atomicMin(status, (STATUS_LIMIT_TAG << 32) | (unsigned long long)(uint32_t)r);
+    return limit;
+}
+
+// One round of the chains of a wavefront's segments. Returns whether the
+// segment's chain has ended (a chain whose rates are all 0 ends in its next
+// round); a segment without a chain passes rate constants of 0. sh_tau: 64
+// values of this wavefront.
+template <class Rules, int G>
+__device__ __forceinline__ bool walk_round(const Model &m, typename Rules::State &c, uint32_t kbase, uint32_t node,
+                                           uint32_t day, uint32_t key0, uint32_t key1, unsigned long long *status,
+                                           int32_t r, double *sh_tau) {
+    const int lane = threadIdx.x & 63, li = lane & (G - 1), seg0 = lane - li;
+    const Draw q = draw_attempt(kbase + (uint32_t)li, node, day, key0, key1);
+    int n[Rules::kFlows];
+#pragma unroll
+    for (int k = 0; k < Rules::kFlows; ++k) n[k] = 0;
+    double lam;
+    int j = pick_after<Rules>(m, c, n, q.U, &lam);  // guess: every attempt sees the round's starting state
+    const int settled = settle_picks<Rules, G>(m, c, q, 0, j, lam);
+    // lambda = 0: tau = inf, never fires; attempts past the settled ones do
+    // not fire and may hold unsettled picks
+    const double tau = li > settled ? __builtin_inf() : q.E / lam;
+    // the clock, attempt by attempt. The waiting times go through LDS and come
+    // back as broadcast reads, which issue ahead of the dependent additions.
+    sh_tau[lane] = tau;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    double clock = c.clock, t = c.clock;
+    int A = 0;
+    for (int i0 = 0; i0 < G; i0 += 8) {
+#pragma unroll
+        for (int i = i0; i < i0 + 8; ++i) {
+            t = t + sh_tau[seg0 + i];
+            const bool in = t < 1.0;
+            clock = in ? t : clock;
+            A += in ? 1 : 0;
+        }
+        if (__ballot(t < 1.0) == 0ull) break;  // every segment's clock is past the window end
+    }
+    __builtin_amdgcn_wave_barrier();  // the next round rewrites sh_tau
+    return fire_attempts<Rules, G>(m, c, j, A, clock, status, r) || A < G;
+}
+
+// One chain walked to the end of the window by the whole wavefront, every lane
+// holding the same state, from attempt kbase on. sh_tau: 64 values of this
+// wavefront.
+template <class Rules>
+__device__ __forceinline__ void walk_wave(const Model &m, typename Rules::State &c, uint32_t kbase, uint32_t node,
+                                          uint32_t day, uint32_t key0, uint32_t key1, unsigned long long *status,
+                                          int32_t r, double *sh_tau) {
+    const int lane = threadIdx.x & 63;
+    for (;; kbase = kbase + 64) {
+        const Draw q = draw_attempt(kbase + (uint32_t)lane, node, day, key0, key1);
+        int n[Rules::kFlows];
+#pragma unroll
+        for (int k = 0; k < Rules::kFlows; ++k) n[k] = 0;
+        double lam;
+        int j = pick_after<Rules>(m, c, n, q.U, &lam);  // guess: the round's starting state
+        const int settled = settle_picks<Rules, 64>(m, c, q, 0, j, lam);
+        const double tau = lane > settled ? __builtin_inf() : q.E / lam;
+        double clock;
+        int A = wave_clock(c.clock, tau, sh_tau, &clock);
+        if (fire_attempts<Rules, 64>(m, c, j, A, clock, status, r) || A < 64) return;
+    }
+}
+
+// Inclusive prefix sums within rows of 16 lanes.
+__device__ __forceinline__ int32_t row_prefix_sum(int32_t v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    return v;
+}
+__device__ __forceinline__ double row_prefix_sum(double v) {
+    v = v + dpp_f64<0x111, 0xf>(v);
+    v = v + dpp_f64<0x112, 0xf>(v);
+    v = v + dpp_f64<0x114, 0xf>(v);
+    v = v + dpp_f64<0x118, 0xf>(v);
+    return v;
+}
+
+// One chain walked by the sixteen wavefronts of a workgroup, kDayBlock attempts
+// per round (attempt kbase + t for thread t): the scheme of walk_round, with
+// the picks of each wavefront shared in LDS as its flows (Rules::flows), so
+// that an attempt's state is the round's state after the flows of the
+// wavefronts below and of the lanes below in its own. One barrier per pass: a
+// wavefront publishes its flows (two to a word) together with whether its picks
+// moved in the pass before; lane w of every row then reads wavefront w's words
+// and the sums over the wavefronts are row prefix sums; a pass that finds no
+// wavefront moved ends the round.
 // The clock follows the rule of clock_by_scan, in every wavefront at once:
-// prefix sums within the wavefronts and the wavefronts' totals through LDS give
-// every partial sum of the binade; an attempt whose sum leaves the binade, or
-// that lies half-way between two multiples, is added as the serial walk adds
-// it, and the scan goes on behind it in the binade of the new sum. A chain's
-// first kHeadAttempts attempts, most of whose sums are the first in their
-// binade, are added one by one from LDS.
-// A round takes about 6,000 cycles, most of them the latency of dependent
-// binary64 arithmetic and of LDS (one wavefront a SIMD): 10 ns an attempt
-// against 13 with the clock decided by one wavefront while three waited and two
-// barriers a pass (37k network, u = 10, 120 days: 47.1 -> 30.4 ms).
+// prefix sums within the wavefronts and over their totals give every partial
+// sum of the binade; an attempt whose sum leaves the binade, or that lies
+// half-way between two multiples, is added as the serial walk adds it, and the
+// scan goes on behind it in the binade of the new sum. A chain's first 64
+// attempts, most of whose sums are the first in their binade, are added one by
+// one by the first wavefront.
+// With one wavefront a SIMD a round takes about 6,000 cycles, nearly all of it
+// the latency of dependent binary64 arithmetic and of LDS; four wavefronts a
+// SIMD take little longer for four times the attempts, until the SIMDs' issue
+// binds.
 // Every thread of the workgroup calls it with the same state and ends with the
-// same state. A round starts only while the window still expects min_attempts
-// attempts (lambda (1 - clock)), and a round whose picks do not settle within
-// kGroupPasses passes is dropped. Returns whether the chain is done; if not,
-// the caller continues with the single-wavefront walk from attempt kbase and
-// state c, which are those at the start of a round.
+// same state. A round starts only while the window still expects
+// kGroupRest attempts (lambda (1 - clock)), and a round whose picks do not
+// settle within kGroupPasses passes is dropped. Returns whether the chain is
+// done; if not, the caller continues with one wavefront from attempt kbase
+// and state c, which are those at the start of a round.
 constexpr int kGroupPasses = 8;
-constexpr int kHeadAttempts = 16;
+constexpr double kGroupRest = 24.0;
 
 template <class Rules>
 __device__ bool walk_group(const Model &m, typename Rules::State &c, uint32_t &kbase, uint32_t node, uint32_t day,
-                           uint32_t key0, uint32_t key1, unsigned long long *status, int32_t r, double min_attempts) {
+                           uint32_t key0, uint32_t key1, unsigned long long *status, int32_t r) {
     constexpr int NT = Rules::NT, K = Rules::kFlows;
-    constexpr int kRound = kBlock;
-    __shared__ int32_t sh_flow[2][kWaves][K], sh_moved[2][kWaves];
-    __shared__ double sh_head[kHeadAttempts], sh_total[kWaves], sh_before, sh_at;
-    __shared__ int32_t sh_tie[kWaves], sh_special;
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    constexpr int kRound = kDayBlock, kWords = (K + 2) / 2;  // flows and the moved mark, two to a word
+    __shared__ int32_t sh_flow[2][kWords][kDayWaves];
+    __shared__ double sh_head[64], sh_total[kDayWaves], sh_before, sh_at;
+    __shared__ int32_t sh_tie[kDayWaves], sh_special;
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const unsigned long long below = (1ull << lane) - 1ull;
     int buf = 0;
+    // publish this wavefront's flows n (and mark); after the barrier, before[]
+    // and all[] are the flows of the wavefronts below and of all; returns
+    // whether any wavefront set its mark
+    auto exchange = [&](const int (&n)[K], bool mark, int (&before)[K], int (&all)[K]) {
+        int f[2 * kWords];
+#pragma unroll
+        for (int k = 0; k < 2 * kWords; ++k) f[k] = 0;
+#pragma unroll
+        for (int k = 0; k < K; ++k) f[k] = n[k];
+        f[K] = mark ? 1 : 0;
+        if (lane == 0) {
+#pragma unroll
+            for (int w = 0; w < kWords; ++w) sh_flow[buf][w][wave] = f[2 * w] + f[2 * w + 1] * 65536;
+        }
+        __syncthreads();
+        int lo[2 * kWords], hi[2 * kWords];  // |sums| <= 1024 fit the halves
+#pragma unroll
+        for (int w = 0; w < kWords; ++w) {
+            const int32_t v = row_prefix_sum(sh_flow[buf][w][lane & 15]);
+            const int32_t a = wave > 0 ? __builtin_amdgcn_readlane(v, wave > 0 ? wave - 1 : 0) : 0;
+            const int32_t z = __builtin_amdgcn_readlane(v, kDayWaves - 1);
+            lo[2 * w] = (int32_t)(int16_t)(a & 0xffff);
+            lo[2 * w + 1] = (a - lo[2 * w]) >> 16;
+            hi[2 * w] = (int32_t)(int16_t)(z & 0xffff);
+            hi[2 * w + 1] = (z - hi[2 * w]) >> 16;
+        }
+        buf ^= 1;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            before[k] = lo[k];
+            all[k] = hi[k];
+        }
+        return hi[K] != 0;
+    };
     for (;;) {
-        if (c.lam * (1.0 - c.clock) < min_attempts) return false;  // the same in every thread
+        if (!(c.lam * (1.0 - c.clock) >= kGroupRest)) return false;  // the same in every thread
         const Word4 o = philox4x32_10(Word4{kbase + (uint32_t)t, node, day, 0u}, key0, key1);
         const double E = minus_log(unit_open(o.a, o.b));
         const double U = unit_open(o.c, o.d);
@@ -587,33 +726,16 @@ __device__ bool walk_group(const Model &m, typename Rules::State &c, uint32_t &k
         bool settled = false, moved = true;
         int all[K];
         for (int pass = 0; pass < kGroupPasses; ++pass) {
-            int n[K];
+            int n[K], before[K];
             Rules::flows(j, ~0ull, n);
-            if (lane == 0) {
-#pragma unroll
-                for (int k = 0; k < K; ++k) sh_flow[buf][wave][k] = n[k];
-                sh_moved[buf][wave] = moved ? 1 : 0;
-            }
-            __syncthreads();
-            bool any = false;
-            Rules::flows(j, below, n);
-#pragma unroll
-            for (int k = 0; k < K; ++k) all[k] = 0;
-#pragma unroll
-            for (int w = 0; w < kWaves; ++w) {
-                any = any || sh_moved[buf][w] != 0;
-#pragma unroll
-                for (int k = 0; k < K; ++k) {
-                    const int f = sh_flow[buf][w][k];
-                    all[k] += f;
-                    n[k] += w < wave ? f : 0;
-                }
-            }
-            buf ^= 1;
+            const bool any = exchange(n, moved, before, all);
             if (!any) {  // the picks are those the waiting rates lam were computed from
                 settled = true;
                 break;
             }
+            Rules::flows(j, below, n);
+#pragma unroll
+            for (int k = 0; k < K; ++k) n[k] += before[k];
             double cum[NT];
             Rules::cum_after(m, c, n, cum);
             lam = cum[NT - 1];
@@ -630,16 +752,29 @@ __device__ bool walk_group(const Model &m, typename Rules::State &c, uint32_t &k
         int done = 0;        // attempts before done fire; s is the clock after them
         bool ended = false;  // attempt done does not fire
         if (!(s > 0.0)) {
-            if (t < kHeadAttempts) sh_head[t] = tau;
-            __syncthreads();
-            for (; done < kHeadAttempts; ++done) {
-                const double s2 = s + sh_head[done];
-                if (!(s2 < 1.0)) {
-                    ended = true;
-                    break;
+            if (wave == 0) {
+                sh_head[lane] = tau;
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                double q = s, z = s;
+                int A = 0;
+#pragma unroll 16
+                for (int i = 0; i < 64; ++i) {
+                    q = q + sh_head[i];
+                    const bool in = q < 1.0;
+                    z = in ? q : z;
+                    A += in ? 1 : 0;
                 }
-                s = s2;
+                if (lane == 0) {
+                    sh_before = z;
+                    sh_special = A;
+                }
             }
+            __syncthreads();
+            s = sh_before;
+            done = sh_special;
+            ended = done < 64;
         }
         while (!ended && done < kRound) {
             const int e = (int)((__double_as_longlong(s) >> 52) & 0x7ff) - 1023;
@@ -655,29 +790,24 @@ __device__ bool walk_group(const Model &m, typename Rules::State &c, uint32_t &k
             const double P = wave_prefix_sum(live ? (fr > 0.5 ? fl + 1.0 : fl) : 0.0);
             const bool tie = live && fr == 0.5;
             const unsigned long long ties = __ballot(tie);
-            const double total = lane_f64(P, 63);
-            if (lane == 0) {
-                sh_total[wave] = total;
+            if (lane == 63) {
+                sh_total[wave] = P;
                 sh_tie[wave] = ties != 0ull ? 1 : 0;
             }
             __syncthreads();
-            double carry = 0.0, mine = 0.0;
-            int first = kWaves;  // the first wavefront with a sum past the binade or a tie
-#pragma unroll
-            for (int w = 0; w < kWaves; ++w) {
-                if (w == wave) mine = carry;
-                carry = carry + sh_total[w];
-                if (first == kWaves && (sh_tie[w] != 0 || !(carry < T))) first = w;
-            }
-            if (first == kWaves) {
-                s = (S0 + carry) * down;
+            const double sums = row_prefix_sum(sh_total[lane & 15]);
+            // the first wavefront with a sum past the binade or a tie
+            const uint32_t odd = (uint32_t)__ballot(sh_tie[lane & 15] != 0 || !(sums < T)) & 0xffffu;
+            if (odd == 0u) {
+                s = (S0 + lane_f64(sums, kDayWaves - 1)) * down;
                 done = kRound;
                 break;
             }
-            if (wave == first) {
+            if (wave == __builtin_ctz(odd)) {
+                const double mine = wave > 0 ? lane_f64(sums, wave > 0 ? wave - 1 : 0) : 0.0;
                 const double Pg = P + mine;
                 const int sp = __ffsll((long long)__ballot(tie || (live && !(Pg < T)))) - 1;
-                const double prior = sp > 0 ? lane_f64(Pg, max(sp, 1) - 1) : mine;
+                const double prior = sp > 0 ? lane_f64(Pg, sp > 0 ? sp - 1 : 0) : mine;
                 if (lane == sp) {
                     sh_at = tau;
                     sh_before = (S0 + prior) * down;
@@ -699,19 +829,9 @@ __device__ bool walk_group(const Model &m, typename Rules::State &c, uint32_t &k
         }
         if (A < kRound) {
             const int nw = A - 64 * wave;
-            int n[K];
+            int n[K], before[K];
             Rules::flows(j, nw >= 64 ? ~0ull : (nw > 0 ? ((1ull << nw) - 1ull) : 0ull), n);
-            if (lane == 0) {
-#pragma unroll
-                for (int k = 0; k < K; ++k) sh_flow[buf][wave][k] = n[k];
-            }
-            __syncthreads();
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-                all[k] = 0;
-#pragma unroll
-                for (int w = 0; w < kWaves; ++w) all[k] += sh_flow[buf][w][k];
-            }
+            exchange(n, false, before, all);
         }
         Rules::advance(m, c, all);
         if (A > 0 && !limit) c.clock = s;
@@ -726,33 +846,62 @@ __device__ bool walk_group(const Model &m, typename Rules::State &c, uint32_t &k
     }
 }
 
-// A single live chain, run by the whole wavefront with every lane holding
-// the same state: lane i computes attempt kbase + i, and the attempts are
-// walked in order with the chosen transition held in a scalar register.
-template <class Rules>
-__device__ __forceinline__ void chain_uniform(const Model &m, typename Rules::State &c, uint32_t kbase,
-                                              uint32_t node, uint32_t day, uint32_t key0, uint32_t key1,
-                                              unsigned long long *status, int32_t r) {
-    const uint32_t lane = threadIdx.x & 63u;
+// Chains of a queue walked side by side by the segments of a wavefront, G
+// lanes each, a segment taking the next chain when its own ends: take(k)
+// claims the next k queue entries for this wavefront and returns the first
+// (entries from n on do not exist), load(i, c, key) fills in chain i, store(i,
+// c) takes its end state. G balances what a round does for one chain (short
+// chains leave the lanes past their end idle) against the rounds that its
+// longest chain needs.
+struct ChainKey {
+    uint32_t kbase, node, day, key0, key1;
+    unsigned long long *status;
+    int32_t r;
+};
+
+template <class Rules, int G, class Take, class Load, class Store>
+__device__ __forceinline__ void walk_queue(const Model &m, int n, double *sh_tau, const Take &take, const Load &load,
+                                           const Store &store) {
+    const int lane = threadIdx.x & 63, li = lane & (G - 1), seg0 = lane - li;
+    typename Rules::State c;
+    ChainKey key{0u, 0u, 0u, 0u, 0u, nullptr, 0};
+    auto none = [&]() {
+#pragma unroll
+        for (int k = 0; k < Rules::NC; ++k) c.xd[k] = 0.0;
+#pragma unroll
+        for (int k = 0; k < Rules::NT; ++k) c.cphi[k] = 0.0;
+        c.clock = 0.0;
+        c.fired = 0;
+        Rules::reactants(m, c);
+    };
+    none();
+    int at = -1;  // the segment's chain
+    bool dry = false;
     for (;;) {
-        const Word4 o = philox4x32_10(Word4{kbase + lane, node, day, 0u}, key0, key1);
-        const double e_mine = minus_log(unit_open(o.a, o.b));
-        const double u_mine = unit_open(o.c, o.d);
-        for (int i = 0; i < 64; ++i) {
-            const double tau = lane_f64(e_mine, i) / c.lam;
-            const double t1 = c.clock + tau;
-            const int j = __builtin_amdgcn_readfirstlane(invert<Rules>(m, c, lane_f64(u_mine, i) * c.lam));
-            if (!(t1 < 1.0)) return;
-            c.clock = t1;
-            Rules::apply_uniform(m, j, c);
-            c.fired = c.fired + 1;
-            if (c.fired >= SIM_MAX_FIRED) {
-                if (lane == 0) atomicMin(status, (STATUS_LIMIT_TAG << 32) | (unsigned long long)(uint32_t)r);
-                return;
+        if (!dry) {
+            const unsigned long long idle = __ballot(at < 0 && li == 0);
+            if (idle != 0ull) {
+                const int k = __popcll(idle), first = take(k);
+                if (at < 0) {
+                    const int i = first + __popcll(idle & ((1ull << seg0) - 1ull));
+                    if (i < n) {
+                        at = i;
+                        load(i, c, key);
+                        Rules::reactants(m, c);
+                    }
+                }
+                dry = first + k >= n;
             }
-            if (!(c.lam > 0.0)) return;
         }
-        kbase = kbase + 64;
+        if (__ballot(at >= 0) == 0ull) break;
+        const bool done = walk_round<Rules, G>(m, c, key.kbase, key.node, key.day, key.key0, key.key1, key.status,
+                                               key.r, sh_tau);
+        key.kbase = key.kbase + (uint32_t)G;
+        if (at >= 0 && done) {
+            if (li == 0) store(at, c);
+            at = -1;
+            none();
+        }
     }
 }
 
@@ -763,7 +912,7 @@ __device__ __forceinline__ void chain_uniform(const Model &m, typename Rules::St
 // live lane then walks its own in order. With all 64 lanes live each lane
 // draws its own block; with one chain left, or at most `few` of which one
 // still expects many attempts, the whole wavefront walks them one after
-// another (pairs_walk_block). Node, day and key are each lane's own (lanes of
+// another (walk_wave). Node, day and key are each lane's own (lanes of
 // a slot handle may be at different days). Every lane of the wavefront must
 // call this.
 template <class Rules>
@@ -773,6 +922,7 @@ __device__ __forceinline__ void run_chains(const Model &m, typename Rules::State
     __shared__ double sh_e[kWaves][64], sh_u[kWaves][64];
     __shared__ uint32_t sh_node[kWaves][64], sh_key[kWaves][64], sh_seed[kWaves][64], sh_k[kWaves][64];
     __shared__ uint32_t sh_day[kWaves][64];
+    __shared__ double sh_tau[kWaves][64];
     const int wave = threadIdx.x >> 6;
     const uint32_t lane = threadIdx.x & 63u;
     uint32_t kbase = 0;  // next attempt index of this lane's chain
@@ -800,7 +950,6 @@ __device__ __forceinline__ void run_chains(const Model &m, typename Rules::State
 #pragma unroll
             for (int k = 0; k < Rules::NT; ++k) {
                 u.cphi[k] = lane_f64(c.cphi[k], h);
-                u.cum[k] = lane_f64(c.cum[k], h);
             }
             u.lam = lane_f64(c.lam, h);
             u.clock = lane_f64(c.clock, h);
@@ -815,11 +964,8 @@ __device__ __forceinline__ void run_chains(const Model &m, typename Rules::State
             const uint32_t k0 = (uint32_t)__builtin_amdgcn_readlane((int)key0, h);
             const uint32_t k1 = (uint32_t)__builtin_amdgcn_readlane((int)key1, h);
             const int32_t rh = __builtin_amdgcn_readlane(r, h);
-            if constexpr (Rules::kPairs > 0) {
-                pairs_walk_block<Rules::kPairs>(m, u, kb, nh, dh, k0, k1, sth, rh);
-            } else {
-                chain_uniform<Rules>(m, u, kb, nh, dh, k0, k1, sth, rh);
-            }
+            Rules::reactants(m, u);
+            walk_wave<Rules>(m, u, kb, nh, dh, k0, k1, sth, rh, sh_tau[wave]);
             if ((int)lane == h) c = u;
         }
         if (few) break;
@@ -1024,62 +1170,6 @@ __device__ void flush_tile(const Model &m, const DevState &s, const Tally<NC> &t
     __syncthreads();
 }
 
-// The SSA of a workgroup whose only herd sits in thread 0 (one lane per node):
-// with paired classes its chain is walked by all four wavefronts, otherwise
-// as anywhere else. Every thread of the workgroup calls it.
-template <class Rules>
-__device__ void group_chain(const Model &m, typename Rules::State &c, bool live, uint32_t node, uint32_t day,
-                            uint32_t key0, uint32_t key1, unsigned long long *status, int32_t r,
-                            uint32_t few_chains, double min_attempts) {
-    if constexpr (Rules::kPairs == 0) {
-        run_chains<Rules>(m, c, live, node, day, key0, key1, status, r, few_chains);
-    } else {
-        constexpr int NT = Rules::NT;
-        __shared__ double sh_x[NT], sh_cphi[NT], sh_cum[NT], sh_lam;
-        __shared__ uint32_t sh_key[4];
-        __shared__ int sh_go;
-        if (threadIdx.x == 0) {
-#pragma unroll
-            for (int k = 0; k < NT; ++k) {
-                sh_x[k] = c.xd[k];
-                sh_cphi[k] = c.cphi[k];
-                sh_cum[k] = c.cum[k];
-            }
-            sh_lam = c.lam;
-            sh_key[0] = node;
-            sh_key[1] = key0;
-            sh_key[2] = key1;
-            sh_key[3] = (uint32_t)r;
-            sh_go = live && c.lam > 0.0 ? 1 : 0;
-        }
-        __syncthreads();
-        if (!sh_go) return;  // the same in every thread
-        // the day's critical chain: its wavefronts issue ahead of the other
-        // waves on their SIMDs while it is walked
-        __builtin_amdgcn_s_setprio(3);
-        typename Rules::State u;
-#pragma unroll
-        for (int k = 0; k < NT; ++k) {
-            u.xd[k] = sh_x[k];
-            u.cphi[k] = sh_cphi[k];
-            u.cum[k] = sh_cum[k];
-        }
-        u.lam = sh_lam;
-        u.clock = 0.0;
-        u.fired = 0;
-        uint32_t kb = 0;
-        // a short chain, or the end of a long one, is walked by wavefront 0
-        // (thread 0 is in it)
-        if (!walk_group<Rules>(m, u, kb, sh_key[0], day, sh_key[1], sh_key[2], status, (int32_t)sh_key[3],
-                               min_attempts) &&
-            threadIdx.x < 64)
-            pairs_walk_block<Rules::kPairs>(m, u, kb, sh_key[0], day, sh_key[1], sh_key[2], status,
-                                            (int32_t)sh_key[3]);
-        __builtin_amdgcn_s_setprio(0);
-        if (threadIdx.x == 0) c = u;
-    }
-}
-
 // Per-lane parameters of a replicate tile, staged in LDS once per tile (every
 // position of a tile belongs to one instance, so lane r has the same set):
 // rate constants, shedding and decay rates and the Philox key.
@@ -1198,29 +1288,35 @@ __device__ __forceinline__ LaneLoad<NC> lane_load(const Model &m, const DevState
     return q;
 }
 
-// What a kernel may add to day_wave: after_prologue() runs on every lane once
-// the previous day is closed, before the SSA; after_ssa(state, active) sees the
-// lane's chain state after the SSA and returns whether day_wave stores it.
-struct NoHooks {
-    __device__ void after_prologue() const {}
-    template <class St>
-    __device__ bool after_ssa(const St &, bool) const { return true; }
-};
+// phi_{d+1} = (1 - beta(day0 + d)) phi_d + alpha I/N (eq:siminfpressure, Euler
+// step) from the counts y, and I.
+template <int NC>
+__device__ __forceinline__ double phi_next(const Model &m, const int32_t *y, double alpha, double beta, double phi,
+                                           long long *Iout) {
+    long long I = 0, N = 0;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        if ((m.imask >> c) & 1u) I += y[c];
+        if ((m.nmask >> c) & 1u) N += y[c];
+    }
+    *Iout = I;
+    const double a = 1.0 - beta;
+    const double b = a * phi;
+    const double shed = N > 0 ? alpha * ((double)I / (double)N) : 0.0;
+    return b + shed;
+}
 
 // The day phase for the lane l of a wavefront (every lane of the wavefront
 // must call it; lanes with l >= L or replicate lane r >= r_end take part in
 // the wavefront-level steps only): close day d-1 (phi update + record) if
 // prologue, then run the SSA of day d if ssa. Adds the lane's counts to t.
-// uniform_set >= 0 is the set of every lane (a workgroup of one instance and
-// one replicate), so that its parameters are read without waiting for the
-// lane's instance. Every load that does not depend on another is issued
-// first (padding positions hold zeros).
-template <class Rules, class Hooks = NoHooks>
+// Every load that does not depend on another is issued first (padding
+// positions hold zeros).
+template <class Rules>
 __device__ __forceinline__ void day_wave(const Model &m, const DevState &s, int64_t l, int32_t d,
                                          bool prologue, bool ssa, Tally<Rules::NC> &t, int32_t r_end,
                                          unsigned long long *status, const TileParams *tp = nullptr,
-                                         const Hooks &hooks = Hooks{}, int32_t uniform_set = -1,
-                                         bool group_walk = false, bool lane_on = true) {
+                                         bool lane_on = true) {
     constexpr int NC = Rules::NC, NT = Rules::NT;
     const int32_t R = s.R, RL = s.RL;
     const bool in_range = l < s.L;
@@ -1240,23 +1336,13 @@ __device__ __forceinline__ void day_wave(const Model &m, const DevState &s, int6
 #pragma unroll
         for (int c = 0; c < NC; ++c) x[c] = 0;
     }
-    const int32_t set = uniform_set >= 0 ? uniform_set : inst * R + r;
+    const int32_t set = inst * R + r;
     const uint32_t node = active ? (uint32_t)nid : 0u;
-    // phi_{d+1} = (1 - beta(day0 + d)) phi_d + alpha I/N (eq:siminfpressure, Euler step)
-    auto phi_next = [&](const int32_t *y, int32_t dd, double ph, long long *Iout) {
-        long long I = 0, N = 0;
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            if ((m.imask >> c) & 1u) I += y[c];
-            if ((m.nmask >> c) & 1u) N += y[c];
-        }
-        *Iout = I;
+    auto phi_after = [&](const int32_t *y, int32_t dd, double ph, long long *Iout) {
         const int q = season((int64_t)m.day0 + dd);
         const int lane = threadIdx.x & 63;
-        const double a = 1.0 - (tp ? tp->beta[q][lane] : s.beta[set * 4 + q]);
-        const double b = a * ph;
-        const double shed = N > 0 ? (tp ? tp->alpha[lane] : s.alpha[set]) * ((double)I / (double)N) : 0.0;
-        return b + shed;
+        return phi_next<NC>(m, y, tp ? tp->alpha[lane] : s.alpha[set], tp ? tp->beta[q][lane] : s.beta[set * 4 + q], ph,
+                            Iout);
     };
     if (active && prologue) {
         const double phi_in = phi;
@@ -1268,7 +1354,7 @@ __device__ __forceinline__ void day_wave(const Model &m, const DevState &s, int6
             for (int c = 0; c < NC; ++c)
                 if ((m.imask >> c) & 1u) I += x[c];
         } else {
-            phi = phi_next(x, dp, phi, &I);
+            phi = phi_after(x, dp, phi, &I);
         }
         t.prev += I > 0 ? 1 : 0;
 #pragma unroll
@@ -1283,7 +1369,6 @@ __device__ __forceinline__ void day_wave(const Model &m, const DevState &s, int6
         }
         if (__double_as_longlong(phi) != __double_as_longlong(phi_in)) s.phi[l] = phi;
     }
-    hooks.after_prologue();
     // d, prologue and ssa may differ between the lanes of a slot handle's
     // wavefront: a lane without the SSA today takes part with no live chain
     if (__ballot(ssa) == 0ull) return;
@@ -1303,14 +1388,10 @@ __device__ __forceinline__ void day_wave(const Model &m, const DevState &s, int6
     ch.clock = 0.0;
     ch.fired = 0;
     Rules::rates(m, ch);
-    if (group_walk)
-        group_chain<Rules>(m, ch, walks, node, (uint32_t)d, key0, key1, status, set, s.few_chains,
-                           s.group_min_attempts);
-    else
-        run_chains<Rules>(m, ch, walks, node, (uint32_t)d, key0, key1, status, set, s.few_chains);
+    run_chains<Rules>(m, ch, walks, node, (uint32_t)d, key0, key1, status, set, s.few_chains);
     t.trans += ch.fired;
     t.most = max(t.most, (int32_t)ch.fired);
-    if (hooks.after_ssa(ch, walks) && walks && ch.fired) {
+    if (walks && ch.fired) {
 #pragma unroll
         for (int c = 0; c < NC; ++c)
             if (comp_on<NC>(m, c)) s.u[(int64_t)c * s.L + l] = (int32_t)ch.xd[c];
@@ -1321,7 +1402,7 @@ __device__ __forceinline__ void day_wave(const Model &m, const DevState &s, int6
 #pragma unroll
         for (int c = 0; c < NC; ++c) y[c] = (int32_t)ch.xd[c];
         long long I = 0;
-        const double phi2 = phi_next(y, d, phi, &I);
+        const double phi2 = phi_after(y, d, phi, &I);
         if (__double_as_longlong(phi2) != __double_as_longlong(phi)) s.phi[l] = phi2;
     }
 }
@@ -1342,7 +1423,7 @@ __device__ __forceinline__ void private_tasks(const Model &m, const DevState &s,
     const int64_t k = (int64_t)d * n_units + unit;
     const int64_t t0 = ev.priv_off[k], t1 = ev.priv_off[k + 1];
     const int64_t count = (t1 - t0) * nl;
-    for (int64_t i = threadIdx.x; i < count; i += kBlock) {
+    for (int64_t i = threadIdx.x; i < count; i += blockDim.x) {
         const int64_t t = t0 + (nl == 1 ? i : i / nl);
         const int32_t r = r0 + (nl == 1 ? 0 : (int32_t)(i % nl));
         if (r < r_end) event_task<NC>(m, s, ev, t, r, d, status);
@@ -1355,35 +1436,12 @@ struct PrivEv {
     int32_t n, g, gm, node;
 };
 
-// A unit's private events in LDS (one lane per node): the event a thread
-// fetched at the start is parked once the prologue is done, and the counts
-// each lane holds after the SSA are handed over instead of being stored.
-template <int NC>
-struct LdsPrivHooks {
-    PrivEv *pe;
-    int32_t (*x)[kBlock];
-    int32_t *touch;
-    const PrivEv *mine;
-    bool has, lds;
-    __device__ void after_prologue() const {
-        if (has) pe[threadIdx.x] = *mine;
-    }
-    template <class St>
-    __device__ bool after_ssa(const St &ch, bool active) const {
-        if (!lds) return true;
-#pragma unroll
-        for (int c = 0; c < NC; ++c) x[c][threadIdx.x] = active ? (int32_t)ch.xd[c] : 0;
-        touch[threadIdx.x] = active && ch.fired ? 1 : 0;
-        return false;
-    }
-};
-
 // One private task (a run of one node's single-node events, i the first)
 // applied to the counts in LDS, with the arithmetic of event_task. A run that
 // draws has the node to itself; runs of additions only may share it and add
 // atomically.
 template <int NC>
-__device__ void private_task_lds(const PrivEv *pe, int i, int n_ev, int32_t (*xs)[kBlock], int32_t *touch,
+__device__ void private_task_lds(const PrivEv *pe, int i, int n_ev, int32_t (*xs)[kMaxUnit], int32_t *touch,
                                  int32_t base, int32_t d, uint32_t key0, uint32_t key1, int32_t set,
                                  unsigned long long *status) {
     const int loc = pe[i].node - base;
@@ -1456,75 +1514,275 @@ struct EventDayShared {
     uint64_t pre[kDayEventCap * kPreDraws];
 };
 
+// One lane per node: a workgroup runs one unit of s.tile_nodes positions (4 to
+// 1024), thread t < tile_nodes owning position t. The counts live in LDS for
+// the day: the owners close the previous day and list their node's chain, as
+// long if it expects kWaveChain attempts (lambda) or more; then the whole
+// workgroup walks the longest chains one after another (walk_group), its
+// wavefronts take the other long ones one each (walk_wave), and the rest are
+// walked side by side by segments of a wavefront (walk_queue); at last the
+// unit's private tasks run on the counts, and each touched node is stored
+// once. What binds a day is the latency of the walks' dependent arithmetic, so
+// the chains of a few nodes are spread over many wavefronts: sixteen a unit,
+// and units small enough for every compute unit to have one (lane_unit on the
+// host). With four wavefronts a unit of 256 nodes, each walking its 64 nodes'
+// chains attempt by attempt in their own lanes, a day's SSA took about 18 us
+// whatever its chains' lengths.
+// The longest chains: those of group_min_attempts and more, in classes of a
+// factor of 4, the highest classes that hold one chain together (three from
+// class kFarClass on). A workgroup walks a chain of 2,000 attempts in about
+// 40,000 cycles, mostly its first round's (10 cycles an attempt past that), a
+// wavefront in 70,000, and several wavefronts side by side cost little more, so
+// several chains of one length are done sooner by a wavefront each (1,000
+// chains of 2,000 in units of 4: 36 us a day, against 82 by their workgroups).
+constexpr double kWaveChain = 48.0;
+constexpr int kFarClass = 3, kLengthClasses = 6;
+
+template <int NC>
+struct DayShared {
+    int32_t x[NC][kMaxUnit];
+    double phi[kMaxUnit];
+    int32_t node[kMaxUnit];
+    int32_t touch[kMaxUnit];     // nodes to store: a transition fired or a private task ran
+    uint16_t list[2][kMaxUnit];  // positions with a chain: long (with the length class << kStageShift), short
+    int32_t n[2], next[2], in_class[kLengthClasses];
+    PrivEv pe[kDayBlock];
+    double tau[kDayWaves][64];
+    long long part[kDayWaves][1 + NC];
+    unsigned long long trans;
+    int32_t most;
+};
+
 template <class Rules>
-__global__ __launch_bounds__(kBlock) void k_day(Model m, DevState s, DevEvents ev, int32_t d, int32_t prologue,
-                                                int32_t ssa) {
-    constexpr int NC = Rules::NC;
-    __shared__ PrivEv sh_pe[kBlock];
-    __shared__ int32_t sh_x[NC][kBlock];
-    __shared__ int32_t sh_touch[kBlock];
-    const int64_t l = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+__global__ __launch_bounds__(kDayBlock) void k_day(Model m, DevState s, DevEvents ev, int32_t d, int32_t prologue,
+                                                   int32_t ssa) {
+    constexpr int NC = Rules::NC, NT = Rules::NT;
+    __shared__ DayShared<NC> sh;
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int32_t U = s.tile_nodes;
+    const int64_t base = (int64_t)blockIdx.x * U;
     // The unit's private events of the day. With at most one per thread they
     // are fetched now, alongside the state, and applied to the counts in LDS
-    // right after the SSA; each node is then stored once. Otherwise the SSA
-    // stores its counts and the tasks run on global memory. Their bounds and
-    // the workgroup's set (one lane per node; instances are padded to whole
-    // workgroups) are read before the status check, which waits for them.
-    const int64_t k = (int64_t)d * (s.Np / kLaneUnit) + blockIdx.x;
+    // right after the SSA; otherwise the counts are stored and the tasks run on
+    // global memory.
+    const int64_t k = (int64_t)d * gridDim.x + blockIdx.x;
     const int32_t pe0 = ssa ? ev.priv_ev_off[k] : 0;
     const int32_t npe = ssa ? ev.priv_ev_off[k + 1] - pe0 : 0;
-    const int32_t set = s.inst[(int64_t)blockIdx.x * kBlock];
-    const bool group = s.unit_group[blockIdx.x] != 0;
+    // instances are padded to whole units: one set per workgroup
+    const int32_t set = s.n_inst == 1 ? 0 : s.inst[base];
     // the unit's nodes among the slots of a day whose remaining events run in
     // LDS: their final counts go to the day's staging buffer (one per thread)
     const bool staged = ssa && ev.unit_stage_off;
     const int32_t st0 = staged ? ev.unit_stage_off[k] : 0;
     const int32_t nst = staged ? ev.unit_stage_off[k + 1] - st0 : 0;
+    const int32_t rec = prologue ? s.rec_slot[d - 1] : -1;
+    const LaneLoad<NC> q = lane_load<NC>(m, s, t < U ? base + t : s.L);
+    if (t < 2) sh.n[t] = sh.next[t] = 0;
+    if (t < kLengthClasses) sh.in_class[t] = 0;
+    if (t == 0) {
+        sh.trans = 0ull;
+        sh.most = 0;
+    }
     if (!block_ok_once(s.status)) return;
     const uint32_t key0 = s.seed[set], key1 = s.repid[set];
-    const bool lds = npe <= kBlock;
-    const bool has = lds && (int)threadIdx.x < npe;
-    const int32_t stage_entry = (int)threadIdx.x < nst ? ev.unit_stage[st0 + threadIdx.x] : -1;
-    PrivEv mine{0u, 0u, 0, 0, 0, 0};
+    const bool lds = npe <= kDayBlock;
+    const bool has = lds && t < npe;
+    const int32_t stage_entry = t < nst ? ev.unit_stage[st0 + t] : -1;
     if (has) {
-        const int64_t e = pe0 + threadIdx.x;
-        mine = PrivEv{ev.meta[e], ev.smap[e], ev.n[e], ev.g[e], ev.gm[e], ev.node[e]};
+        const int64_t e = pe0 + t;
+        sh.pe[t] = PrivEv{ev.meta[e], ev.smap[e], ev.n[e], ev.g[e], ev.gm[e], ev.node[e]};
     }
-    const LdsPrivHooks<NC> hooks{sh_pe, sh_x, sh_touch, &mine, has, lds && ssa};
-    Tally<NC> t{};
-    day_wave<Rules>(m, s, l, d, prologue != 0, ssa != 0, t, s.R, s.status, nullptr, hooks, set, group);
-    const int32_t d_rec = prologue ? d - 1 : -1;
-    const int32_t d_ssa = ssa ? d : -1;
-    flush_block<NC>(m, s, t, set, d_rec, d_ssa, s.n_regions ? s.pos_region[(int64_t)blockIdx.x * kBlock] : -1);
-    if (!ssa) return;
-    if (!lds) {
-        private_tasks<NC>(m, s, ev, d, blockIdx.x, s.Np / kLaneUnit, 0, 1, 1, s.status);
-        if (nst > 0) {
-            __syncthreads();
-            fresh_l1();
-            if (stage_entry >= 0) {
-                const int64_t ls = (int64_t)blockIdx.x * kBlock + (stage_entry & 0xff);
+    const bool active = q.nid >= 0;
+    double coef[NT];
 #pragma unroll
-                for (int c = 0; c < NC; ++c)
-                    ev.stage[(stage_entry >> 8) * NC + c] = comp_on<NC>(m, c) ? load_state(&s.u[(int64_t)c * s.L + ls]) : 0;
+    for (int i = 0; i < NT; ++i) coef[i] = trans_on<NT>(m, i) ? s.coef[set * m.nt + i] : 0.0;
+    if (wave * 64 < U) {
+        double phi = q.phi;
+        if (prologue) {
+            const int32_t dp = d - 1;
+            long long I = 0, prev = 0;
+            if (active) {
+                if (m.phi_pre) {
+                    // phi was already fed by the state before the events of day dp
+#pragma unroll
+                    for (int c = 0; c < NC; ++c)
+                        if ((m.imask >> c) & 1u) I += q.x[c];
+                } else {
+                    phi = phi_next<NC>(m, q.x, s.alpha[set], s.beta[set * 4 + season((int64_t)m.day0 + dp)], phi, &I);
+                }
+                prev = I > 0 ? 1 : 0;
+                if (rec >= 0) {
+                    const int64_t at = (int64_t)rec * s.n_nodes + s.inst_off[set] + q.nid;
+#pragma unroll
+                    for (int c = 0; c < NC; ++c)
+                        if (comp_on<NC>(m, c)) s.snap_u[at * m.nc + c] = q.x[c];
+                    s.snap_v[at] = phi;
+                }
+                if (__double_as_longlong(phi) != __double_as_longlong(q.phi)) s.phi[base + t] = phi;
+            }
+            const long long np = wave_sum(prev);
+            if (lane == 0) sh.part[wave][0] = np;
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                const long long w = wave_sum(q.x[c]);
+                if (lane == 0) sh.part[wave][1 + c] = w;
             }
         }
-    } else {
-        // flush_block's barriers make the parked events and counts visible
-        if (has && !(sh_pe[threadIdx.x].meta & kMetaCont))
-            private_task_lds<NC>(sh_pe, threadIdx.x, npe, sh_x, sh_touch, (int32_t)(blockIdx.x * kBlock), d, key0,
-                                 key1, set, s.status);
+        if (ssa) {
+            typename Rules::State ch;
+#pragma unroll
+            for (int i = 0; i < NT; ++i) ch.cphi[i] = active ? ((m.uses_phi >> i) & 1u ? coef[i] * phi : coef[i]) : 0.0;
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                ch.xd[c] = (double)q.x[c];
+                sh.x[c][t] = q.x[c];
+            }
+            sh.phi[t] = phi;
+            sh.node[t] = q.nid;
+            sh.touch[t] = 0;
+            Rules::rates(m, ch);
+            const double gm = s.group_min_attempts;
+            int cls = 0;
+            if (ch.lam >= gm) {
+                cls = 1 + (ch.lam >= 4.0 * gm) + (ch.lam >= 16.0 * gm) + (ch.lam >= 64.0 * gm) + (ch.lam >= 256.0 * gm);
+                atomicAdd(&sh.in_class[cls], 1);
+            }
+            const int kind = !(ch.lam > 0.0) ? -1 : (cls > 0 || ch.lam >= kWaveChain ? 0 : 1);
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const unsigned long long in = __ballot(kind == i);
+                if (in == 0ull) continue;
+                int at = 0;
+                if (lane == 0) at = atomicAdd(&sh.n[i], (int)__popcll(in));
+                at = __builtin_amdgcn_readfirstlane(at);
+                if (kind == i)
+                    sh.list[i][at + __popcll(in & ((1ull << lane) - 1ull))] = (uint16_t)(t | (cls << kStageShift));
+            }
+        }
+    }
+    __syncthreads();
+    if (prologue && t >= kDayBlock - 64 && lane < 1 + NC) {
+        long long sum = 0;
+        for (int w = 0; w * 64 < U; ++w) sum += sh.part[w][lane];
+        if (lane == 0) {
+            if (sum) atomicAdd(&s.prevalence[(int64_t)(d - 1) * s.n_inst + set], (int32_t)sum);
+        } else if (sum && comp_on<NC>(m, lane - 1)) {
+            const int64_t row = (int64_t)(d - 1) * s.n_inst + set;
+            atomicAdd((unsigned long long *)&s.totals[row * m.nc + (lane - 1)], (unsigned long long)sum);
+            const int32_t region = s.n_regions ? s.pos_region[base] : -1;
+            if (region >= 0)
+                atomicAdd((unsigned long long *)&s.regional[(row * s.n_regions + region) * m.nc + (lane - 1)],
+                          (unsigned long long)sum);
+        }
+    }
+    if (!ssa) return;
+    auto load = [&](int i, typename Rules::State &c) {
+        const double phi = sh.phi[i];
+#pragma unroll
+        for (int k2 = 0; k2 < NT; ++k2) c.cphi[k2] = (m.uses_phi >> k2) & 1u ? coef[k2] * phi : coef[k2];
+#pragma unroll
+        for (int c2 = 0; c2 < NC; ++c2) c.xd[c2] = (double)sh.x[c2][i];
+        c.clock = 0.0;
+        c.fired = 0;
+    };
+    auto store = [&](int i, const typename Rules::State &c) {  // by one lane
+        if (c.fired == 0) return;
+#pragma unroll
+        for (int c2 = 0; c2 < NC; ++c2) sh.x[c2][i] = (int32_t)c.xd[c2];
+        sh.touch[i] = 1;
+        atomicAdd(&sh.trans, (unsigned long long)c.fired);
+        atomicMax(&sh.most, c.fired);
+    };
+    const int n_long = sh.n[0], n_seg = sh.n[1];
+    int group_class = kLengthClasses, n_group = 0;  // classes from group_class on are the workgroup's
+    for (int b = kLengthClasses - 1; b > 0 && n_group + sh.in_class[b] <= (b >= kFarClass ? 3 : 1); --b) {
+        group_class = b;
+        n_group += sh.in_class[b];
+    }
+    for (int i = 0; n_group > 0 && i < n_long; ++i) {
+        const int entry = sh.list[0][i];
+        if (entry >> kStageShift < group_class) continue;
+        --n_group;
+        // the day's critical chain: its wavefronts issue ahead of the other
+        // waves on their SIMDs while it is walked
+        __builtin_amdgcn_s_setprio(3);
+        const int pos = entry & (kMaxUnit - 1);
+        const uint32_t node = (uint32_t)sh.node[pos];
+        typename Rules::State c;
+        load(pos, c);
+        Rules::rates(m, c);
+        uint32_t kb = 0;
+        if (!walk_group<Rules>(m, c, kb, node, (uint32_t)d, key0, key1, s.status, set) && wave == 0)
+            walk_wave<Rules>(m, c, kb, node, (uint32_t)d, key0, key1, s.status, set, sh.tau[0]);
+        if (t == 0) store(pos, c);
+        __builtin_amdgcn_s_setprio(0);
+        __syncthreads();  // the next chain reuses the walk's LDS
+    }
+    auto take = [&](int which, int k2) {
+        int at = 0;
+        if (lane == 0) at = atomicAdd(&sh.next[which], k2);
+        return __builtin_amdgcn_readfirstlane(at);
+    };
+    for (;;) {
+        const int i = n_long > 0 ? take(0, 1) : 0;
+        if (i >= n_long) break;
+        const int entry = sh.list[0][i];
+        if (entry >> kStageShift >= group_class) continue;
+        const int pos = entry & (kMaxUnit - 1);
+        typename Rules::State c;
+        load(pos, c);
+        Rules::reactants(m, c);
+        walk_wave<Rules>(m, c, 0u, (uint32_t)sh.node[pos], (uint32_t)d, key0, key1, s.status, set, sh.tau[wave]);
+        if (lane == 0) store(pos, c);
+    }
+    if (n_seg > 0)
+        walk_queue<Rules, 16>(m, n_seg, sh.tau[wave], [&](int k2) { return take(1, k2); },
+                              [&](int i, typename Rules::State &c, ChainKey &key) {
+                                  const int pos = sh.list[1][i];
+                                  load(pos, c);
+                                  key = ChainKey{0u, (uint32_t)sh.node[pos], (uint32_t)d, key0, key1, s.status, set};
+                              },
+                              [&](int i, const typename Rules::State &c) { store(sh.list[1][i], c); });
+    __syncthreads();
+    if (t == 0 && sh.trans != 0ull) {
+        const int64_t row = (int64_t)d * s.n_inst + set;
+        atomicAdd((unsigned long long *)&s.transitions[row], sh.trans);
+        atomicMax(&s.max_fired[row], sh.most);
+    }
+    if (m.phi_pre) {
+        // eq:numstep5 as written: phi from the state after the SSA, before the events
+        if (t < U && active) {
+            int32_t y[NC];
+#pragma unroll
+            for (int c = 0; c < NC; ++c) y[c] = sh.x[c][t];
+            long long I = 0;
+            const double phi = sh.phi[t];
+            const double phi2 = phi_next<NC>(m, y, s.alpha[set], s.beta[set * 4 + season((int64_t)m.day0 + d)], phi, &I);
+            if (__double_as_longlong(phi2) != __double_as_longlong(phi)) s.phi[base + t] = phi2;
+        }
         __syncthreads();
-        if (sh_touch[threadIdx.x]) {
+    }
+    if (lds) {
+        if (has && !(sh.pe[t].meta & kMetaCont))
+            private_task_lds<NC>(sh.pe, t, npe, sh.x, sh.touch, (int32_t)base, d, key0, key1, set, s.status);
+        __syncthreads();
+    }
+    if (t < U && sh.touch[t]) {
 #pragma unroll
-            for (int c = 0; c < NC; ++c)
-                if (comp_on<NC>(m, c)) s.u[(int64_t)c * s.L + l] = sh_x[c][threadIdx.x];
-        }
-        if (stage_entry >= 0) {
+        for (int c = 0; c < NC; ++c)
+            if (comp_on<NC>(m, c)) s.u[(int64_t)c * s.L + base + t] = sh.x[c][t];
+    }
+    if (!lds) {
+        __syncthreads();
+        private_tasks<NC>(m, s, ev, d, blockIdx.x, gridDim.x, 0, 1, 1, s.status);
+        __syncthreads();
+        fresh_l1();
+    }
+    if (stage_entry >= 0) {
+        const int at = stage_entry & (kMaxUnit - 1), slot = stage_entry >> kStageShift;
 #pragma unroll
-            for (int c = 0; c < NC; ++c)
-                ev.stage[(stage_entry >> 8) * NC + c] = comp_on<NC>(m, c) ? sh_x[c][stage_entry & 0xff] : 0;
-        }
+        for (int c = 0; c < NC; ++c)
+            ev.stage[slot * NC + c] = !comp_on<NC>(m, c) ? 0 : lds ? sh.x[c][at] : load_state(&s.u[(int64_t)c * s.L + base + at]);
     }
 }
 
@@ -1686,7 +1944,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(Rules::k
     for (int j = wave; j < s.tile_nodes;) {
         const int64_t pos = pos0 + j;
         if (pos >= s.Np) break;
-        day_wave<Rules>(m, s, pos * s.RL + r, day, pro, walk, t, s.RL, status, &tp, NoHooks{}, -1, false, on);
+        day_wave<Rules>(m, s, pos * s.RL + r, day, pro, walk, t, s.RL, status, &tp, on);
         int32_t next = 0;
         if (lane == 0) next = atomicAdd(&sh_next, 1);
         j = __shfl(next, 0);
@@ -2268,7 +2526,7 @@ __global__ __launch_bounds__(kBlock) void k_persist(Model m, DevState s, DevEven
                     day_wave<Rules>(m, s, l, d, prologue, ssa, t, s.R, s.status);
                     flush_block<NC>(m, s, t, s.inst[chunk * kBlock], d_rec, d_ssa,
                                     s.n_regions ? s.pos_region[chunk * kBlock] : -1);
-                    if (ssa) private_tasks<NC>(m, s, ev, d, chunk, s.Np / kLaneUnit, 0, 1, 1, s.status);
+                    if (ssa) private_tasks<NC>(m, s, ev, d, chunk, s.Np / kBlock, 0, 1, 1, s.status);
                 }
             }
         }
@@ -2341,6 +2599,7 @@ Table table() {
 Table pick(const Model &m) {
     if (m.pairs && m.nc == 2) return table<PairRules<1>>();
     if (m.pairs && m.nc == 6) return table<PairRules<3>>();
+    if (m.nc <= 4 && m.nt <= 4) return table<GenericRules<4, 4>>();
     return table<GenericRules<MAXC, MAXT>>();
 }
 
@@ -2360,8 +2619,9 @@ int launch_day(const Model &m, const DevState &s, const DevEvents &ev, int32_t d
         const unsigned nx = (unsigned)((s.Np + s.tile_nodes - 1) / s.tile_nodes + (int64_t)s.n_heavy * kHeavyBlocks);
         return (int)hipLaunchKernel(t.tile, dim3(nx, (unsigned)(s.RL / 64)), dim3(kBlock), args, 0, (hipStream_t)stream);
     }
-    const unsigned grid = (unsigned)((s.L + kBlock - 1) / kBlock);
-    return (int)hipLaunchKernel(t.day, dim3(grid), dim3(kBlock), args, 0, (hipStream_t)stream);
+    if (s.tile_nodes < 4 || s.tile_nodes > kMaxUnit || s.L % s.tile_nodes != 0) return hipErrorInvalidValue;
+    const unsigned grid = (unsigned)(s.L / s.tile_nodes);
+    return (int)hipLaunchKernel(t.day, dim3(grid), dim3(kDayBlock), args, 0, (hipStream_t)stream);
 }
 
 int launch_events(const Model &m, const DevState &s, const DevEvents &ev, int32_t d, int64_t begin,

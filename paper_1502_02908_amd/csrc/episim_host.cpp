@@ -365,10 +365,11 @@ int same_model(const sim_problem *a, const sim_problem *b, std::string *err) {
     return SIM_OK;
 }
 
-// One lane per node for a single replicate, unless tile_nodes asks for tiles:
-// then each wavefront of a tile walks one node's chains with all its lanes
-// (networks of few nodes with long chains).
-int choose_layout(int32_t R, int32_t tile_nodes) { return R == 1 && tile_nodes <= 0 ? LAYOUT_LANES : LAYOUT_TILE; }
+// One lane per node for a single replicate (the persistent kernel also runs one
+// in tiles where tile_nodes asks for them).
+int choose_layout(int32_t R, int32_t tile_nodes, int32_t launch) {
+    return R == 1 && (tile_nodes <= 0 || launch != SIM_LAUNCH_PERSISTENT) ? LAYOUT_LANES : LAYOUT_TILE;
+}
 
 // Lanes per position: one, or in tiles the replicate count rounded up to
 // whole wavefronts (replicate lanes r >= R idle).
@@ -376,18 +377,29 @@ int32_t lane_stride(int32_t R, int layout) {
     return layout == LAYOUT_LANES ? 1 : (int32_t)(((int64_t)R + 63) / 64 * 64);
 }
 
-// Nodes of one unit of work and the padding granule of an instance.
-int64_t unit_nodes(int layout, int64_t tile) { return layout == LAYOUT_TILE ? tile : 64; }
-int64_t pad_nodes(int layout, int64_t tile) { return unit_positions(layout, tile); /* one workgroup */ }
+// One lane per node: positions of a unit (a workgroup of the day kernel) unless
+// tile_nodes names them: the fewest, as a power of two from 4, that leave at
+// most one unit per compute unit, so that a day's chains spread over as many of
+// them as there are. (37k nodes: 256 positions in 145 units; from 262,144
+// nodes on 1024, whose wavefronts all have owners. 1,000 nodes, 365 days: 7.3
+// ms in units of 4, 8.1 of 64, 9.1 of 256; 5,000 nodes of a general model, 120
+// days: 3.6 ms in units of 32, 8.3 of 4, five to a compute unit.)
+constexpr int64_t kUnitsWanted = 256;
+int64_t lane_unit(int64_t n_nodes) {
+    int64_t u = 4;
+    while (u < kMaxUnit && (n_nodes + u - 1) / u > kUnitsWanted) u *= 2;
+    return u;
+}
 
 // Positions of one instance's nodes: herds sorted by size (largest first)
 // are dealt one per unit of work in turn, back and forth (snake order), so the
 // longest SSA chains of a day run in different units, start first, and share
-// their unit with the lightest herds of the next round. With one lane per
-// node, the kSoloHerds largest herds get a wavefront each (the other lanes are
-// padding), so their chains are walked by the whole wavefront from the first
-// attempt. Returns the number of positions (a multiple of the padding
-// granule); pos_node[pos] = node or -1.
+// their unit with the lightest herds of the next round. In the persistent
+// kernel's one-lane-per-node layout the unit of work is a wavefront, and the
+// kSoloHerds largest herds get one each (the other lanes are padding), so
+// their chains are walked by the whole wavefront from the first attempt.
+// Returns the number of positions (a multiple of the padding granule);
+// pos_node[pos] = node or -1.
 constexpr int64_t kSoloHerds = 128;
 // With replicate tiles, the largest herds of an instance (at most
 // kHeavyHerds, and one per 64 nodes) get units of their own whose every
@@ -396,21 +408,21 @@ constexpr int64_t kSoloHerds = 128;
 constexpr int64_t kHeavyHerds = 64;
 // With one lane per node and per-day launches, the largest herds of a large
 // instance (kGroupHerds unless the options say otherwise) get a workgroup
-// each: the herd sits at the unit's first position and its chain is walked by
-// all four wavefronts of the workgroup.
+// each, so that no other chain waits for theirs.
+constexpr int64_t kGroupMinNodes = 8192;
 constexpr int64_t kGroupHerds = 4;
 constexpr int32_t kMaxGroupHerds = 16;
 constexpr int32_t kMaxHeavyHerds = 256;
 
 // One group of herds, ranked largest first, placed from position base: solo
-// wavefronts first (one lane per node, large groups only), then dealt over the
-// units of the group; the group is padded to whole workgroups / tiles.
+// wavefronts first (by_wave, large groups only), then dealt over the wavefronts
+// or the units of the group; the group is padded to whole units.
 // Returns the positions it takes.
-int64_t place_group(const std::vector<int32_t> &ranked, int layout, int64_t tile, int64_t base,
+int64_t place_group(const std::vector<int32_t> &ranked, bool by_wave, int64_t tile, int64_t base,
                     std::vector<int32_t> *pos_node) {
-    const int64_t n = (int64_t)ranked.size(), G = unit_nodes(layout, tile), P = pad_nodes(layout, tile);
+    const int64_t n = (int64_t)ranked.size(), G = by_wave ? 64 : tile, P = tile;
     // solo wavefronts only pay off when the rest still fills many wavefronts
-    const int64_t solo = (layout == LAYOUT_LANES && n >= 64 * kSoloHerds) ? kSoloHerds : 0;
+    const int64_t solo = (by_wave && n >= 64 * kSoloHerds) ? kSoloHerds : 0;
     const int64_t span = n == 0 ? 0 : ((solo * 64 + (n - solo) + P - 1) / P) * P;
     pos_node->resize(base + span, -1);
     for (int64_t q = 0; q < solo; ++q) (*pos_node)[base + q * 64] = ranked[q];
@@ -430,7 +442,7 @@ int64_t place_group(const std::vector<int32_t> &ranked, int layout, int64_t tile
 // work holds herds of one region only, so the per-unit sums of the records
 // are also regional sums; the heavy herds' own units may mix regions (their
 // chains record on their own).
-int64_t order_nodes(const sim_problem *p, int layout, int64_t tile, int64_t heavy, int64_t group,
+int64_t order_nodes(const sim_problem *p, int layout, bool by_wave, int64_t tile, int64_t heavy, int64_t group,
                     std::vector<int32_t> *pos_node, std::vector<int32_t> *pos_region) {
     const int64_t Nn = p->n_nodes, Nc = p->n_comp;
     // a herd's size is its largest population over the horizon: the SSA only
@@ -493,11 +505,11 @@ int64_t order_nodes(const sim_problem *p, int layout, int64_t tile, int64_t heav
     std::sort(by_size.begin(), by_size.end());
     std::vector<int32_t> rank(Nn);
     for (int64_t i = 0; i < Nn; ++i) rank[i] = by_size[i].second;
-    const int64_t G = unit_nodes(layout, tile);
+    const int64_t G = tile;
     const int64_t hv = layout == LAYOUT_TILE ? std::min(heavy, Nn) : 0;
     const int64_t hv_span = ((hv + G - 1) / G) * G;
     const int64_t gr = layout == LAYOUT_LANES ? std::min(group, Nn) : 0;
-    const int64_t lead = hv_span + gr * pad_nodes(layout, tile);
+    const int64_t lead = hv_span + gr * tile;
     const int32_t J = p->n_regions > 0 ? p->n_regions : 0;
     auto region_of = [&](int32_t i) { return J > 0 ? p->region[i] : -1; };
     pos_node->assign(lead, -1);
@@ -508,16 +520,16 @@ int64_t order_nodes(const sim_problem *p, int layout, int64_t tile, int64_t heav
     }
     // a workgroup per group herd: the herd first, the rest padding of its region
     for (int64_t q = 0; q < gr; ++q) {
-        const int64_t b = hv_span + q * pad_nodes(layout, tile);
+        const int64_t b = hv_span + q * tile;
         (*pos_node)[b] = rank[hv + q];
-        for (int64_t i = 0; i < pad_nodes(layout, tile); ++i) (*pos_region)[b + i] = region_of(rank[hv + q]);
+        for (int64_t i = 0; i < tile; ++i) (*pos_region)[b + i] = region_of(rank[hv + q]);
     }
     // groups: the herds outside regions, then region by region (one group without regions)
     std::vector<std::vector<int32_t>> groups(J + 1);
     for (int64_t q = hv + gr; q < Nn; ++q) groups[region_of(rank[q]) + 1].push_back(rank[q]);
     int64_t base = lead;
     for (int32_t j = -1; j < J; ++j) {
-        const int64_t span = place_group(groups[j + 1], layout, tile, base, pos_node);
+        const int64_t span = place_group(groups[j + 1], by_wave, tile, base, pos_node);
         pos_region->resize(base + span, j);
         base += span;
     }
@@ -528,7 +540,7 @@ int64_t order_nodes(const sim_problem *p, int layout, int64_t tile, int64_t heav
 struct Layout {
     size_t u, phi, node_id, inst, inst_off, seed, coef, alpha, beta, repid, status, ev_g, ev_gm, ev_node,
         ev_dest, ev_n, ev_meta, ev_smap, task_off, priv_off, priv_ev_off, day_slot_off, slot_pos, unit_stage_off, unit_stage, stage, slot_key, lvl_ev_off, ev_slot_src, ev_slot_dst, lvl_off, lvl_ptr, prevalence, transitions, totals, max_fired, snap_u, snap_v, rec_slot, slots,
-        u0, v0, run, heavy_pos, unit_heavy, unit_group, pos_region, regional, goal_ref, goal_part, total;
+        u0, v0, run, heavy_pos, unit_heavy, pos_region, regional, goal_ref, goal_part, total;
 };
 
 size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -592,7 +604,6 @@ Layout layout_for(int64_t Np, int64_t n_nodes, int64_t n_inst, int64_t Nc, int64
     l.goal_ref = take(sizeof(int64_t) * D * n_regions * Nc);
     l.goal_part = take(n_regions ? sizeof(double) * 2 * D : 0);
     l.unit_heavy = take(n_units);
-    l.unit_group = take(n_units);
     l.u0 = take(n_slots ? sizeof(int32_t) * Nc * Np : 0);
     l.v0 = take(n_slots ? sizeof(double) * Np : 0);
     // slot handles: the step's running slots, then its running columns
@@ -604,7 +615,7 @@ Layout layout_for(int64_t Np, int64_t n_nodes, int64_t n_inst, int64_t Nc, int64
 // Everything a handle uploads, built on the host from one or more problems.
 struct Packed {
     int32_t n_inst = 0, R = 0, RL = 0, D = 0, Nc = 0, Nt = 0, n_record = 0, layout = 0, n_slots = 0;
-    int64_t tile = kTileNodes;  // positions of one replicate tile
+    int64_t tile = kTileNodes;  // positions of one unit (replicate tile, or workgroup with one lane per node)
     int32_t slot_lanes = 64;    // replicate lanes of one slot of a slot handle
     int64_t Np = 0, n_nodes = 0, n_events = 0, n_levels = 0;
     std::vector<int32_t> node_id, inst, inst_off, inst_pos0;
@@ -622,7 +633,6 @@ struct Packed {
     std::vector<int32_t> pos_region; // region of each position (-1 outside regions)
     std::vector<int32_t> heavy_pos; // positions of the herds whose chains get a wavefront each
     std::vector<uint8_t> unit_heavy;
-    std::vector<uint8_t> unit_group;  // units whose first herd is walked by the whole workgroup
     std::vector<int32_t> day_slot_off, slot_pos, ev_slot_src, ev_slot_dst;  // days run in LDS
     std::vector<int32_t> unit_stage_off, unit_stage;  // their slots by (day, unit)
     std::vector<uint32_t> slot_key;     // per slot: Philox key (seed, replicate id) and set of its node
@@ -665,14 +675,18 @@ int build_packed(const sim_problem *const *ps, int32_t n, int32_t events_mode, P
     pk->Nc = p0->n_comp;
     pk->Nt = p0->n_trans;
     pk->n_record = p0->n_record;
-    pk->layout = n_slots > 0 ? LAYOUT_TILE : choose_layout(pk->R, o ? o->tile_nodes : 0);
+    pk->layout = n_slots > 0 ? LAYOUT_TILE : choose_layout(pk->R, o ? o->tile_nodes : 0, launch);
     pk->RL = lane_stride(pk->R, pk->layout);
     const int32_t R = pk->R;
     // positions
     std::vector<std::vector<int32_t>> pos_node(n);
     pk->inst_off.assign(n, 0);
     pk->inst_pos0.assign(n, 0);
-    std::vector<int64_t> group_units;
+    if (pk->layout == LAYOUT_LANES) {
+        int64_t all = 0;
+        for (int32_t k = 0; k < n; ++k) all += ps[k]->n_nodes;
+        pk->tile = launch == SIM_LAUNCH_PERSISTENT ? kPersistUnit : o && o->tile_nodes > 0 ? o->tile_nodes : lane_unit(all);
+    }
     for (int32_t k = 0; k < n; ++k) {
         pk->inst_off[k] = (int32_t)pk->n_nodes;
         pk->inst_pos0[k] = (int32_t)pk->Np;
@@ -682,24 +696,21 @@ int build_packed(const sim_problem *const *ps, int32_t n, int32_t events_mode, P
                                   ? std::min<int64_t>(heavy_herds > 0 ? heavy_herds : kHeavyHerds, ps[k]->n_nodes / 64)
                                   : 0;
         const int64_t group = (pk->layout == LAYOUT_LANES && launch == SIM_LAUNCH_KERNELS &&
-                               ps[k]->n_nodes >= 64 * kSoloHerds && group_herds >= 0)
+                               ps[k]->n_nodes >= kGroupMinNodes && group_herds >= 0)
                                   ? (group_herds > 0 ? group_herds : kGroupHerds) : 0;
         std::vector<int32_t> preg;
-        const int64_t np_k = order_nodes(ps[k], pk->layout, pk->tile, heavy, group, &pos_node[k], &preg);
+        const int64_t np_k = order_nodes(ps[k], pk->layout, pk->layout == LAYOUT_LANES && launch == SIM_LAUNCH_PERSISTENT, pk->tile,
+                                          heavy, group, &pos_node[k], &preg);
         pk->pos_region.insert(pk->pos_region.end(), preg.begin(), preg.end());
         for (int64_t j = 0; j < heavy; ++j) pk->heavy_pos.push_back((int32_t)(pk->Np + j));
-        for (int64_t j = 0; j < group; ++j)
-            group_units.push_back((pk->Np + j * pad_nodes(pk->layout, pk->tile)) / unit_positions(pk->layout, pk->tile));
         pk->Np += np_k;
         pk->n_nodes += ps[k]->n_nodes;
         pk->n_events += ps[k]->n_events;
     }
     if (pk->Np * (int64_t)pk->RL > INT32_MAX) return *err = "positions x replicate lanes must stay below 2^31", SIM_EINVAL;
     if (pk->n_events > INT32_MAX) return *err = "too many events", SIM_EINVAL;
-    pk->unit_heavy.assign(pk->Np / unit_positions(pk->layout, pk->tile), 0);
-    for (int32_t hp : pk->heavy_pos) pk->unit_heavy[hp / unit_positions(pk->layout, pk->tile)] = 1;
-    pk->unit_group.assign(pk->Np / unit_positions(pk->layout, pk->tile), 0);
-    for (int64_t u : group_units) pk->unit_group[u] = 1;
+    pk->unit_heavy.assign(pk->Np / pk->tile, 0);
+    for (int32_t hp : pk->heavy_pos) pk->unit_heavy[hp / pk->tile] = 1;
     pk->node_id.assign(pk->Np, -1);
     pk->inst.assign(pk->Np, 0);
     pk->lane_of.assign(pk->n_nodes, 0);
@@ -827,7 +838,7 @@ int build_packed(const sim_problem *const *ps, int32_t n, int32_t events_mode, P
     // then private tasks by day, unit and first event; a task's events stay
     // together in list order. Levels and (day, unit) pairs belong to one day,
     // so each range counts and places its own tasks.
-    const int64_t U = pk->Np / unit_positions(pk->layout, pk->tile);
+    const int64_t U = pk->Np / pk->tile;
     pk->n_units = U;
     big_vec<int64_t> task_glv(n_tasks);
     big_vec<int32_t> task_n(n_tasks), tslot(n_tasks);
@@ -836,7 +847,7 @@ int build_packed(const sim_problem *const *ps, int32_t n, int32_t events_mode, P
     run_ranges(cut, [&](int c, int64_t b, int64_t end) {
         std::fill(task_n.begin() + tcut[c], task_n.begin() + tcut[c + 1], 0);
         for (int64_t e = b; e < end; ++e) {
-            task_glv[task[e]] = priv[task[e]] ? (int64_t)mday[e] * U + mnode[e] / unit_positions(pk->layout, pk->tile)
+            task_glv[task[e]] = priv[task[e]] ? (int64_t)mday[e] * U + mnode[e] / pk->tile
                                               : pk->lvl_ptr[mday[e]] + level[e] - 1;
             task_n[task[e]]++;
         }
@@ -965,10 +976,10 @@ int build_packed(const sim_problem *const *ps, int32_t n, int32_t events_mode, P
         }
     }
     // The slots of such a day by unit: the unit's day kernel hands their
-    // counts over in the day's staging buffer (local position | slot << 8).
+    // counts over in the day's staging buffer (local position | slot << kStageShift).
     pk->unit_stage_off.assign((size_t)pk->D * U + 1, 0);
     if (pk->layout == LAYOUT_LANES) {
-        const int64_t G = unit_positions(pk->layout, pk->tile);
+        const int64_t G = pk->tile;
         for (int32_t d = 0; d < pk->D; ++d)
             for (int32_t i = pk->day_slot_off[d]; i < pk->day_slot_off[d + 1]; ++i)
                 pk->unit_stage_off[(size_t)d * U + pk->slot_pos[i] / G + 1]++;
@@ -979,7 +990,7 @@ int build_packed(const sim_problem *const *ps, int32_t n, int32_t events_mode, P
             for (int32_t i = pk->day_slot_off[d]; i < pk->day_slot_off[d + 1]; ++i) {
                 const int32_t pos = pk->slot_pos[i];
                 pk->unit_stage[fill[(size_t)d * U + pos / G]++] =
-                    (int32_t)(pos % G) | ((i - pk->day_slot_off[d]) << 8);
+                    (int32_t)(pos % G) | ((i - pk->day_slot_off[d]) << kStageShift);
             }
     }
     pk->rec_slot.assign(std::max(pk->D, 1), -1);
@@ -1223,6 +1234,11 @@ int create(const sim_problem *const *ps, int32_t n, const sim_device_opts *o, si
         m.reactant2[k] = p->reactant2 ? p->reactant2[k] : -1;
         for (int c = 0; c < h->Nc; ++c) m.S[c][k] = p->S[(size_t)c * h->Nt + k];
     }
+    for (int k = 0; k < h->Nt; ++k)
+        for (int i = 0; i < h->Nt; ++i) {
+            m.react[k][i] = (double)m.S[m.reactant[k]][i];
+            m.react2[k][i] = m.reactant2[k] >= 0 ? (double)m.S[m.reactant2[k]][i] : 0.0;
+        }
     m.imask = p->phi_I_mask;
     m.nmask = p->phi_N_mask;
     // paired S <-> I classes: transition k moves one individual from compartment k to k ^ 1
@@ -1292,7 +1308,6 @@ int create(const sim_problem *const *ps, int32_t n, const sim_device_opts *o, si
     s.n_heavy = (int32_t)pk.heavy_pos.size();
     s.heavy_pos = at<int32_t>(h->ws, l.heavy_pos);
     s.unit_heavy = s.n_heavy ? at<uint8_t>(h->ws, l.unit_heavy) : nullptr;
-    s.unit_group = at<uint8_t>(h->ws, l.unit_group);
     s.n_regions = p->n_regions;
     s.pos_region = at<int32_t>(h->ws, l.pos_region);
     s.regional = at<int64_t>(h->ws, l.regional);
@@ -1361,7 +1376,6 @@ int create(const sim_problem *const *ps, int32_t n, const sim_device_opts *o, si
         {(void *)s.heavy_pos, pk.heavy_pos.data(), sizeof(int32_t) * pk.heavy_pos.size()},
         {(void *)s.pos_region, pk.pos_region.data(), s.n_regions ? sizeof(int32_t) * pk.pos_region.size() : 0},
         {(void *)s.unit_heavy, pk.unit_heavy.data(), s.n_heavy ? pk.unit_heavy.size() : 0},
-        {(void *)s.unit_group, pk.unit_group.data(), pk.unit_group.size()},
     };
     for (const Up &up : ups) {
         if (up.bytes == 0) continue;

@@ -44,6 +44,8 @@ struct Model {
     int32_t reactant2[MAXT];    // second reactant of a mass-action rate, -1 if none
     int32_t phi_pre;            // 1: phi from the state after the SSA, before the events
     int32_t S[MAXC][MAXT];      // S[c][k]
+    // change of X[reactant[k]] and X[reactant2[k]] when transition i fires
+    double react[MAXT][MAXT], react2[MAXT][MAXT];
 };
 
 // One slot of a slot handle: the handle step at which the slot's day 0 runs
@@ -84,14 +86,14 @@ struct DevState {
     const int32_t *run_cols;    // [RL / 64]
     // replicate tiles: the herds whose every (herd, replicate) chain gets a
     // wavefront of its own, and the units that hold only such herds
-    int32_t tile_nodes;         // positions of one replicate tile (a power of two, 32 .. 512)
+    int32_t tile_nodes;         // positions of one unit: a replicate tile (a power of two, 4 .. 512), or
+                                // a workgroup's nodes with one lane per node (4 .. kMaxUnit)
     int32_t slot_lanes;         // slot handles: replicate lanes of one slot (8, 16, 32 or 64)
     uint32_t few_chains;        // at most this many live chains of a wavefront are walked one after another
-    double group_min_attempts;  // a workgroup walks one chain while it expects this many attempts
+    double group_min_attempts;  // one lane per node: a workgroup walks a chain that expects this many attempts
     int32_t n_heavy;
     const int32_t *heavy_pos;   // [n_heavy]
     const uint8_t *unit_heavy;  // [n_units], null if n_heavy == 0
-    const uint8_t *unit_group;  // [n_units]: one lane per node, the unit's first herd is walked by the whole workgroup
     // daily records
     int32_t *prevalence;        // [D][sets]
     int64_t *transitions;       // [D][sets]
@@ -124,7 +126,7 @@ struct DevEvents {
     const int32_t *day_slot_off;
     const int32_t *slot_pos;
     const int32_t *unit_stage_off;  // [D * n_units + 1]: slots of day d held by unit u (one lane per node):
-    const int32_t *unit_stage;      // local position | slot << 8
+    const int32_t *unit_stage;      // local position | slot << kStageShift
     int32_t *stage;                 // [kDaySlotCap * MAXC]: their counts after the day kernel, [slot][c]
     const uint32_t *slot_key;   // [3 per slot] Philox key (seed, replicate id) and set of the slot's node
     const int64_t *lvl_ev_off;  // event offsets of each level
@@ -135,21 +137,18 @@ struct DevEvents {
 
 // Layouts of the day phase: one lane per node with workgroup sums (R == 1),
 // or tiles of kTileNodes nodes x 64 replicate lanes per workgroup (R > 1,
-// lane stride RL a multiple of 64).
+// lane stride RL a multiple of 64). A private task (a level-1 run of one node's
+// single-node events) runs in its node's unit right after the SSA.
 constexpr int kTileNodes = 128;       // default positions of a replicate tile
 constexpr uint32_t kFewChains = 4;     // default: at most this many live chains walked one after another
-// default: a workgroup walks a chain while it expects this many attempts. A round of the
-// workgroup (256 attempts) takes about 6,000 cycles, a round of one wavefront (64) about 2,000: below
-// some 128 attempts the wavefront is done as soon (37k network, run of 365 days: 22.1 ms from 4096
-// attempts, 18.6 from 512, 17.9 from 128, 18.0 from 16)
-constexpr double kGroupMinAttempts = 128.0;
-constexpr int kLaneUnit = 256;  // positions of one workgroup with one lane per node
+constexpr double kGroupMinAttempts = 256.0;  // default: a workgroup walks a chain expecting this many attempts
+// One lane per node: positions of one workgroup, a power of two up to kMaxUnit
+// (the persistent kernel's workgroups take kPersistUnit).
+constexpr int kMaxUnit = 1024;
+constexpr int kPersistUnit = 256;
+constexpr int kStageShift = 10;
+static_assert(kMaxUnit == 1 << kStageShift, "local positions fit below the slot (and the length class of a chain)");
 enum { LAYOUT_LANES = 0, LAYOUT_TILE = 1 };
-
-// Positions per unit of the day phase (a workgroup's nodes); a private task
-// (a level-1 run of one node's single-node events) runs in its node's unit
-// right after the SSA.
-inline int64_t unit_positions(int layout, int64_t tile) { return layout == LAYOUT_TILE ? tile : kLaneUnit; }
 
 // Host-side launchers (episim_device.hip). Each returns a hipError_t as int.
 // A day whose levels run in LDS: its levels lv0 .. lv0 + nl - 1, slots

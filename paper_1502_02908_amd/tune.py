@@ -18,11 +18,10 @@ the schedule of the workload at hand (candidates_for):
                      another by the whole wavefront (0: default 4, negative: never);
 one lane per node (one trajectory per instance):
   group_herds        how many of the largest herds of a large instance get a
-                     whole workgroup for their chains (0: default 4, negative: none);
-  group_min_attempts how many attempts a chain must still expect in the day for
-                     the workgroup to walk it (0: default 128);
-  tile_nodes         nonzero: tiles of this many nodes instead, each wavefront
-                     walking one node's chain with all its lanes;
+                     workgroup to themselves (0: default 4, negative: none);
+  group_min_attempts how many attempts a chain must expect in the day for the
+                     whole workgroup to walk it (0: default 256);
+  tile_nodes         nodes per workgroup (0: by the network's size);
 replicate tiles (several replicates per instance):
   tile_nodes         nodes per tile of 64 replicate lanes (0: default 128), taken
                      one at a time by the tile's four wavefronts;

@@ -1,0 +1,97 @@
+"""The walks of SSA chains on the GPU against the oracle, bit for bit, at the
+sizes where a walk or a unit changes: herds whose chains are walked by a
+segment of a wavefront, a wavefront or a workgroup; unit sizes from 64 to 1024
+nodes; more private events in a unit than threads; and models of three to
+eight compartments, with and without a second reactant."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+from farmnet import synth
+from oracle import oracle as O
+import paper_1502_02908_amd as P
+
+from .gpu_common import assert_parity, gpu_run, say
+
+pytestmark = pytest.mark.gpu
+
+
+def check(p, **kw):
+    g = gpu_run(p, **kw)
+    assert_parity(g, O.run(p, threads=8))
+    return g
+
+
+@pytest.mark.parametrize("classes", [1, 3])
+def test_chains_of_every_length(classes):
+    # herds of 1 to 40,000 animals at one transition per animal and day: the
+    # attempts expected run across the bounds of the three walks (48, 256), of
+    # a round (8, 16, 64, 1024) and of the summed head of a chain (64)
+    make = synth.flip_model if classes == 1 else synth.flip_classes
+    p = make(n_nodes=120, S0=0, I0=0, n_days=3)
+    sizes = [1, 2, 7, 8, 9, 15, 16, 17, 40, 47, 48, 49, 60, 64, 66, 128, 250, 256, 260, 900, 1020, 1030, 2100, 40000]
+    p.u0 = np.ascontiguousarray(p.u0)
+    for i, n in enumerate(sizes):
+        p.u0[5 * i % 120 + i % 5, i % p.n_comp] = n
+    p.record_days = np.array([0, 2], np.int32)
+    say(f"[walks] lengths classes={classes}")
+    check(p)
+
+
+@pytest.mark.parametrize("n_nodes", [1, 63, 64, 65, 1000, 16385, 32769, 70000, 262145])
+def test_unit_sizes(n_nodes):
+    # 64 positions a unit up to 16,384 nodes, then 128, 256, 512 and 1024
+    p = synth.sise3_network(n_nodes=n_nodes, n_days=4, seed=91, u=10.0, seeded_frac=0.2, seeded_I=0.3, age_days=(1, 2))
+    p.v0[:] = 5.0
+    p.record_days = np.array([0, 3], np.int32)
+    say(f"[walks] unit sizes n_nodes={n_nodes}")
+    check(p)
+
+
+@pytest.mark.parametrize("density", [14.0, 24.0])
+def test_private_events_around_the_workgroup_size(density):
+    # a unit of 64 nodes with about 900 and 1,500 private events a day: the
+    # tasks run in LDS up to 1,024 and on global memory past that
+    p = synth.sise3_network(n_nodes=256, n_days=12, seed=92, age_days=(2, 5), median=400.0, e1_per_node_day=density)
+    p.record_days = np.array([0, 11], np.int32)
+    check(p)
+
+
+def chain_model(n_comp, n_nodes, n_days, bimolecular, seed):
+    """Compartments 0 -> 1 -> ... -> n_comp - 1 -> 0, the first step forced by
+    phi (or by the count of compartment 1), births, deaths and movements."""
+    base = synth.sis_network(n_nodes=n_nodes, n_days=n_days, seed=seed, p_exit=0.02, p_enter=0.02, p_ext=0.01)
+    S = np.zeros((n_comp, n_comp), np.int32)
+    for k in range(n_comp):
+        S[k, k] -= 1
+        S[(k + 1) % n_comp, k] += 1
+    u0 = np.zeros((n_nodes, n_comp), np.int32)
+    u0[:, :2] = base.u0
+    u0[::5, 1] += 7
+    u0[3] = 3000
+    E = np.ones((n_comp, 2), np.int32)
+    E[1:, 0] = 0
+    phi = np.zeros(n_comp, np.int32)
+    phi[0] = 0 if bimolecular else 1
+    coef = np.full((1, n_comp), 0.3)
+    r2 = None
+    if bimolecular:
+        coef[0, 0] = 0.001
+        r2 = np.full(n_comp, -1, np.int32)
+        r2[0] = 1
+    return dataclasses.replace(base, n_comp=n_comp, n_trans=n_comp, u0=u0, S=S, reactant=np.arange(n_comp, dtype=np.int32),
+                               uses_phi=phi, coef=coef, reactant2=r2, phi_I_mask=0b10, phi_N_mask=(1 << n_comp) - 1,
+                               E=E, N=np.zeros((n_comp, 0), np.int32), name="chain")
+
+
+@pytest.mark.parametrize("n_comp,bimolecular,reps", [(3, False, 1), (4, True, 1), (5, False, 1), (8, True, 1),
+                                                     (3, True, 5), (7, False, 3)])
+def test_general_models(n_comp, bimolecular, reps):
+    p = chain_model(n_comp, 150, 8, bimolecular, 93)
+    if reps > 1:
+        p = p.with_replicates(reps, replicate_id=np.arange(reps, dtype=np.uint32) + 9)
+    p.record_days = np.array([0, 7], np.int32)
+    say(f"[walks] general n_comp={n_comp} bimolecular={bimolecular} reps={reps}")
+    g = check(p)
+    assert g["transitions"].sum() > 1000
