@@ -636,8 +636,8 @@ __device__ __forceinline__ double row_prefix_sum(double v) {
     return v;
 }
 
-// One chain walked by the sixteen wavefronts of a workgroup, kDayBlock attempts
-// per round (attempt kbase + t for thread t): the scheme of walk_round, with
+// One chain walked by the wavefronts of a workgroup (sixteen at most), an
+// attempt a thread per round (attempt kbase + t for thread t): the scheme of walk_round, with
 // the picks of each wavefront shared in LDS as its flows (Rules::flows), so
 // that an attempt's state is the round's state after the flows of the
 // wavefronts below and of the lanes below in its own. One barrier per pass: a
@@ -669,13 +669,23 @@ template <class Rules>
 __device__ bool walk_group(const Model &m, typename Rules::State &c, uint32_t &kbase, uint32_t node, uint32_t day,
                            uint32_t key0, uint32_t key1, unsigned long long *status, int32_t r) {
     constexpr int NT = Rules::NT, K = Rules::kFlows;
-    constexpr int kRound = kDayBlock, kWords = (K + 2) / 2;  // flows and the moved mark, two to a word
+    constexpr int kWords = (K + 2) / 2;  // flows and the moved mark, two to a word
+    const int round = (int)blockDim.x;
     __shared__ int32_t sh_flow[2][kWords][kDayWaves];
     __shared__ double sh_head[64], sh_total[kDayWaves], sh_before, sh_at;
     __shared__ int32_t sh_tie[kDayWaves], sh_special;
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const unsigned long long below = (1ull << lane) - 1ull;
     int buf = 0;
+    if (round < kDayBlock) {  // the wavefronts that are not there add nothing
+        if (t < kDayWaves) {
+#pragma unroll
+            for (int k = 0; k < kWords; ++k) sh_flow[0][k][t] = sh_flow[1][k][t] = 0;
+            sh_total[t] = 0.0;
+            sh_tie[t] = 0;
+        }
+        __syncthreads();
+    }
     // publish this wavefront's flows n (and mark); after the barrier, before[]
     // and all[] are the flows of the wavefronts below and of all; returns
     // whether any wavefront set its mark
@@ -776,7 +786,7 @@ __device__ bool walk_group(const Model &m, typename Rules::State &c, uint32_t &k
             done = sh_special;
             ended = done < 64;
         }
-        while (!ended && done < kRound) {
+        while (!ended && done < round) {
             const int e = (int)((__double_as_longlong(s) >> 52) & 0x7ff) - 1023;
             if (e < -960) return false;  // too small to scale; nothing of this round applied
             const double up = __longlong_as_double((long long)(1023 + 52 - e) << 52);    // 2^(52-e)
@@ -800,7 +810,7 @@ __device__ bool walk_group(const Model &m, typename Rules::State &c, uint32_t &k
             const uint32_t odd = (uint32_t)__ballot(sh_tie[lane & 15] != 0 || !(sums < T)) & 0xffffu;
             if (odd == 0u) {
                 s = (S0 + lane_f64(sums, kDayWaves - 1)) * down;
-                done = kRound;
+                done = round;
                 break;
             }
             if (wave == __builtin_ctz(odd)) {
@@ -827,7 +837,7 @@ __device__ bool walk_group(const Model &m, typename Rules::State &c, uint32_t &k
             A = SIM_MAX_FIRED - c.fired;
             limit = true;
         }
-        if (A < kRound) {
+        if (A < round) {
             const int nw = A - 64 * wave;
             int n[K], before[K];
             Rules::flows(j, nw >= 64 ? ~0ull : (nw > 0 ? ((1ull << nw) - 1ull) : 0ull), n);
@@ -841,8 +851,8 @@ __device__ bool walk_group(const Model &m, typename Rules::State &c, uint32_t &k
             if (t == 0) atomicMin(status, (STATUS_LIMIT_TAG << 32) | (unsigned long long)(uint32_t)r);
             return true;
         }
-        if (A < kRound || !(c.lam > 0.0)) return true;
-        kbase = kbase + kRound;
+        if (A < round || !(c.lam > 0.0)) return true;
+        kbase = kbase + round;
     }
 }
 
@@ -1170,16 +1180,6 @@ __device__ void flush_tile(const Model &m, const DevState &s, const Tally<NC> &t
     __syncthreads();
 }
 
-// Per-lane parameters of a replicate tile, staged in LDS once per tile (every
-// position of a tile belongs to one instance, so lane r has the same set):
-// rate constants, shedding and decay rates and the Philox key.
-struct TileParams {
-    double (*coef)[64];   // [MAXT][64]
-    double *alpha;        // [64]
-    double (*beta)[64];   // [4][64]
-    uint32_t *key0, *key1;
-};
-
 // Draw n of the tot individuals in the compartments of mask from x without
 // replacement (Sec. 3.2): draw q picks the individual at a uniform position
 // in [0, remaining) of the selected compartments in ascending order, from the
@@ -1289,20 +1289,20 @@ __device__ __forceinline__ LaneLoad<NC> lane_load(const Model &m, const DevState
 }
 
 // phi_{d+1} = (1 - beta(day0 + d)) phi_d + alpha I/N (eq:siminfpressure, Euler
-// step) from the counts y, and I.
+// step) from the counts y, and I (sums of counts are exact in binary64).
 template <int NC>
 __device__ __forceinline__ double phi_next(const Model &m, const int32_t *y, double alpha, double beta, double phi,
-                                           long long *Iout) {
-    long long I = 0, N = 0;
+                                           double *Iout) {
+    double I = 0.0, N = 0.0;
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-        if ((m.imask >> c) & 1u) I += y[c];
-        if ((m.nmask >> c) & 1u) N += y[c];
+        if ((m.imask >> c) & 1u) I += (double)y[c];
+        if ((m.nmask >> c) & 1u) N += (double)y[c];
     }
     *Iout = I;
     const double a = 1.0 - beta;
     const double b = a * phi;
-    const double shed = N > 0 ? alpha * ((double)I / (double)N) : 0.0;
+    const double shed = N > 0.0 ? alpha * (I / N) : 0.0;
     return b + shed;
 }
 
@@ -1315,8 +1315,7 @@ __device__ __forceinline__ double phi_next(const Model &m, const int32_t *y, dou
 template <class Rules>
 __device__ __forceinline__ void day_wave(const Model &m, const DevState &s, int64_t l, int32_t d,
                                          bool prologue, bool ssa, Tally<Rules::NC> &t, int32_t r_end,
-                                         unsigned long long *status, const TileParams *tp = nullptr,
-                                         bool lane_on = true) {
+                                         unsigned long long *status) {
     constexpr int NC = Rules::NC, NT = Rules::NT;
     const int32_t R = s.R, RL = s.RL;
     const bool in_range = l < s.L;
@@ -1329,7 +1328,7 @@ __device__ __forceinline__ void day_wave(const Model &m, const DevState &s, int6
     double phi = q.phi;
     int32_t nid = q.nid, inst = q.inst;
     // padding positions and idle lanes take part in the wavefront steps only
-    const bool active = lane_on && r < r_end && nid >= 0;
+    const bool active = r < r_end && nid >= 0;
     if (!active) {
         inst = 0;
         phi = 0.0;
@@ -1338,16 +1337,14 @@ __device__ __forceinline__ void day_wave(const Model &m, const DevState &s, int6
     }
     const int32_t set = inst * R + r;
     const uint32_t node = active ? (uint32_t)nid : 0u;
-    auto phi_after = [&](const int32_t *y, int32_t dd, double ph, long long *Iout) {
+    auto phi_after = [&](const int32_t *y, int32_t dd, double ph, double *Iout) {
         const int q = season((int64_t)m.day0 + dd);
-        const int lane = threadIdx.x & 63;
-        return phi_next<NC>(m, y, tp ? tp->alpha[lane] : s.alpha[set], tp ? tp->beta[q][lane] : s.beta[set * 4 + q], ph,
-                            Iout);
+        return phi_next<NC>(m, y, s.alpha[set], s.beta[set * 4 + q], ph, Iout);
     };
     if (active && prologue) {
         const double phi_in = phi;
         const int32_t dp = d - 1;
-        long long I = 0;
+        double I = 0.0;
         if (m.phi_pre) {
             // phi was already fed by the state before the events of day dp
 #pragma unroll
@@ -1356,7 +1353,7 @@ __device__ __forceinline__ void day_wave(const Model &m, const DevState &s, int6
         } else {
             phi = phi_after(x, dp, phi, &I);
         }
-        t.prev += I > 0 ? 1 : 0;
+        t.prev += I > 0.0 ? 1 : 0;
 #pragma unroll
         for (int c = 0; c < NC; ++c) t.tot[c] += x[c];
         const int32_t slot = rec;
@@ -1374,12 +1371,11 @@ __device__ __forceinline__ void day_wave(const Model &m, const DevState &s, int6
     if (__ballot(ssa) == 0ull) return;
     const bool walks = active && ssa;
     typename Rules::State ch;
-    const int lane_t = threadIdx.x & 63;
-    const uint32_t key0 = active ? (tp ? tp->key0[lane_t] : s.seed[inst]) : 0u;
-    const uint32_t key1 = active ? (tp ? tp->key1[lane_t] : s.repid[set]) : 0u;
+    const uint32_t key0 = active ? s.seed[inst] : 0u;
+    const uint32_t key1 = active ? s.repid[set] : 0u;
 #pragma unroll
     for (int k = 0; k < NT; ++k) {
-        double c = active && trans_on<NT>(m, k) ? (tp ? tp->coef[k][lane_t] : s.coef[set * m.nt + k]) : 0.0;
+        double c = active && trans_on<NT>(m, k) ? s.coef[set * m.nt + k] : 0.0;
         if ((m.uses_phi >> k) & 1u) c = c * phi;
         ch.cphi[k] = c;
     }
@@ -1401,7 +1397,7 @@ __device__ __forceinline__ void day_wave(const Model &m, const DevState &s, int6
         int32_t y[NC];
 #pragma unroll
         for (int c = 0; c < NC; ++c) y[c] = (int32_t)ch.xd[c];
-        long long I = 0;
+        double I = 0.0;
         const double phi2 = phi_after(y, d, phi, &I);
         if (__double_as_longlong(phi2) != __double_as_longlong(phi)) s.phi[l] = phi2;
     }
@@ -1412,9 +1408,9 @@ __device__ __forceinline__ void event_task(const Model &m, const DevState &s, co
                                            int32_t r, int32_t d, unsigned long long *status);
 
 // The private tasks of one unit (a workgroup's positions) on day d, right after
-// its SSA: lane_of_pair maps the pairs (task, lane) of the workgroup, nl lanes
-// per position starting at r0, lanes r >= r_end idle. The SSA results of the
-// unit must be visible to the whole workgroup (a workgroup barrier first).
+// its SSA: the pairs (task, lane) of the workgroup, nl lanes per position
+// starting at r0, lanes r >= r_end idle. The SSA results of the unit must be
+// visible to the whole workgroup (a workgroup barrier first).
 template <int NC>
 __device__ __forceinline__ void private_tasks(const Model &m, const DevState &s, const DevEvents &ev, int32_t d,
                                               int64_t unit, int64_t n_units, int32_t r0, int32_t nl, int32_t r_end,
@@ -1525,7 +1521,7 @@ struct EventDayShared {
 // once. What binds a day is the latency of the walks' dependent arithmetic, so
 // the chains of a few nodes are spread over many wavefronts: sixteen a unit,
 // and units small enough for every compute unit to have one (lane_unit on the
-// host). With four wavefronts a unit of 256 nodes, each walking its 64 nodes'
+// host); with more units than that, fewer. With four wavefronts a unit of 256 nodes, each walking its 64 nodes'
 // chains attempt by attempt in their own lanes, a day's SSA took about 18 us
 // whatever its chains' lengths.
 // The longest chains: those of group_min_attempts and more, in classes of a
@@ -1585,7 +1581,7 @@ __global__ __launch_bounds__(kDayBlock) void k_day(Model m, DevState s, DevEvent
     }
     if (!block_ok_once(s.status)) return;
     const uint32_t key0 = s.seed[set], key1 = s.repid[set];
-    const bool lds = npe <= kDayBlock;
+    const bool lds = npe <= (int)blockDim.x;
     const bool has = lds && t < npe;
     const int32_t stage_entry = t < nst ? ev.unit_stage[st0 + t] : -1;
     if (has) {
@@ -1600,7 +1596,8 @@ __global__ __launch_bounds__(kDayBlock) void k_day(Model m, DevState s, DevEvent
         double phi = q.phi;
         if (prologue) {
             const int32_t dp = d - 1;
-            long long I = 0, prev = 0;
+            double I = 0.0;
+            long long prev = 0;
             if (active) {
                 if (m.phi_pre) {
                     // phi was already fed by the state before the events of day dp
@@ -1610,7 +1607,7 @@ __global__ __launch_bounds__(kDayBlock) void k_day(Model m, DevState s, DevEvent
                 } else {
                     phi = phi_next<NC>(m, q.x, s.alpha[set], s.beta[set * 4 + season((int64_t)m.day0 + dp)], phi, &I);
                 }
-                prev = I > 0 ? 1 : 0;
+                prev = I > 0.0 ? 1 : 0;
                 if (rec >= 0) {
                     const int64_t at = (int64_t)rec * s.n_nodes + s.inst_off[set] + q.nid;
 #pragma unroll
@@ -1661,7 +1658,7 @@ __global__ __launch_bounds__(kDayBlock) void k_day(Model m, DevState s, DevEvent
         }
     }
     __syncthreads();
-    if (prologue && t >= kDayBlock - 64 && lane < 1 + NC) {
+    if (prologue && t >= (int)blockDim.x - 64 && lane < 1 + NC) {
         long long sum = 0;
         for (int w = 0; w * 64 < U; ++w) sum += sh.part[w][lane];
         if (lane == 0) {
@@ -1755,7 +1752,7 @@ __global__ __launch_bounds__(kDayBlock) void k_day(Model m, DevState s, DevEvent
             int32_t y[NC];
 #pragma unroll
             for (int c = 0; c < NC; ++c) y[c] = sh.x[c][t];
-            long long I = 0;
+            double I = 0.0;
             const double phi = sh.phi[t];
             const double phi2 = phi_next<NC>(m, y, s.alpha[set], s.beta[set * 4 + season((int64_t)m.day0 + d)], phi, &I);
             if (__double_as_longlong(phi2) != __double_as_longlong(phi)) s.phi[base + t] = phi2;
@@ -1786,62 +1783,34 @@ __global__ __launch_bounds__(kDayBlock) void k_day(Model m, DevState s, DevEvent
     }
 }
 
-// Replicate tiles (replicate lanes in columns of 64): a tile workgroup takes
-// positions [x * tile_nodes, (x + 1) * tile_nodes) and the replicate lanes
-// [64 y, 64 y + 64) of column y; its wavefronts take the positions one at a
-// time, and a lane always holds the same replicate, so its counts add up in
-// registers. In a slot handle the columns are those of the step's run list,
-// each holding 64 / slot_lanes slots: d is the handle's step, a slot's own
-// day is d - t0, and its lanes past its replicate count are idle.
+// Replicate tiles (replicate lanes in columns of 64): workgroup (x, y) takes the
+// x-th of gridDim.x ranges of positions and the replicate lanes [64 y, 64 y + 64)
+// of column y; the ranges are as even as groups of four positions allow (an
+// instance and a region fill whole groups). In a slot handle the columns are those of the
+// step's run list, each holding 64 / slot_lanes slots: d is the handle's step,
+// a slot's own day is d - t0, and its lanes past its replicate count are idle.
 //
-// Past the regular tiles, workgroups of four wavefronts take the heavy herds:
-// each wavefront one (herd, replicate) chain, walked with the whole wavefront
-// (kHeavyBlocks workgroups cover the 64 replicate lanes of a column), then the
-// herd's private task for that replicate; the units holding heavy herds are
-// skipped by the regular tiles.
-constexpr int kHeavyBlocks = 64 / kWaves;
+// Its wavefronts first close the previous day of every lane, a position at a
+// time with a lane per replicate (so that counts add up in registers), and list
+// the lanes with a chain to walk; then every lane takes listed chains, the long
+// ones first, and walks them attempt by attempt, kTileRefill or more lanes of a
+// wavefront taking their next chains together. The lanes stay busy whatever the
+// mix of empty herds, short and long chains at a position: walked where they
+// are listed, a position's chains kept a wavefront until the longest had ended,
+// with 39 % of the lanes idle.
+//
+// Chains that expect s.far_min attempts or more are not walked there but listed
+// for a launch of their own (k_day_far), a wavefront each, which spreads them
+// over the chip wherever their herds sit. The day's private tasks run in a
+// launch over all of them after that.
+constexpr int kTileList = 4096;   // chains listed before they are walked
+constexpr int kTileBatch = 32;    // positions between looks at the list's length
+constexpr int kTileSpan = 1024;   // positions listed before they are walked (16-bit entries)
+constexpr int kTileRefill = 16;
+constexpr double kTileLong = 32.0;
 
-template <class Rules>
-__device__ __forceinline__ void heavy_chain(const Model &m, const DevState &s, const DevEvents &ev, int64_t hb,
-                                            int32_t r, int32_t d, bool prologue, bool ssa, bool on,
-                                            unsigned long long *status) {
-    constexpr int NC = Rules::NC;
-    const int lane = threadIdx.x & 63;
-    const int32_t pos = s.heavy_pos[hb / kHeavyBlocks];
-    if (!on) return;  // the same in every lane of the wavefront
-    Tally<NC> t{};
-    day_wave<Rules>(m, s, lane == 0 ? (int64_t)pos * s.RL + r : s.L, d, prologue, ssa, t, s.RL, status);
-    const int32_t inst = s.inst[pos];
-    const int64_t S = (int64_t)s.n_inst * s.R;
-    const int64_t set = (int64_t)inst * s.R + r;
-    if (lane == 0) {
-        if (prologue) {
-            if (t.prev) atomicAdd(&s.prevalence[(d - 1) * S + set], (int32_t)t.prev);
-            const int32_t region = s.n_regions ? s.pos_region[pos] : -1;
-#pragma unroll
-            for (int c = 0; c < NC; ++c)
-                if (comp_on<NC>(m, c) && t.tot[c]) {
-                    atomicAdd((unsigned long long *)&s.totals[((d - 1) * S + set) * m.nc + c], (unsigned long long)t.tot[c]);
-                    if (region >= 0)
-                        atomicAdd((unsigned long long *)&s.regional[(((d - 1) * S + set) * s.n_regions + region) * m.nc + c],
-                                  (unsigned long long)t.tot[c]);
-                }
-        }
-        if (ssa && t.trans) {
-            atomicAdd((unsigned long long *)&s.transitions[d * S + set], (unsigned long long)t.trans);
-            atomicMax(&s.max_fired[d * S + set], t.most);
-        }
-    }
-    if (!ssa) return;
-    // the herd's private task of the day (at most one per node and day), run
-    // by another lane of this wavefront: lane 0's stores first, then fresh lines
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    fresh_l1();
-    const int64_t k = (int64_t)d * (s.Np / s.tile_nodes) + pos / s.tile_nodes;
-    const int64_t t0 = ev.priv_off[k], t1 = ev.priv_off[k + 1];
-    for (int64_t tk = t0 + lane; tk < t1; tk += 64)
-        if (ev.node[ev.task_off[tk]] == pos) event_task<NC>(m, s, ev, tk, r, d, status);
-}
+// Class of a far chain (longest first) in s.far_list.
+__device__ __forceinline__ int far_class(double lam) { return lam >= 2048.0 ? 0 : (lam >= 256.0 ? 1 : 2); }
 
 // A lane r of a slot handle: its slot (slot_lanes lanes each), whether the
 // slot runs at handle step d, the slot's own day and its error word. A slot
@@ -1874,94 +1843,392 @@ __device__ __forceinline__ SlotLane slot_lane(const DevState &s, int32_t d, int3
 template <class Rules, bool SLOTS>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(Rules::kTileWaves, 8))) void k_day_tile(
     Model m, DevState s, DevEvents ev, int32_t d, int32_t prologue, int32_t ssa) {
-    constexpr int NC = Rules::NC;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int64_t nx = s.Np / s.tile_nodes;
-    // Dispatch order (workgroups start in linear order): the tiles of every
-    // column first, then the heavy-herd chains, largest herd first with all
-    // its columns, so that the short chains of the smaller heavy herds fill
-    // the compute units that the last tiles leave free. bx is the tile (or
-    // nx + heavy block) and by the grid row of the workgroup.
-    const int64_t lin = (int64_t)blockIdx.x + (int64_t)gridDim.x * blockIdx.y;
-    const int64_t n_tiles = nx * gridDim.y;
-    const bool heavy = lin >= n_tiles;
-    const int64_t bx = heavy ? nx + (lin - n_tiles) / gridDim.y : lin % nx;
-    const int64_t by = heavy ? (lin - n_tiles) % gridDim.y : lin / nx;
-    if (s.n_heavy && bx < nx && s.unit_heavy[bx]) return;  // uniform over the workgroup
+    constexpr int NC = Rules::NC, NT = Rules::NT;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int64_t bx = blockIdx.x, by = blockIdx.y;
     if constexpr (!SLOTS) {
         if (!block_ok_once(s.status)) return;
     }
+    __shared__ double sh_tau[kWaves][64];
     // the column of 64 replicate lanes (a slot handle launches only the
     // columns that run this step)
     const int32_t col = SLOTS ? s.run_cols[by] : (int32_t)by;
-    if (heavy) {
-        const int64_t hb = bx - nx;
-        const int32_t rh = col * 64 + (int32_t)(hb % kHeavyBlocks) * kWaves + wave;
-        if constexpr (SLOTS) {
-            const SlotLane q = slot_lane(s, d, rh);
-            heavy_chain<Rules>(m, s, ev, hb, rh, q.day, q.prologue, q.ssa, q.on, q.status);
-        } else {
-            heavy_chain<Rules>(m, s, ev, hb, rh, d, prologue != 0, ssa != 0, rh < s.R, s.status);
-        }
-        return;
-    }
-    const int64_t pos0 = bx * s.tile_nodes;
     const int32_t r = col * 64 + lane;
     bool on = r < s.R, pro = prologue != 0, walk = ssa != 0;
     int32_t day = d;
-    unsigned long long *status = s.status;
     if constexpr (SLOTS) {
         const SlotLane q = slot_lane(s, d, r);
         on = q.on;
         pro = q.prologue;
         walk = q.ssa;
         day = q.day;
-        status = q.status;
         if (!__syncthreads_or(on ? 1 : 0)) return;  // no lane of the column runs
     }
-    __shared__ double sh_coef[Rules::NT][64], sh_alpha[64], sh_beta[4][64];
-    __shared__ uint32_t sh_k0[64], sh_k1[64];
-    __shared__ int32_t sh_next;  // the next position of the tile that no wavefront has taken
-    if (threadIdx.x == 0) sh_next = kWaves;
-    if (wave == 0 && on) {
-        const int32_t inst = s.inst[pos0];  // every position of a tile belongs to one instance
-        const int64_t set = (int64_t)inst * s.R + r;
+    pro = pro && on;
+    walk = walk && on;
+    // per replicate lane: rate constants, shedding and decay rates, Philox key,
+    // day, and what its chains add to the day's records
+    __shared__ double sh_coef[NT][64], sh_alpha[64], sh_beta[4][64];
+    __shared__ uint32_t sh_k1[64];
+    __shared__ int32_t sh_day[64], sh_most[64];
+    __shared__ unsigned long long sh_trans[64];
+    // listed chains, position << 6 | lane: long ones from the front, short ones from the back
+    constexpr int kList = kTileList;
+    __shared__ uint16_t sh_list[kList];
+    __shared__ int32_t sh_n[2], sh_next, sh_end;
+    const int32_t rec = !SLOTS && prologue ? s.rec_slot[d - 1] : -1;
+    const int season_in = pro ? season((int64_t)m.day0 + day - 1) : 0;
+    const int season_out = walk ? season((int64_t)m.day0 + day) : 0;
+    const int64_t groups = s.Np / kWaves;
+    int64_t p = bx * groups / gridDim.x * kWaves;
+    const int64_t p_end = (bx + 1) * groups / gridDim.x * kWaves;
+    while (p < p_end) {
+        // a run of positions of one instance and one region
+        const int32_t inst = s.inst[p], region = s.n_regions ? s.pos_region[p] : -1;
+        const uint32_t key0 = s.seed[inst];
+        if (threadIdx.x == 0) sh_end = (int32_t)p_end;
+        __syncthreads();
+        if (s.n_inst > 1 || s.n_regions)
+            for (int64_t q = p + kWaves * (1 + (int64_t)threadIdx.x); q < p_end; q += kWaves * kBlock)
+                if (s.inst[q] != inst || (s.n_regions && s.pos_region[q] != region)) atomicMin(&sh_end, (int32_t)q);
+        if (wave == 0) {
+            const int64_t set = (int64_t)inst * s.R + (on ? r : 0);
 #pragma unroll
-        for (int k = 0; k < Rules::NT; ++k) sh_coef[k][lane] = trans_on<Rules::NT>(m, k) ? s.coef[set * m.nt + k] : 0.0;
-        sh_alpha[lane] = s.alpha[set];
+            for (int k = 0; k < NT; ++k) sh_coef[k][lane] = on && trans_on<NT>(m, k) ? s.coef[set * m.nt + k] : 0.0;
+            sh_alpha[lane] = on ? s.alpha[set] : 0.0;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) sh_beta[q][lane] = s.beta[set * 4 + q];
-        sh_k0[lane] = s.seed[inst];
-        sh_k1[lane] = s.repid[set];
-    }
-    __syncthreads();
-    const TileParams tp{sh_coef, sh_alpha, sh_beta, sh_k0, sh_k1};
-    Tally<NC> t{};
-    // positions are taken one at a time as wavefronts come free: a herd with
-    // a long chain holds up only its own wavefront, the others take the
-    // remaining positions (nodes are independent within the day, and the
-    // tallies are integer sums and maxima, so the order changes no result)
-    for (int j = wave; j < s.tile_nodes;) {
-        const int64_t pos = pos0 + j;
-        if (pos >= s.Np) break;
-        day_wave<Rules>(m, s, pos * s.RL + r, day, pro, walk, t, s.RL, status, &tp, on);
-        int32_t next = 0;
-        if (lane == 0) next = atomicAdd(&sh_next, 1);
-        j = __shfl(next, 0);
-    }
-    // instances are padded to whole tiles: one instance per workgroup
-    flush_tile<NC>(m, s, t, on ? s.inst[pos0] * s.R + r : -1, pro ? day - 1 : -1, walk ? day : -1,
-                   s.n_regions ? s.pos_region[pos0] : -1);
-    if constexpr (SLOTS) {
-        // each slot of the column at its own day (flush_tile's barriers publish the SSA results)
-        for (int32_t g = 0; g < 64 / s.slot_lanes; ++g) {
-            const int32_t r0 = col * 64 + g * s.slot_lanes;
-            const SlotLane q = slot_lane(s, d, r0);  // the same in every thread
-            if (q.ssa)
-                private_tasks<NC>(m, s, ev, q.day, bx, nx, r0, s.slot_lanes, r0 + q.n_live, q.status);
+            for (int q = 0; q < 4; ++q) sh_beta[q][lane] = on ? s.beta[set * 4 + q] : 0.0;
+            sh_k1[lane] = on ? s.repid[set] : 0u;
+            sh_day[lane] = day;
+            sh_most[lane] = 0;
+            sh_trans[lane] = 0ull;
         }
-    } else {
-        if (ssa) private_tasks<NC>(m, s, ev, d, bx, nx, col * 64, 64, s.R, s.status);
+        if (threadIdx.x < 2) sh_n[threadIdx.x] = 0;
+        if (threadIdx.x == 2) sh_next = 0;
+        __syncthreads();
+        const int64_t run_end = sh_end;
+        Tally<NC> t{};
+        while (p < run_end) {
+            const int64_t base = p;
+            // one position per wavefront at a time, the loads of its next one in
+            // flight meanwhile (a position is little more than a round trip to
+            // memory otherwise); past the end, the first position's state
+            int32_t nid_next = -1, x_next[NC];
+            double phi_ahead = 0.0;
+            auto fetch = [&](int64_t j) {
+                nid_next = j < run_end ? s.node_id[j] : -1;
+                const int64_t l = (j < run_end ? j : base) * s.RL + r;
+#pragma unroll
+                for (int c = 0; c < NC; ++c) x_next[c] = on && comp_on<NC>(m, c) ? s.u[(int64_t)c * s.L + l] : 0;
+                phi_ahead = on ? s.phi[l] : 0.0;
+            };
+            fetch(base + wave);
+            int n_far, n_all;
+            do {
+                const int64_t batch_end = min(p + kTileBatch, run_end);
+                for (int64_t j = p + wave; j < batch_end; j += kWaves) {
+                    const int64_t l = j * s.RL + r;
+                    const int32_t nid = nid_next;
+                    int32_t x[NC];
+#pragma unroll
+                    for (int c = 0; c < NC; ++c) x[c] = x_next[c];
+                    const double phi_in = phi_ahead;
+                    fetch(j + kWaves);
+                    if (nid < 0) continue;  // padding
+                    double phi = phi_in;
+                    if (pro) {
+                        double I = 0.0;
+                        if (m.phi_pre) {
+                            // phi was already fed by the state before the events of the day
+#pragma unroll
+                            for (int c = 0; c < NC; ++c)
+                                if ((m.imask >> c) & 1u) I += x[c];
+                        } else {
+                            phi = phi_next<NC>(m, x, sh_alpha[lane], sh_beta[season_in][lane], phi, &I);
+                        }
+                        t.prev += I > 0.0 ? 1 : 0;
+#pragma unroll
+                        for (int c = 0; c < NC; ++c) t.tot[c] += x[c];
+                        if (rec >= 0) {
+                            const int64_t at = ((int64_t)rec * s.R + r) * s.n_nodes + s.inst_off[inst] + nid;
+#pragma unroll
+                            for (int c = 0; c < NC; ++c)
+                                if (comp_on<NC>(m, c)) s.snap_u[at * m.nc + c] = x[c];
+                            s.snap_v[at] = phi;
+                        }
+                    }
+                    double lam = 0.0;
+                    if (walk) {
+                        typename Rules::State ch;
+#pragma unroll
+                        for (int k = 0; k < NT; ++k) {
+                            const double c = sh_coef[k][lane];
+                            ch.cphi[k] = (m.uses_phi >> k) & 1u ? c * phi : c;
+                        }
+#pragma unroll
+                        for (int c = 0; c < NC; ++c) ch.xd[c] = (double)x[c];
+                        Rules::rates(m, ch);
+                        lam = ch.lam;
+                        if (m.phi_pre && !(lam > 0.0)) {
+                            // eq:numstep5 as written: phi from the state after the SSA, before the events
+                            double I = 0.0;
+                            phi = phi_next<NC>(m, x, sh_alpha[lane], sh_beta[season_out][lane], phi, &I);
+                        }
+                    }
+                    if (__double_as_longlong(phi) != __double_as_longlong(phi_in)) s.phi[l] = phi;
+                    bool live = lam > 0.0;
+                    if (__ballot(lam >= s.far_min) != 0ull) {
+                        const int cls = lam >= s.far_min ? far_class(lam) : -1;
+#pragma unroll
+                        for (int i = 0; i < kFarLists; ++i) {
+                            const unsigned long long in = __ballot(cls == i);
+                            if (in == 0ull) continue;
+                            int a = 0;
+                            if (lane == 0) a = atomicAdd(&s.far_n[(d & 1) * kFarLists + i], (int)__popcll(in));
+                            a = __builtin_amdgcn_readfirstlane(a) + (int)__popcll(in & ((1ull << lane) - 1ull));
+                            if (cls == i && a < s.far_cap) {  // a chain past the list's end is walked here
+                                s.far_list[(int64_t)i * s.far_cap + a] = (int32_t)l;
+                                live = false;
+                            }
+                        }
+                    }
+                    const unsigned long long any = __ballot(live);
+                    if (any != 0ull) {
+                        const unsigned long long far = any & __ballot(lam >= kTileLong), near = any & ~far;
+                        int a = 0, b = 0;
+                        if (lane == 0) {
+                            if (far != 0ull) a = atomicAdd(&sh_n[0], (int)__popcll(far));
+                            if (near != 0ull) b = atomicAdd(&sh_n[1], (int)__popcll(near));
+                        }
+                        a = __builtin_amdgcn_readfirstlane(a);
+                        b = __builtin_amdgcn_readfirstlane(b);
+                        const unsigned long long below = (1ull << lane) - 1ull;
+                        if (live)
+                            sh_list[(far >> lane) & 1ull ? a + (int)__popcll(far & below) : kList - 1 - b - (int)__popcll(near & below)] =
+                                (uint16_t)(((int)(j - base) << 6) | lane);
+                    }
+                }
+                __syncthreads();
+                n_far = sh_n[0];
+                n_all = n_far + sh_n[1];
+                p = batch_end;
+                __syncthreads();  // the lengths are read before the next batch lists
+            } while (p < run_end && n_all <= kList - kTileBatch * 64 && p - base <= kTileSpan - kTileBatch);
+            fresh_l1();  // phi of the listed chains was stored by another wavefront
+            // the walks: a chain is that of position at >> 6 and replicate lane at & 63
+            auto entry = [&](int i) { return (int)sh_list[i < n_far ? i : kList - 1 - (i - n_far)]; };
+            auto lane_of = [&](int e) { return (base + (e >> 6)) * s.RL + col * 64 + (e & 63); };
+            auto start = [&](int e, typename Rules::State &ch) {  // returns phi
+                const int ln = e & 63;
+                const int64_t l = lane_of(e);
+                const double phi = s.phi[l];
+#pragma unroll
+                for (int cc = 0; cc < NC; ++cc) ch.xd[cc] = comp_on<NC>(m, cc) ? (double)s.u[(int64_t)cc * s.L + l] : 0.0;
+#pragma unroll
+                for (int kk = 0; kk < NT; ++kk) {
+                    const double cc = sh_coef[kk][ln];
+                    ch.cphi[kk] = (m.uses_phi >> kk) & 1u ? cc * phi : cc;
+                }
+                ch.clock = 0.0;
+                ch.fired = 0;
+            };
+            auto finish = [&](int e, const typename Rules::State &ch) {
+                const int ln = e & 63;
+                const int64_t l = lane_of(e);
+                if (ch.fired) {
+#pragma unroll
+                    for (int cc = 0; cc < NC; ++cc)
+                        if (comp_on<NC>(m, cc)) s.u[(int64_t)cc * s.L + l] = (int32_t)ch.xd[cc];
+                    atomicAdd(&sh_trans[ln], (unsigned long long)ch.fired);
+                    atomicMax(&sh_most[ln], ch.fired);
+                }
+                if (m.phi_pre) {
+                    // eq:numstep5 as written: phi from the state after the SSA, before the events
+                    int32_t y[NC];
+#pragma unroll
+                    for (int cc = 0; cc < NC; ++cc) y[cc] = (int32_t)ch.xd[cc];
+                    double I = 0.0;
+                    const double phi = s.phi[l];
+                    const double phi2 = phi_next<NC>(m, y, sh_alpha[ln],
+                                                     sh_beta[season((int64_t)m.day0 + sh_day[ln])][ln], phi, &I);
+                    if (__double_as_longlong(phi2) != __double_as_longlong(phi)) s.phi[l] = phi2;
+                }
+            };
+            auto status_of = [&](int ln) { return SLOTS ? s.status + (col * 64 + ln) / s.slot_lanes : s.status; };
+            typename Rules::State c;
+            bool has = false, live = false, dry = n_all == 0;
+            int at = 0;
+            uint32_t k = 0, node = 0;
+            while (true) {
+                const unsigned long long lives = __ballot(live);
+                const int idle = 64 - (int)__popcll(lives);
+                if (lives == 0ull || (!dry && idle >= kTileRefill)) {
+                    if (has && !live) {
+                        finish(at, c);
+                        has = false;
+                    }
+                    if (!dry) {
+                        int first = 0;
+                        if (lane == 0) first = atomicAdd(&sh_next, idle);
+                        first = __builtin_amdgcn_readfirstlane(first);
+                        const int i = first + (int)__popcll(~lives & ((1ull << lane) - 1ull));
+                        dry = first + idle >= n_all;
+                        if (!live && i < n_all) {
+                            at = entry(i);
+                            node = (uint32_t)s.node_id[base + (at >> 6)];
+                            start(at, c);
+                            Rules::rates(m, c);
+                            k = 0;
+                            has = live = true;
+                        }
+                    }
+                    if (__ballot(live) == 0ull) break;
+                    continue;
+                }
+                const int ln = at & 63;
+                const uint32_t dd = SLOTS ? (uint32_t)sh_day[ln] : (uint32_t)d;
+                // the list is empty and few chains are left, one of which still
+                // expects many attempts: the whole wavefront walks them one after
+                // another
+                const uint32_t nlive = 64u - (uint32_t)idle;
+                if (dry && nlive <= s.few_chains &&
+                    (nlive == 1 || __ballot(live && c.lam * (1.0 - c.clock) > 10.0 * (double)nlive) != 0ull)) {
+                    for (unsigned long long left = lives; left != 0ull; left &= left - 1ull) {
+                        const int h = __ffsll((long long)left) - 1;
+                        typename Rules::State u;
+#pragma unroll
+                        for (int i = 0; i < NC; ++i) u.xd[i] = lane_f64(c.xd[i], h);
+#pragma unroll
+                        for (int i = 0; i < NT; ++i) u.cphi[i] = lane_f64(c.cphi[i], h);
+                        u.clock = lane_f64(c.clock, h);
+                        u.fired = __builtin_amdgcn_readlane(c.fired, h);
+                        Rules::reactants(m, u);
+                        const int lh = __builtin_amdgcn_readlane(ln, h);
+                        walk_wave<Rules>(m, u, (uint32_t)__builtin_amdgcn_readlane((int)k, h),
+                                         (uint32_t)__builtin_amdgcn_readlane((int)node, h),
+                                         (uint32_t)__builtin_amdgcn_readlane((int)dd, h), key0, sh_k1[lh], status_of(lh),
+                                         inst * s.R + col * 64 + lh, sh_tau[wave]);
+                        if (lane == h) c = u;
+                    }
+                    live = false;
+                    continue;
+                }
+                if (live) {
+                    const Draw q = draw_attempt(k, node, dd, key0, sh_k1[ln]);
+                    k = k + 1;
+                    live = chain_step<Rules>(m, c, q.E, q.U, status_of(ln), inst * s.R + col * 64 + ln);
+                }
+            }
+            __syncthreads();
+            if (threadIdx.x < 2) sh_n[threadIdx.x] = 0;
+            if (threadIdx.x == 2) sh_next = 0;
+            __syncthreads();
+        }
+        if (wave == 0) {
+            t.trans = (long long)sh_trans[lane];
+            t.most = sh_most[lane];
+        }
+        flush_tile<NC>(m, s, t, on ? inst * s.R + r : -1, pro ? day - 1 : -1, walk ? day : -1, region);
+    }
+}
+
+// The day's far chains, walked by a wavefront one at a time, the longest first.
+// A chain is short against the round trips that fetch it (list, state,
+// parameters, about 10 us), so where there are more chains than wavefronts a
+// wavefront takes up to kFarBatch of the shortest class together: a lane each
+// for the loads and stores. d is the day, in a slot handle the step.
+constexpr int kFarBatch = 8;
+
+template <class Rules, bool SLOTS>
+__global__ __launch_bounds__(kBlock) void k_day_far(Model m, DevState s, DevEvents, int32_t d) {
+    constexpr int NC = Rules::NC, NT = Rules::NT;
+    __shared__ double sh_tau[kWaves][64];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int waves = (int)(gridDim.x * kWaves);
+    static_assert(kFarLists == 3, "two classes walked singly, one in batches");
+    const int32_t *counts = s.far_n + (d & 1) * kFarLists;
+    const int n0 = min(counts[0], s.far_cap), n1 = min(counts[1], s.far_cap), n2 = min(counts[2], s.far_cap);
+    if constexpr (!SLOTS) {
+        if (!block_ok_once(s.status)) return;
+    }
+    // the next day's lists start empty (this launch reads the other parity)
+    if (blockIdx.x == 0 && threadIdx.x < kFarLists) s.far_n[((d + 1) & 1) * kFarLists + threadIdx.x] = 0;
+    const int batch = max(1, min(kFarBatch, n2 / waves));
+    const int items = n0 + n1 + (n2 + batch - 1) / batch;
+    for (int w = (int)(blockIdx.x * kWaves) + wave; w < items; w += waves) {
+        int64_t at = w;
+        int count = 1;
+        if (w >= n0 + n1) {
+            at = (int64_t)2 * s.far_cap + (int64_t)(w - n0 - n1) * batch;
+            count = min(batch, n2 - (w - n0 - n1) * batch);
+        } else if (w >= n0) {
+            at = (int64_t)s.far_cap + (w - n0);
+        }
+        // lane b < count holds chain b of the batch
+        const bool mine = lane < count;
+        const int64_t l = s.far_list[at + (mine ? lane : 0)];
+        const int32_t r = (int32_t)(l % s.RL);
+        int32_t day = d;
+        unsigned long long *status = s.status;
+        if constexpr (SLOTS) {
+            const SlotLane q = slot_lane(s, d, r);
+            day = q.day;
+            status = q.status;
+        }
+        const LaneLoad<NC> q = lane_load<NC>(m, s, l);
+        const int32_t inst = s.n_inst == 1 ? 0 : q.inst;
+        const int32_t set = inst * s.R + r;
+        const uint32_t key0 = s.seed[inst], key1 = s.repid[set];
+        double cphi[NT];
+#pragma unroll
+        for (int k = 0; k < NT; ++k) {
+            const double a = trans_on<NT>(m, k) ? s.coef[set * m.nt + k] : 0.0;
+            cphi[k] = (m.uses_phi >> k) & 1u ? a * q.phi : a;
+        }
+        int32_t y[NC], fired = 0;
+#pragma unroll
+        for (int k = 0; k < NC; ++k) y[k] = q.x[k];
+        for (int b = 0; b < count; ++b) {
+            typename Rules::State c;
+#pragma unroll
+            for (int k = 0; k < NT; ++k) c.cphi[k] = lane_f64(cphi[k], b);
+#pragma unroll
+            for (int k = 0; k < NC; ++k) c.xd[k] = (double)__builtin_amdgcn_readlane(y[k], b);
+            c.clock = 0.0;
+            c.fired = 0;
+            Rules::reactants(m, c);
+            const uint64_t st = (uint64_t)status;
+            unsigned long long *stb = (unsigned long long *)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane(
+                                                                  (int)(uint32_t)(st >> 32), b) << 32) |
+                                                              (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)st, b));
+            walk_wave<Rules>(m, c, 0u, (uint32_t)__builtin_amdgcn_readlane(q.nid, b),
+                             (uint32_t)__builtin_amdgcn_readlane(day, b),
+                             (uint32_t)__builtin_amdgcn_readlane((int)key0, b),
+                             (uint32_t)__builtin_amdgcn_readlane((int)key1, b), stb,
+                             __builtin_amdgcn_readlane(set, b), sh_tau[wave]);
+            if (lane == b) {
+                fired = c.fired;
+#pragma unroll
+                for (int k = 0; k < NC; ++k) y[k] = (int32_t)c.xd[k];
+            }
+        }
+        if (mine) {
+            if (fired) {
+                const int64_t row = (int64_t)day * s.n_inst * s.R + set;
+#pragma unroll
+                for (int k = 0; k < NC; ++k)
+                    if (comp_on<NC>(m, k)) s.u[(int64_t)k * s.L + l] = y[k];
+                atomicAdd((unsigned long long *)&s.transitions[row], (unsigned long long)fired);
+                atomicMax(&s.max_fired[row], fired);
+            }
+            if (m.phi_pre) {
+                // eq:numstep5 as written: phi from the state after the SSA, before the events
+                double I = 0.0;
+                const double phi2 = phi_next<NC>(m, y, s.alpha[set], s.beta[set * 4 + season((int64_t)m.day0 + day)],
+                                                 q.phi, &I);
+                if (__double_as_longlong(phi2) != __double_as_longlong(q.phi)) s.phi[l] = phi2;
+            }
+        }
     }
 }
 
@@ -2368,7 +2635,8 @@ __global__ __launch_bounds__(kEvBlock) void k_event_day(Model m, DevState s, Dev
     event_day_levels<NC>(m, s, ev, a, d, sh);
 }
 
-// Slot handles: level k of each slot's own day, one grid row per slot of
+// Slot handles: level k of each slot's own day (k = -1: its private tasks, which
+// come before its levels), one grid row per slot of
 // s.run_slots (the slots with a day of events this step). With
 // k_end > k + 1 the grid is one workgroup per slot and runs the levels
 // k .. k_end-1 with a workgroup barrier between them.
@@ -2383,9 +2651,11 @@ __global__ __launch_bounds__(kEvBlock) void k_slot_events(Model m, DevState s, D
     if (!block_ok_once(status)) return;
     const int32_t W = s.slot_lanes;
     const int32_t lv0 = ev.lvl_ptr[d], lv_day_end = ev.lvl_ptr[d + 1];
+    const int64_t units = s.Np / s.tile_nodes;
     const int64_t stride = (int64_t)gridDim.x * kEvBlock;
-    for (int32_t kk = k; kk < k_end && lv0 + kk < lv_day_end; ++kk) {
-        const int64_t begin = ev.lvl_off[lv0 + kk], end = ev.lvl_off[lv0 + kk + 1];
+    for (int32_t kk = k; kk < k_end && (kk < 0 || lv0 + kk < lv_day_end); ++kk) {
+        const int64_t begin = kk < 0 ? ev.priv_off[d * units] : ev.lvl_off[lv0 + kk];
+        const int64_t end = kk < 0 ? ev.priv_off[(d + 1) * units] : ev.lvl_off[lv0 + kk + 1];
         const int64_t count = (end - begin) * W;
         for (int64_t t = (int64_t)blockIdx.x * kEvBlock + threadIdx.x; t < count; t += stride) {
             const int32_t rr = (int32_t)(t % W);
@@ -2578,6 +2848,8 @@ struct Kernels {
     static void *day() { return (void *)&k_day<Rules>; }
     static void *tile() { return (void *)&k_day_tile<Rules, false>; }
     static void *tile_slots() { return (void *)&k_day_tile<Rules, true>; }
+    static void *far() { return (void *)&k_day_far<Rules, false>; }
+    static void *far_slots() { return (void *)&k_day_far<Rules, true>; }
     static void *events() { return (void *)&k_events<Rules::NC>; }
     static void *levels() { return (void *)&k_event_levels<Rules::NC>; }
     static void *persist() { return (void *)&k_persist<Rules>; }
@@ -2586,14 +2858,14 @@ struct Kernels {
 };
 
 struct Table {
-    void *day, *events, *persist, *levels, *tile, *slot_events, *event_day, *tile_slots;
+    void *day, *events, *persist, *levels, *tile, *slot_events, *event_day, *tile_slots, *far, *far_slots;
 };
 
 template <class Rules>
 Table table() {
     return {Kernels<Rules>::day(),    Kernels<Rules>::events(), Kernels<Rules>::persist(),
             Kernels<Rules>::levels(), Kernels<Rules>::tile(),   Kernels<Rules>::slot_events(),
-            Kernels<Rules>::event_day(), Kernels<Rules>::tile_slots()};
+            Kernels<Rules>::event_day(), Kernels<Rules>::tile_slots(), Kernels<Rules>::far(), Kernels<Rules>::far_slots()};
 }
 
 Table pick(const Model &m) {
@@ -2604,6 +2876,31 @@ Table pick(const Model &m) {
 }
 
 }  // namespace
+
+// A day of replicate tiles over n_cols columns of 64 lanes: the tiles, then
+// their far chains. A far chain costs about twice as much an attempt as the
+// lanes of the tile kernel, so a launch that fills the chip leaves them to it
+// up to kFarWide attempts; in a launch of less than kNarrow positions (times
+// columns) the tile kernel's longest chain is what the day waits for.
+static int launch_tiles(void *tile, void *far, const Model &m, DevState s, const DevEvents &ev, int32_t d, int prologue,
+                        int ssa, int64_t n_cols, void *stream) {
+    if (s.Np % kWaves != 0) return hipErrorInvalidValue;
+    if (s.far_min == 0.0) s.far_min = s.Np * n_cols < kNarrow ? kFarNarrow : kFarWide;
+    Model mm = m;
+    DevEvents ee = ev;
+    int32_t dd = d, pro = prologue, sa = ssa;
+    void *args[] = {&mm, &s, &ee, &dd, &pro, &sa};
+    // a unit each where they are about as many as wanted: a unit's herds are dealt evenly
+    const int64_t wanted = s.Np * n_cols < kNarrow ? kTileBlocks : kTileBlocksWide, units = s.Np / s.tile_nodes;
+    const bool by_unit = units * n_cols <= wanted + wanted / 4 && units * n_cols >= wanted / 2;
+    const int64_t blocks_x = by_unit ? units : std::min<int64_t>(s.Np / kWaves, wanted / n_cols);
+    const unsigned nx = (unsigned)std::max<int64_t>(1, blocks_x);
+    const hipError_t e = hipLaunchKernel(tile, dim3(nx, (unsigned)n_cols), dim3(kBlock), args, 0, (hipStream_t)stream);
+    if (e != hipSuccess || !ssa) return (int)e;
+    void *far_args[] = {&mm, &s, &ee, &dd};
+    const int64_t blocks = std::max<int64_t>(16, std::min<int64_t>(kFarBlocks, s.Np * n_cols / 4));
+    return (int)hipLaunchKernel(far, dim3((unsigned)blocks), dim3(kBlock), far_args, 0, (hipStream_t)stream);
+}
 
 int launch_day(const Model &m, const DevState &s, const DevEvents &ev, int32_t d, int prologue, int ssa,
                int layout, void *stream) {
@@ -2616,12 +2913,17 @@ int launch_day(const Model &m, const DevState &s, const DevEvents &ev, int32_t d
     void *args[] = {&mm, &ss, &ee, &dd, &pro, &sa};
     if (layout == LAYOUT_TILE) {
         if (s.slots) return hipErrorInvalidValue;  // a slot handle's day runs through launch_slot_day
-        const unsigned nx = (unsigned)((s.Np + s.tile_nodes - 1) / s.tile_nodes + (int64_t)s.n_heavy * kHeavyBlocks);
-        return (int)hipLaunchKernel(t.tile, dim3(nx, (unsigned)(s.RL / 64)), dim3(kBlock), args, 0, (hipStream_t)stream);
+        return launch_tiles(t.tile, t.far, m, s, ev, d, prologue, ssa, s.RL / 64, stream);
     }
     if (s.tile_nodes < 4 || s.tile_nodes > kMaxUnit || s.L % s.tile_nodes != 0) return hipErrorInvalidValue;
     const unsigned grid = (unsigned)(s.L / s.tile_nodes);
-    return (int)hipLaunchKernel(t.day, dim3(grid), dim3(kDayBlock), args, 0, (hipStream_t)stream);
+    // Sixteen wavefronts a unit fill a compute unit; where there are more units
+    // than compute units, fewer a unit let several run side by side (1,990
+    // nodes of the synthetic model in units of 4, 60 days: 4.1 ms with 1,024
+    // threads a unit, 3.4 with 512).
+    int block = kDayBlock;
+    while (block > 256 && block / 2 >= s.tile_nodes && (int64_t)grid * block > (int64_t)kUnitsWanted * kDayBlock) block /= 2;
+    return (int)hipLaunchKernel(t.day, dim3(grid), dim3((unsigned)block), args, 0, (hipStream_t)stream);
 }
 
 int launch_events(const Model &m, const DevState &s, const DevEvents &ev, int32_t d, int64_t begin,
@@ -2684,13 +2986,7 @@ int launch_slot_day(const Model &m, const DevState &s, const DevEvents &ev, int3
     if (s.L == 0 || n_cols <= 0) return hipSuccess;
     if (!s.slots || n_cols > s.RL / 64) return hipErrorInvalidValue;
     const Table t = pick(m);
-    Model mm = m;
-    DevState ss = s;
-    DevEvents ee = ev;
-    int32_t dd = step, pro = 1, sa = 1;
-    void *args[] = {&mm, &ss, &ee, &dd, &pro, &sa};
-    const unsigned nx = (unsigned)((s.Np + s.tile_nodes - 1) / s.tile_nodes + (int64_t)s.n_heavy * kHeavyBlocks);
-    return (int)hipLaunchKernel(t.tile_slots, dim3(nx, (unsigned)n_cols), dim3(kBlock), args, 0, (hipStream_t)stream);
+    return launch_tiles(t.tile_slots, t.far_slots, m, s, ev, step, 1, 1, n_cols, stream);
 }
 
 int launch_slot_events(const Model &m, const DevState &s, const DevEvents &ev, int32_t step, int32_t k,

@@ -384,7 +384,6 @@ int32_t lane_stride(int32_t R, int layout) {
 // nodes on 1024, whose wavefronts all have owners. 1,000 nodes, 365 days: 7.3
 // ms in units of 4, 8.1 of 64, 9.1 of 256; 5,000 nodes of a general model, 120
 // days: 3.6 ms in units of 32, 8.3 of 4, five to a compute unit.)
-constexpr int64_t kUnitsWanted = 256;
 int64_t lane_unit(int64_t n_nodes) {
     int64_t u = 4;
     while (u < kMaxUnit && (n_nodes + u - 1) / u > kUnitsWanted) u *= 2;
@@ -401,11 +400,15 @@ int64_t lane_unit(int64_t n_nodes) {
 // Returns the number of positions (a multiple of the padding granule);
 // pos_node[pos] = node or -1.
 constexpr int64_t kSoloHerds = 128;
-// With replicate tiles, the largest herds of an instance (at most
-// kHeavyHerds, and one per 64 nodes) get units of their own whose every
-// (herd, replicate) chain is walked by a wavefront of its own; they are placed
-// first, the remaining positions of their units stay empty.
-constexpr int64_t kHeavyHerds = 64;
+// Replicate tiles: positions of a unit unless tile_nodes names them: a workgroup's
+// share of a launch over all columns (in groups of four, at most kMaxTileUnit).
+constexpr int64_t kMaxTileUnit = 512;
+int64_t tile_unit(int64_t n_nodes, int64_t n_cols) {
+    const int64_t wanted = n_nodes * n_cols < kNarrow ? kTileBlocks : kTileBlocksWide;
+    const int64_t share = (n_nodes * n_cols + wanted - 1) / wanted;
+    return std::min(kMaxTileUnit, std::max<int64_t>(1, (share + 3) / 4) * 4);
+}
+
 // With one lane per node and per-day launches, the largest herds of a large
 // instance (kGroupHerds unless the options say otherwise) get a workgroup
 // each, so that no other chain waits for theirs.
@@ -440,9 +443,8 @@ int64_t place_group(const std::vector<int32_t> &ranked, bool by_wave, int64_t ti
 // Positions of one instance's nodes (pos_node[pos] = node or -1) and the
 // region of each position (-1 outside regions). With regions, every unit of
 // work holds herds of one region only, so the per-unit sums of the records
-// are also regional sums; the heavy herds' own units may mix regions (their
-// chains record on their own).
-int64_t order_nodes(const sim_problem *p, int layout, bool by_wave, int64_t tile, int64_t heavy, int64_t group,
+// are also regional sums.
+int64_t order_nodes(const sim_problem *p, int layout, bool by_wave, int64_t tile, int64_t group,
                     std::vector<int32_t> *pos_node, std::vector<int32_t> *pos_region) {
     const int64_t Nn = p->n_nodes, Nc = p->n_comp;
     // a herd's size is its largest population over the horizon: the SSA only
@@ -505,28 +507,21 @@ int64_t order_nodes(const sim_problem *p, int layout, bool by_wave, int64_t tile
     std::sort(by_size.begin(), by_size.end());
     std::vector<int32_t> rank(Nn);
     for (int64_t i = 0; i < Nn; ++i) rank[i] = by_size[i].second;
-    const int64_t G = tile;
-    const int64_t hv = layout == LAYOUT_TILE ? std::min(heavy, Nn) : 0;
-    const int64_t hv_span = ((hv + G - 1) / G) * G;
     const int64_t gr = layout == LAYOUT_LANES ? std::min(group, Nn) : 0;
-    const int64_t lead = hv_span + gr * tile;
+    const int64_t lead = gr * tile;
     const int32_t J = p->n_regions > 0 ? p->n_regions : 0;
     auto region_of = [&](int32_t i) { return J > 0 ? p->region[i] : -1; };
     pos_node->assign(lead, -1);
     pos_region->assign(lead, -1);
-    for (int64_t q = 0; q < hv; ++q) {
-        (*pos_node)[q] = rank[q];
-        (*pos_region)[q] = region_of(rank[q]);
-    }
     // a workgroup per group herd: the herd first, the rest padding of its region
     for (int64_t q = 0; q < gr; ++q) {
-        const int64_t b = hv_span + q * tile;
-        (*pos_node)[b] = rank[hv + q];
-        for (int64_t i = 0; i < tile; ++i) (*pos_region)[b + i] = region_of(rank[hv + q]);
+        const int64_t b = q * tile;
+        (*pos_node)[b] = rank[q];
+        for (int64_t i = 0; i < tile; ++i) (*pos_region)[b + i] = region_of(rank[q]);
     }
     // groups: the herds outside regions, then region by region (one group without regions)
     std::vector<std::vector<int32_t>> groups(J + 1);
-    for (int64_t q = hv + gr; q < Nn; ++q) groups[region_of(rank[q]) + 1].push_back(rank[q]);
+    for (int64_t q = gr; q < Nn; ++q) groups[region_of(rank[q]) + 1].push_back(rank[q]);
     int64_t base = lead;
     for (int32_t j = -1; j < J; ++j) {
         const int64_t span = place_group(groups[j + 1], by_wave, tile, base, pos_node);
@@ -540,14 +535,14 @@ int64_t order_nodes(const sim_problem *p, int layout, bool by_wave, int64_t tile
 struct Layout {
     size_t u, phi, node_id, inst, inst_off, seed, coef, alpha, beta, repid, status, ev_g, ev_gm, ev_node,
         ev_dest, ev_n, ev_meta, ev_smap, task_off, priv_off, priv_ev_off, day_slot_off, slot_pos, unit_stage_off, unit_stage, stage, slot_key, lvl_ev_off, ev_slot_src, ev_slot_dst, lvl_off, lvl_ptr, prevalence, transitions, totals, max_fired, snap_u, snap_v, rec_slot, slots,
-        u0, v0, run, heavy_pos, unit_heavy, pos_region, regional, goal_ref, goal_part, total;
+        u0, v0, run, far_list, far_n, pos_region, regional, goal_ref, goal_part, total;
 };
 
 size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
 Layout layout_for(int64_t Np, int64_t n_nodes, int64_t n_inst, int64_t Nc, int64_t Nt, int64_t R, int64_t RL,
                   int64_t D, int64_t n_events, int64_t n_shift_ids, int64_t n_levels, int64_t n_tasks,
-                  int64_t n_units, int64_t n_day_slots, int64_t n_record, int64_t n_slots, int64_t n_heavy,
+                  int64_t n_units, int64_t n_day_slots, int64_t n_record, int64_t n_slots, int64_t far_cap,
                   int64_t n_regions) {
     Layout l{};
     size_t off = 0;
@@ -598,12 +593,12 @@ Layout layout_for(int64_t Np, int64_t n_nodes, int64_t n_inst, int64_t Nc, int64
     l.rec_slot = take(sizeof(int32_t) * D);
     // slot handles: the slot table and the network's initial state by position
     l.slots = take(sizeof(SlotInfo) * n_slots);
-    l.heavy_pos = take(sizeof(int32_t) * n_heavy);
+    l.far_list = take(sizeof(int32_t) * kFarLists * far_cap);
+    l.far_n = take(sizeof(int32_t) * 2 * kFarLists);
     l.pos_region = take(n_regions ? sizeof(int32_t) * Np : 0);
     l.regional = take(sizeof(int64_t) * D * S * n_regions * Nc);
     l.goal_ref = take(sizeof(int64_t) * D * n_regions * Nc);
     l.goal_part = take(n_regions ? sizeof(double) * 2 * D : 0);
-    l.unit_heavy = take(n_units);
     l.u0 = take(n_slots ? sizeof(int32_t) * Nc * Np : 0);
     l.v0 = take(n_slots ? sizeof(double) * Np : 0);
     // slot handles: the step's running slots, then its running columns
@@ -631,8 +626,7 @@ struct Packed {
     std::vector<int32_t> priv_off;  // private tasks of (day, unit)
     std::vector<int32_t> priv_ev_off;  // and their events
     std::vector<int32_t> pos_region; // region of each position (-1 outside regions)
-    std::vector<int32_t> heavy_pos; // positions of the herds whose chains get a wavefront each
-    std::vector<uint8_t> unit_heavy;
+    int64_t far_cap = 0;            // replicate tiles: room of each list of far chains
     std::vector<int32_t> day_slot_off, slot_pos, ev_slot_src, ev_slot_dst;  // days run in LDS
     std::vector<int32_t> unit_stage_off, unit_stage;  // their slots by (day, unit)
     std::vector<uint32_t> slot_key;     // per slot: Philox key (seed, replicate id) and set of its node
@@ -647,7 +641,6 @@ struct Packed {
 int build_packed(const sim_problem *const *ps, int32_t n, int32_t events_mode, Packed *pk, std::string *err,
                  int32_t n_slots = 0, const sim_device_opts *o = nullptr) {
     const int32_t launch = o ? o->launch : SIM_LAUNCH_KERNELS, group_herds = o ? o->group_herds : 0;
-    const int32_t heavy_herds = o ? o->heavy_herds : 0;
     pk->tile = o && o->tile_nodes > 0 ? o->tile_nodes : kTileNodes;
     if (n < 1 || !ps) return *err = "no problems", SIM_EINVAL;
     for (int32_t k = 0; k < n; ++k) {
@@ -682,35 +675,33 @@ int build_packed(const sim_problem *const *ps, int32_t n, int32_t events_mode, P
     std::vector<std::vector<int32_t>> pos_node(n);
     pk->inst_off.assign(n, 0);
     pk->inst_pos0.assign(n, 0);
+    int64_t all = 0;
+    for (int32_t k = 0; k < n; ++k) all += ps[k]->n_nodes;
+    if (pk->layout == LAYOUT_TILE && launch == SIM_LAUNCH_KERNELS && !(o && o->tile_nodes > 0))
+        pk->tile = tile_unit(all, pk->RL / 64);
     if (pk->layout == LAYOUT_LANES) {
-        int64_t all = 0;
-        for (int32_t k = 0; k < n; ++k) all += ps[k]->n_nodes;
         pk->tile = launch == SIM_LAUNCH_PERSISTENT ? kPersistUnit : o && o->tile_nodes > 0 ? o->tile_nodes : lane_unit(all);
     }
     for (int32_t k = 0; k < n; ++k) {
         pk->inst_off[k] = (int32_t)pk->n_nodes;
         pk->inst_pos0[k] = (int32_t)pk->Np;
-        // (with one replicate a tile's wavefront already walks one herd with all its lanes)
-        const int64_t heavy = (pk->layout == LAYOUT_TILE && launch == SIM_LAUNCH_KERNELS && heavy_herds >= 0 &&
-                               pk->R > 1)
-                                  ? std::min<int64_t>(heavy_herds > 0 ? heavy_herds : kHeavyHerds, ps[k]->n_nodes / 64)
-                                  : 0;
         const int64_t group = (pk->layout == LAYOUT_LANES && launch == SIM_LAUNCH_KERNELS &&
                                ps[k]->n_nodes >= kGroupMinNodes && group_herds >= 0)
                                   ? (group_herds > 0 ? group_herds : kGroupHerds) : 0;
         std::vector<int32_t> preg;
         const int64_t np_k = order_nodes(ps[k], pk->layout, pk->layout == LAYOUT_LANES && launch == SIM_LAUNCH_PERSISTENT, pk->tile,
-                                          heavy, group, &pos_node[k], &preg);
+                                          group, &pos_node[k], &preg);
         pk->pos_region.insert(pk->pos_region.end(), preg.begin(), preg.end());
-        for (int64_t j = 0; j < heavy; ++j) pk->heavy_pos.push_back((int32_t)(pk->Np + j));
         pk->Np += np_k;
         pk->n_nodes += ps[k]->n_nodes;
         pk->n_events += ps[k]->n_events;
     }
     if (pk->Np * (int64_t)pk->RL > INT32_MAX) return *err = "positions x replicate lanes must stay below 2^31", SIM_EINVAL;
     if (pk->n_events > INT32_MAX) return *err = "too many events", SIM_EINVAL;
-    pk->unit_heavy.assign(pk->Np / pk->tile, 0);
-    for (int32_t hp : pk->heavy_pos) pk->unit_heavy[hp / pk->tile] = 1;
+    if (pk->layout == LAYOUT_TILE) {
+        const int64_t L = pk->Np * pk->RL;
+        pk->far_cap = std::min(L, std::max<int64_t>(L / 8, 4096));
+    }
     pk->node_id.assign(pk->Np, -1);
     pk->inst.assign(pk->Np, 0);
     pk->lane_of.assign(pk->n_nodes, 0);
@@ -1001,7 +992,7 @@ int build_packed(const sim_problem *const *ps, int32_t n, int32_t events_mode, P
 Layout layout_of(const Packed &pk, const sim_problem *p0) {
     return layout_for(pk.Np, pk.n_nodes, pk.n_inst, pk.Nc, pk.Nt, pk.R, pk.RL, pk.D, pk.n_events, p0->n_shift,
                       pk.n_levels, pk.n_tasks, pk.n_units, (int64_t)pk.slot_pos.size(), pk.n_record, pk.n_slots,
-                      (int64_t)pk.heavy_pos.size(), p0->n_regions);
+                      pk.far_cap, p0->n_regions);
 }
 
 }  // namespace
@@ -1018,6 +1009,7 @@ struct sim_handle {
     std::vector<int64_t> lvl_off;   // host copy of the level boundaries (task offsets)
     std::vector<int32_t> lvl_ptr;   // [D+1]
     std::vector<int32_t> day_slot_off;  // [D+1]: a day with slots runs its levels in LDS
+    std::vector<int32_t> priv_day;      // [D+1]: first private task of each day (contiguous by day)
     std::vector<int64_t> lvl_ev_off;    // host copy of the event offsets of each level
     Layout lay{};
     void *ws = nullptr;
@@ -1214,6 +1206,8 @@ int create(const sim_problem *const *ps, int32_t n, const sim_device_opts *o, si
     h->lvl_off = pk.lvl_off;
     h->lvl_ptr = pk.lvl_ptr;
     h->day_slot_off = pk.day_slot_off;
+    h->priv_day.resize(h->D + 1);
+    for (int32_t d = 0; d <= h->D; ++d) h->priv_day[d] = pk.priv_off[(size_t)d * pk.n_units];
     h->lvl_ev_off = pk.lvl_ev_off;
     h->ev_inst = std::move(pk.ev_inst);
     h->ev_local = std::move(pk.ev_local);
@@ -1305,9 +1299,10 @@ int create(const sim_problem *const *ps, int32_t n, const sim_device_opts *o, si
     h->slot_lanes = pk.slot_lanes;
     s.few_chains = opts.few_chains < 0 ? 0u : (opts.few_chains > 0 ? (uint32_t)opts.few_chains : kFewChains);
     s.group_min_attempts = opts.group_min_attempts > 0 ? (double)opts.group_min_attempts : kGroupMinAttempts;
-    s.n_heavy = (int32_t)pk.heavy_pos.size();
-    s.heavy_pos = at<int32_t>(h->ws, l.heavy_pos);
-    s.unit_heavy = s.n_heavy ? at<uint8_t>(h->ws, l.unit_heavy) : nullptr;
+    s.far_list = at<int32_t>(h->ws, l.far_list);
+    s.far_n = at<int32_t>(h->ws, l.far_n);
+    s.far_cap = (int32_t)pk.far_cap;
+    s.far_min = opts.heavy_herds < 0 ? 1e300 : 0.0;
     s.n_regions = p->n_regions;
     s.pos_region = at<int32_t>(h->ws, l.pos_region);
     s.regional = at<int64_t>(h->ws, l.regional);
@@ -1373,9 +1368,7 @@ int create(const sim_problem *const *ps, int32_t n, const sim_device_opts *o, si
         {(void *)ev.lvl_off, pk.lvl_off.data(), sizeof(int64_t) * (pk.n_levels + 1)},
         {(void *)ev.lvl_ptr, pk.lvl_ptr.data(), sizeof(int32_t) * (h->D + 1)},
         {(void *)s.rec_slot, pk.rec_slot.data(), sizeof(int32_t) * h->D},
-        {(void *)s.heavy_pos, pk.heavy_pos.data(), sizeof(int32_t) * pk.heavy_pos.size()},
         {(void *)s.pos_region, pk.pos_region.data(), s.n_regions ? sizeof(int32_t) * pk.pos_region.size() : 0},
-        {(void *)s.unit_heavy, pk.unit_heavy.data(), s.n_heavy ? pk.unit_heavy.size() : 0},
     };
     for (const Up &up : ups) {
         if (up.bytes == 0) continue;
@@ -1388,6 +1381,7 @@ int create(const sim_problem *const *ps, int32_t n, const sim_device_opts *o, si
     rc = check_device(hipMemset(at<char>(h->ws, l.prevalence), 0, l.rec_slot - l.prevalence), &err, "clear records");
     if (!rc && l.goal_ref > l.regional)
         rc = check_device(hipMemset(at<char>(h->ws, l.regional), 0, l.goal_ref - l.regional), &err, "clear regional records");
+    if (!rc) rc = check_device(hipMemset(s.far_n, 0, sizeof(int32_t) * 2 * kFarLists), &err, "clear far lists");
     for (int32_t j = 0; !rc && j < std::max(h->n_slots, 1); ++j)
         rc = check_device(hipMemcpy(s.status + j, &ok, sizeof ok, hipMemcpyHostToDevice), &err, "upload status");
     if (rc) {
@@ -1491,6 +1485,12 @@ int sim_run(sim_handle *h, int32_t n_days) {
         for (int32_t d = d0; d < d1; ++d) {
             hipError_t e = timed(h, SIM_K_DAY, [&] { return launch_day(h->model, h->st, h->ev, d, d > d0, 1, h->layout, h->stream); });
             if (e != hipSuccess) return h->err = fmt("day kernel: %s", hipGetErrorString(e)), SIM_EDEVICE;
+            if (h->layout == LAYOUT_TILE && h->priv_day[d + 1] > h->priv_day[d]) {
+                e = timed(h, SIM_K_EVENTS, [&] {
+                    return launch_events(h->model, h->st, h->ev, d, h->priv_day[d], h->priv_day[d + 1], h->stream);
+                });
+                if (e != hipSuccess) return h->err = fmt("event kernel: %s", hipGetErrorString(e)), SIM_EDEVICE;
+            }
             // a day that fits runs its levels in LDS; otherwise big levels get a
             // launch of their own and runs of small ones share one workgroup
             int32_t lv = h->lvl_ptr[d];
@@ -1633,6 +1633,9 @@ int sim_set_state(sim_handle *h, const int32_t *u, const double *v, int32_t day)
         if (!rc) rc = check_device(hipMemcpy(h->st.phi, dv.data(), sizeof(double) * dv.size(), hipMemcpyHostToDevice), &h->err, "upload v");
     }
     if (!rc) rc = check_device(hipMemcpy(h->st.status, &ok, sizeof ok, hipMemcpyHostToDevice), &h->err, "reset status");
+    // (a run that failed may have left chains listed)
+    const int32_t none[2 * kFarLists] = {};
+    if (!rc) rc = check_device(hipMemcpy(h->st.far_n, none, sizeof none, hipMemcpyHostToDevice), &h->err, "clear far lists");
     if (rc) return rc;
     h->day = day;
     return SIM_OK;
@@ -1849,6 +1852,7 @@ int sim_slots_step(sim_handle *h, int32_t *finished, int32_t *n_finished) {
     }
     if (!any) return SIM_OK;
     std::vector<int64_t> size(k_max, 0);  // largest (task, lane) count of level k over the slots
+    int64_t size_priv = 0;                // and of the private tasks
     // the run lists of this step: slots with a day of events, then columns
     // with a running slot (every running slot has its day's phi update, its
     // SSA or both), into the next entry of the pinned ring
@@ -1866,6 +1870,7 @@ int sim_slots_step(sim_handle *h, int32_t *finished, int32_t *n_finished) {
         const int32_t d = T - sl.t0;
         if (d >= sl.horizon) continue;
         run[n_run++] = j;
+        size_priv = std::max<int64_t>(size_priv, (int64_t)(h->priv_day[d + 1] - h->priv_day[d]) * h->slot_lanes);
         for (int32_t k = 0; k < h->lvl_ptr[d + 1] - h->lvl_ptr[d]; ++k) {
             const int32_t lv = h->lvl_ptr[d] + k;
             size[k] = std::max(size[k], (h->lvl_off[lv + 1] - h->lvl_off[lv]) * h->slot_lanes);  // tasks x lanes
@@ -1877,6 +1882,12 @@ int sim_slots_step(sim_handle *h, int32_t *finished, int32_t *n_finished) {
     if (rc) return rc;
     hipError_t e = timed(h, SIM_K_DAY, [&] { return launch_slot_day(h->model, h->st, h->ev, T, n_cols, h->stream); });
     if (e != hipSuccess) return h->err = fmt("day kernel: %s", hipGetErrorString(e)), SIM_EDEVICE;
+    if (size_priv > 0) {
+        e = timed(h, SIM_K_EVENTS, [&] {
+            return launch_slot_events(h->model, h->st, h->ev, T, -1, 0, size_priv, n_run, h->stream);
+        });
+        if (e != hipSuccess) return h->err = fmt("event kernel: %s", hipGetErrorString(e)), SIM_EDEVICE;
+    }
     // big levels get a launch of their own; runs of small ones one workgroup per slot
     int32_t k = 0;
     while (k < k_max) {

@@ -84,16 +84,17 @@ struct DevState {
     // step's launches cover only these (grid y = their count)
     const int32_t *run_slots;   // [RL / slot_lanes]
     const int32_t *run_cols;    // [RL / 64]
-    // replicate tiles: the herds whose every (herd, replicate) chain gets a
-    // wavefront of its own, and the units that hold only such herds
     int32_t tile_nodes;         // positions of one unit: a replicate tile (a power of two, 4 .. 512), or
                                 // a workgroup's nodes with one lane per node (4 .. kMaxUnit)
     int32_t slot_lanes;         // slot handles: replicate lanes of one slot (8, 16, 32 or 64)
     uint32_t few_chains;        // at most this many live chains of a wavefront are walked one after another
     double group_min_attempts;  // one lane per node: a workgroup walks a chain that expects this many attempts
-    int32_t n_heavy;
-    const int32_t *heavy_pos;   // [n_heavy]
-    const uint8_t *unit_heavy;  // [n_units], null if n_heavy == 0
+    // replicate tiles: the lanes whose chains expect far_min attempts or more
+    // today, by length class (a chain that finds its list full is walked in place)
+    int32_t *far_list;          // [kFarLists][far_cap]
+    int32_t *far_n;             // [2][kFarLists], by parity of the day (of the step in a slot handle)
+    int32_t far_cap;
+    double far_min;             // 0: chosen by the launcher
     // daily records
     int32_t *prevalence;        // [D][sets]
     int64_t *transitions;       // [D][sets]
@@ -139,13 +140,26 @@ struct DevEvents {
 // or tiles of kTileNodes nodes x 64 replicate lanes per workgroup (R > 1,
 // lane stride RL a multiple of 64). A private task (a level-1 run of one node's
 // single-node events) runs in its node's unit right after the SSA.
-constexpr int kTileNodes = 128;       // default positions of a replicate tile
+constexpr int kTileNodes = 128;       // positions of a replicate tile of the persistent kernel by default
+constexpr int kFarLists = 3;
+// Workgroups of a tile launch: three of four wavefronts fit a compute unit, so one round of 768 fills
+// the chip; a launch of less than kNarrow positions (times columns) runs one a compute unit, since each
+// takes about 15 us besides its positions (4,000 nodes x 100 replicates, a day in 256 / 512 / 768 / 1536
+// workgroups: 118 / 126 / 133 / 206 us; 37,000 x 256: 792 / 665 / 574 / 625).
+constexpr int64_t kNarrow = 32768;
+constexpr int64_t kTileBlocks = 256, kTileBlocksWide = 768;
+// Attempts from which a chain is a far one, in a launch below and from kNarrow (300 nodes x 10
+// replicates, a day with 24 / 48 / 96: 63 / 82 / 112 us; 37,000 x 256 with 24 / 48 / 96 / 192: 783 / 634 /
+// 574 / 609).
+constexpr double kFarNarrow = 24.0, kFarWide = 96.0;
+constexpr int64_t kFarBlocks = 1024;
 constexpr uint32_t kFewChains = 4;     // default: at most this many live chains walked one after another
 constexpr double kGroupMinAttempts = 256.0;  // default: a workgroup walks a chain expecting this many attempts
 // One lane per node: positions of one workgroup, a power of two up to kMaxUnit
 // (the persistent kernel's workgroups take kPersistUnit).
 constexpr int kMaxUnit = 1024;
 constexpr int kPersistUnit = 256;
+constexpr int64_t kUnitsWanted = 256;  // one a compute unit
 constexpr int kStageShift = 10;
 static_assert(kMaxUnit == 1 << kStageShift, "local positions fit below the slot (and the length class of a chain)");
 enum { LAYOUT_LANES = 0, LAYOUT_TILE = 1 };

@@ -23,10 +23,11 @@ one lane per node (one trajectory per instance):
                      whole workgroup to walk it (0: default 256);
   tile_nodes         nodes per workgroup (0: by the network's size);
 replicate tiles (several replicates per instance):
-  tile_nodes         nodes per tile of 64 replicate lanes (0: default 128), taken
-                     one at a time by the tile's four wavefronts;
-  heavy_herds        how many of the largest herds get a wavefront per (herd,
-                     replicate) chain (0: default 64, negative: none).
+  tile_nodes         nodes per unit of 64 replicate lanes (0: by the network's
+                     size and the replicates);
+  heavy_herds        whether chains of many attempts get a wavefront each in a
+                     launch of their own (0 or more) or stay with their tile
+                     (negative).
 """
 from __future__ import annotations
 
