@@ -1426,89 +1426,135 @@ __device__ __forceinline__ void private_tasks(const Model &m, const DevState &s,
     }
 }
 
+// One event applied to counts in LDS: compartment c of its node at xs[c], of its
+// destination at xd[c]. A node drawn from is the event's alone;
+// additions are atomic. pre: its first N draws, if they were computed ahead.
+template <int NC, int N>
+__device__ __forceinline__ void event_lds(uint32_t meta, uint32_t smap, int32_t n, uint32_t g, const int32_t *gm,
+                                          int32_t *xs, int32_t *xd, uint32_t key0, uint32_t key1,
+                                          int32_t set, int32_t d, unsigned long long *status,
+                                          const uint64_t (&pre)[N], bool ahead) {
+    const int kind = (int)(meta & kEvKindMask);
+    const uint32_t mask = (meta >> 2) & 0xffu;
+    auto add = [&](int32_t *p, int32_t v) {
+        __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    // A selection of one or two compartments c0 < c1 with its draws computed
+    // ahead (every column of the farm model, every movement of up to six
+    // animals): the running sums of the walk below are 0 before c0, x[c0]
+    // from c0 to c1 and the total from c1 on, so a pick below the count left
+    // in c0 takes from c0 and any other from c1 (the same picks, counts and
+    // write order as the walk over all compartments).
+    const uint32_t rest = mask & (mask - 1u);
+    if (mask != 0u && (rest & (rest - 1u)) == 0u && ahead && n <= N && (kind != SIM_ENTER || rest == 0u)) {
+        const int c0 = __builtin_ctz(mask);
+        const int c1 = rest ? __builtin_ctz(rest) : c0;
+        if (kind == SIM_ENTER) {
+            add(&xs[c0], n);
+            return;
+        }
+        const int32_t x0 = xs[c0], x1 = rest ? xs[c1] : 0;
+        const long long tot = (long long)x0 + (long long)x1;
+        if ((long long)n > tot) {
+            atomicMin(status, ((unsigned long long)(uint32_t)*gm << 32) | (unsigned long long)(uint32_t)set);
+            return;
+        }
+        if (tot <= 0x7fffffffLL) {
+            int32_t t0 = 0;
+            uint32_t left0 = (uint32_t)x0;
+#pragma unroll
+            for (int q = 0; q < N; ++q) {
+                const uint32_t pick = (uint32_t)__umul64hi(pre[q], (uint64_t)(tot - q));
+                const int in0 = q < n && pick < left0 ? 1 : 0;
+                left0 -= (uint32_t)in0;
+                t0 += in0;
+            }
+            const int t1 = n - t0;
+            xs[c0] = x0 - t0;
+            if (rest) xs[c1] = x1 - t1;
+            if (kind == SIM_INTERNAL) {
+                if (t0) xs[shifted(smap, c0)] += t0;
+                if (t1) xs[shifted(smap, c1)] += t1;
+            } else if (kind == SIM_EXTERNAL) {
+                if (t0) add(&xd[shifted(smap, c0)], t0);
+                if (t1) add(&xd[shifted(smap, c1)], t1);
+            }
+            return;
+        }
+    }
+    if (kind == SIM_ENTER) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+            if ((mask >> c) & 1u) add(&xs[c], n);
+        return;
+    }
+    int32_t x[NC];
+    long long tot = 0;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        x[c] = ((mask >> c) & 1u) ? xs[c] : 0;
+        tot += x[c];
+    }
+    if ((long long)n > tot) {
+        atomicMin(status, ((unsigned long long)(uint32_t)*gm << 32) | (unsigned long long)(uint32_t)set);
+        return;
+    }
+    int32_t take[NC];
+    draw_individuals<NC>(x, take, mask, n, tot, g, d, key0, key1);
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+        if ((mask >> c) & 1u) xs[c] = x[c];
+    if (kind == SIM_EXIT) return;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        if (take[c]) {
+            const int to = shifted(smap, c);
+            if (kind == SIM_INTERNAL)
+                xs[to] += take[c];
+            else
+                add(&xd[to], take[c]);
+        }
+    }
+}
+
+// The first n draws of event g on day d (pairs from Philox blocks).
+template <int N>
+__device__ __forceinline__ void draws_ahead(uint64_t (&pre)[N], int32_t n, uint32_t g, int32_t d, uint32_t key0,
+                                            uint32_t key1) {
+#pragma unroll
+    for (int b = 0; b < N / 2; ++b) {
+        pre[2 * b] = pre[2 * b + 1] = 0;
+        if (2 * b >= n) continue;
+        const Word4 o = philox4x32_10(Word4{(uint32_t)b, g, (uint32_t)d, 1u}, key0, key1);
+        pre[2 * b] = ((uint64_t)o.b << 32) | o.a;
+        pre[2 * b + 1] = ((uint64_t)o.d << 32) | o.c;
+    }
+}
+
 // One private event of a workgroup's day, staged in LDS.
 struct PrivEv {
     uint32_t meta, smap;
     int32_t n, g, gm, node;
 };
+constexpr int kPrivDraws = 2;
 
 // One private task (a run of one node's single-node events, i the first)
-// applied to the counts in LDS, with the arithmetic of event_task. A run that
-// draws has the node to itself; runs of additions only may share it and add
-// atomically.
+// applied to the counts in LDS (position loc's compartment c at xs[loc * NC + c]).
+// A run that draws has the node to itself; runs of additions only may share it
+// and add atomically. pre: the first draws of event i.
 template <int NC>
-__device__ void private_task_lds(const PrivEv *pe, int i, int n_ev, int32_t (*xs)[kMaxUnit], int32_t *touch,
-                                 int32_t base, int32_t d, uint32_t key0, uint32_t key1, int32_t set,
-                                 unsigned long long *status) {
+__device__ void private_task_lds(const PrivEv *pe, int i, int n_ev, int32_t *xs, int32_t *touch, int32_t base,
+                                 int32_t d, uint32_t key0, uint32_t key1, int32_t set, unsigned long long *status,
+                                 const uint64_t (&pre)[kPrivDraws]) {
     const int loc = pe[i].node - base;
-    int end = i + 1;
-    while (end < n_ev && (pe[end].meta & kMetaCont)) ++end;
-    bool draws = false;
-    for (int j = i; j < end; ++j) draws = draws || (int)(pe[j].meta & kEvKindMask) != SIM_ENTER;
     touch[loc] = 1;
-    if (!draws) {
-        for (int j = i; j < end; ++j) {
-            const uint32_t mask = (pe[j].meta >> 2) & 0xffu;
-#pragma unroll
-            for (int c = 0; c < NC; ++c)
-                if ((mask >> c) & 1u) atomicAdd(&xs[c][loc], pe[j].n);
-        }
-        return;
-    }
-    int32_t x[NC];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) x[c] = xs[c][loc];
-    for (int j = i; j < end; ++j) {
-        const uint32_t meta = pe[j].meta;
-        const int kind = (int)(meta & kEvKindMask);
-        const uint32_t mask = (meta >> 2) & 0xffu;
-        const int32_t n = pe[j].n;
-        if (kind == SIM_ENTER) {
-#pragma unroll
-            for (int c = 0; c < NC; ++c)
-                if ((mask >> c) & 1u) x[c] += n;
-            continue;
-        }
-        long long tot = 0;
-#pragma unroll
-        for (int c = 0; c < NC; ++c)
-            if ((mask >> c) & 1u) tot += x[c];
-        if ((long long)n > tot) {
-            atomicMin(status, ((unsigned long long)(uint32_t)pe[j].gm << 32) | (unsigned long long)(uint32_t)set);
-            break;
-        }
-        int32_t take[NC];
-        draw_individuals<NC>(x, take, mask, n, tot, (uint32_t)pe[j].g, d, key0, key1);
-        if (kind == SIM_INTERNAL) {
-#pragma unroll
-            for (int c = 0; c < NC; ++c) {
-                if (take[c]) {
-                    const int to = shifted(pe[j].smap, c);
-#pragma unroll
-                    for (int cc = 0; cc < NC; ++cc)
-                        if (cc == to) x[cc] += take[c];
-                }
-            }
-        }
-    }
-#pragma unroll
-    for (int c = 0; c < NC; ++c) xs[c][loc] = x[c];
+    int j = i;
+    do {
+        event_lds<NC>(pe[j].meta, pe[j].smap, pe[j].n, (uint32_t)pe[j].g, &pe[j].gm, &xs[loc * NC], &xs[loc * NC], key0, key1,
+                      set, d, status, pre, j == i);
+        ++j;
+    } while (j < n_ev && (pe[j].meta & kMetaCont));
 }
-
-// The LDS of a day whose levels run in LDS: the touched nodes' counts (slots),
-// their Philox keys and sets, the day's events, the level bounds and the first
-// draws of every event.
-template <int NC>
-struct EventDayShared {
-    int32_t u[kDaySlotCap * NC];
-    uint32_t k0[kDaySlotCap], k1[kDaySlotCap];
-    int32_t set[kDaySlotCap], pos[kDaySlotCap];
-    int32_t n[kDayEventCap], g[kDayEventCap];
-    uint32_t meta[kDayEventCap], smap[kDayEventCap];
-    int16_t ss[kDayEventCap], sd[kDayEventCap];
-    int32_t lv[kDayLevelCap + 1];
-    uint64_t pre[kDayEventCap * kPreDraws];
-};
 
 // One lane per node: a workgroup runs one unit of s.tile_nodes positions (4 to
 // 1024), thread t < tile_nodes owning position t. The counts live in LDS for
@@ -1534,28 +1580,108 @@ struct EventDayShared {
 constexpr double kWaveChain = 48.0;
 constexpr int kFarClass = 3, kLengthClasses = 6;
 
-template <int NC>
-struct DayShared {
-    int32_t x[NC][kMaxUnit];
-    double phi[kMaxUnit];
-    int32_t node[kMaxUnit];
-    int32_t touch[kMaxUnit];     // nodes to store: a transition fired or a private task ran
-    uint16_t list[2][kMaxUnit];  // positions with a chain: long (with the length class << kStageShift), short
-    int32_t n[2], next[2], in_class[kLengthClasses];
-    PrivEv pe[kDayBlock];
-    double tau[kDayWaves][64];
-    long long part[kDayWaves][1 + NC];
+//
+// A day whose levels touch few nodes (EventDayArgs) has no launch for them: the
+// workgroups of the next day's launch (or of the closing one) each apply all of
+// the day's level events to the touched nodes' counts, a thread an event, from
+// the counts that the day before left in s.stage, and keep the nodes of their
+// own unit. Levels take about 0.5 us each there, and the launch, its two
+// boundaries and the round trip of the counts through memory, about 6 us a day,
+// are gone (a day of the SIS network of 1,000 nodes 12.0 -> 11.4 us, of the farm
+// model with 1,000 nodes 17.7 -> 15.5, with 37,000 33.4 -> 29.3).
+struct DayCounts {
+    int32_t n[2], next[2], in_class[kLengthClasses], most;
     unsigned long long trans;
-    int32_t most;
 };
 
-template <class Rules>
+// The LDS of a unit of U positions and a workgroup of B threads (offsets into
+// the launch's dynamic LDS).
+template <int NC>
+struct DayShared {
+    int32_t *x;         // [U][NC] counts
+    double *phi;        // [U]
+    int32_t *node;      // [U]
+    int32_t *touch;     // [U] nodes to store: a transition fired or an event changed them
+    uint16_t *list;     // [2][U] positions with a chain: long (with the length class << kStageShift), short
+    PrivEv *pe;         // [B]
+    uint64_t *pd;       // [kPrivDraws][B] their first draws
+    double *tau;        // [B] 64 values a wavefront
+    long long *part;    // [B / 64][1 + NC]
+    // a day's level events and the counts of the nodes they touch
+    int32_t *eu;        // [kDaySlotCap][NC]
+    uint32_t *ev;       // [kDayEventCap][4] meta, smap, n, g
+    int32_t *lv;        // [kDayLevelCap + 1]
+    __host__ __device__ size_t place(char *at, int U, int B, bool events) {
+        size_t off = 0;
+        auto take = [&](size_t bytes) {
+            char *p = at + off;
+            off += (bytes + 15) & ~(size_t)15;
+            return p;
+        };
+        phi = (double *)take(sizeof(double) * U);
+        tau = (double *)take(sizeof(double) * B);
+        part = (long long *)take(sizeof(long long) * (B / 64) * (1 + NC));
+        x = (int32_t *)take(sizeof(int32_t) * NC * U);
+        node = (int32_t *)take(sizeof(int32_t) * U);
+        touch = (int32_t *)take(sizeof(int32_t) * U);
+        list = (uint16_t *)take(sizeof(uint16_t) * 2 * U);
+        pe = (PrivEv *)take(sizeof(PrivEv) * B);
+        pd = (uint64_t *)take(sizeof(uint64_t) * kPrivDraws * B);
+        eu = (int32_t *)take(events ? sizeof(int32_t) * kDaySlotCap * NC : 0);
+        ev = (uint32_t *)take(events ? sizeof(uint32_t) * 4 * kDayEventCap : 0);
+        lv = (int32_t *)take(events ? sizeof(int32_t) * (kDayLevelCap + 1) : 0);
+        return off;
+    }
+};
+
+// The level events a of day d on the touched nodes' counts, an event a thread
+// (a.ne <= kDayEventCap <= blockDim.x). Every thread calls it; the counts stand
+// in sh.eu after its last barrier. A later event of a task is applied by the
+// thread of its first, without draws ahead.
+struct LevelEvent {
+    uint32_t meta, smap, g, key0, key1;
+    int32_t n, src, dst, set;
+};
+
+template <int NC>
+__device__ __forceinline__ void event_levels_lds(const DevState &s, const DevEvents &ev, const EventDayArgs &a,
+                                                 int32_t d, const LevelEvent e, const DayShared<NC> &sh) {
+    const int i = threadIdx.x;
+    uint64_t pre[kPreDraws];
+    draws_ahead<kPreDraws>(pre, (int)(e.meta & kEvKindMask) == SIM_ENTER ? 0 : e.n, e.g, d, e.key0, e.key1);
+    for (int k = 0; k < a.nl; ++k) {
+        const int end = sh.lv[k + 1];
+        if (i >= sh.lv[k] && i < end && !(e.meta & kMetaCont)) {
+            int32_t *xs = &sh.eu[e.src * NC], *xd = &sh.eu[(e.dst >= 0 ? e.dst : e.src) * NC];
+            uint32_t meta = e.meta, smap = e.smap, g = e.g;
+            int32_t n = e.n;
+            for (int j = i;;) {
+                event_lds<NC>(meta, smap, n, g, &ev.gm[a.e0 + j], xs, xd, e.key0,
+                              e.key1, e.set, d, s.status, pre, j == i);
+                // (a task of several events is one of a single node)
+                if (++j >= end || !(sh.ev[4 * j] & kMetaCont)) break;
+                meta = sh.ev[4 * j];
+                smap = sh.ev[4 * j + 1];
+                n = (int32_t)sh.ev[4 * j + 2];
+                g = sh.ev[4 * j + 3];
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// LEVELS: some day of the run has such events (the plain variant keeps the
+// registers for them free).
+template <class Rules, bool LEVELS>
 __global__ __launch_bounds__(kDayBlock) void k_day(Model m, DevState s, DevEvents ev, int32_t d, int32_t prologue,
-                                                   int32_t ssa) {
+                                                   int32_t ssa, EventDayArgs a) {
     constexpr int NC = Rules::NC, NT = Rules::NT;
-    __shared__ DayShared<NC> sh;
+    extern __shared__ __align__(16) char day_lds[];
+    __shared__ DayCounts cnt;
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int32_t U = s.tile_nodes;
+    const int U = s.tile_nodes, B = (int)blockDim.x;
+    DayShared<NC> sh;
+    sh.place(day_lds, U, B, LEVELS);
     const int64_t base = (int64_t)blockIdx.x * U;
     // The unit's private events of the day. With at most one per thread they
     // are fetched now, alongside the state, and applied to the counts in LDS
@@ -1566,32 +1692,92 @@ __global__ __launch_bounds__(kDayBlock) void k_day(Model m, DevState s, DevEvent
     const int32_t npe = ssa ? ev.priv_ev_off[k + 1] - pe0 : 0;
     // instances are padded to whole units: one set per workgroup
     const int32_t set = s.n_inst == 1 ? 0 : s.inst[base];
-    // the unit's nodes among the slots of a day whose remaining events run in
-    // LDS: their final counts go to the day's staging buffer (one per thread)
-    const bool staged = ssa && ev.unit_stage_off;
+    // the unit's nodes among the slots of a day whose level events run in LDS:
+    // their counts after today's private tasks go to the day's staging buffer
+    // (one per thread)
+    const bool staged = LEVELS && ssa;
     const int32_t st0 = staged ? ev.unit_stage_off[k] : 0;
     const int32_t nst = staged ? ev.unit_stage_off[k + 1] - st0 : 0;
+    // and those of yesterday's, whose counts the level events below leave
+    const bool levels = LEVELS && a.ns > 0;
+    const int32_t sp0 = levels ? ev.unit_stage_off[k - gridDim.x] : 0;
+    const int32_t nsp = levels ? ev.unit_stage_off[k - gridDim.x + 1] - sp0 : 0;
     const int32_t rec = prologue ? s.rec_slot[d - 1] : -1;
     const LaneLoad<NC> q = lane_load<NC>(m, s, t < U ? base + t : s.L);
-    if (t < 2) sh.n[t] = sh.next[t] = 0;
-    if (t < kLengthClasses) sh.in_class[t] = 0;
+    LevelEvent le{0u, 0u, 0u, 0u, 0u, 0, 0, -1, 0};
+    if (levels) {
+        const int32_t *stage = ev.stage + (int64_t)((d - 1) & 1) * kDaySlotCap * MAXC;
+        for (int i = t; i < a.ns * NC; i += B) sh.eu[i] = stage[i];
+        if (t <= a.nl) sh.lv[t] = (int32_t)(ev.lvl_ev_off[a.lv0 + t] - a.e0);
+        if (t < a.ne) {
+            const int64_t e = a.e0 + t;
+            le.meta = ev.meta[e];
+            le.smap = ev.smap[e];
+            le.n = ev.n[e];
+            le.g = (uint32_t)ev.g[e];
+            le.src = ev.slot_src[e];
+            le.dst = ev.slot_dst[e];
+            sh.ev[4 * t] = le.meta;
+            sh.ev[4 * t + 1] = le.smap;
+            sh.ev[4 * t + 2] = (uint32_t)le.n;
+            sh.ev[4 * t + 3] = le.g;
+        }
+    }
+    if (t < 2) cnt.n[t] = cnt.next[t] = 0;
+    if (t < kLengthClasses) cnt.in_class[t] = 0;
     if (t == 0) {
-        sh.trans = 0ull;
-        sh.most = 0;
+        cnt.trans = 0ull;
+        cnt.most = 0;
     }
     if (!block_ok_once(s.status)) return;
     const uint32_t key0 = s.seed[set], key1 = s.repid[set];
-    const bool lds = npe <= (int)blockDim.x;
+    const bool lds = npe <= B;
     const bool has = lds && t < npe;
     const int32_t stage_entry = t < nst ? ev.unit_stage[st0 + t] : -1;
+    const int32_t stage_prev = t < nsp ? ev.unit_stage[sp0 + t] : -1;
     if (has) {
         const int64_t e = pe0 + t;
-        sh.pe[t] = PrivEv{ev.meta[e], ev.smap[e], ev.n[e], ev.g[e], ev.gm[e], ev.node[e]};
+        const PrivEv mine{ev.meta[e], ev.smap[e], ev.n[e], ev.g[e], ev.gm[e], ev.node[e]};
+        sh.pe[t] = mine;
+        uint64_t pre[kPrivDraws];
+        draws_ahead<kPrivDraws>(pre, (int)(mine.meta & kEvKindMask) == SIM_ENTER ? 0 : mine.n, (uint32_t)mine.g, d, key0,
+                                key1);
+#pragma unroll
+        for (int i = 0; i < kPrivDraws; ++i) sh.pd[i * B + t] = pre[i];
     }
     const bool active = q.nid >= 0;
     double coef[NT];
 #pragma unroll
     for (int i = 0; i < NT; ++i) coef[i] = trans_on<NT>(m, i) ? s.coef[set * m.nt + i] : 0.0;
+    int32_t x[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) x[c] = q.x[c];
+    if (t < U) sh.touch[t] = 0;
+    if (levels) {
+        if (t < a.ne) {
+            const bool one = s.n_inst == 1;
+            const uint32_t *key = &ev.slot_key[3 * (int64_t)(a.s0 + le.src)];
+            le.key0 = one ? key0 : key[0];
+            le.key1 = one ? key1 : key[1];
+            le.set = one ? 0 : (int32_t)key[2];
+        }
+        if (t < U) {
+#pragma unroll
+            for (int c = 0; c < NC; ++c) sh.x[t * NC + c] = x[c];
+        }
+        event_levels_lds<NC>(s, ev, a, d - 1, le, sh);
+        if (stage_prev >= 0) {
+            const int at = stage_prev & (kMaxUnit - 1), slot = stage_prev >> kStageShift;
+#pragma unroll
+            for (int c = 0; c < NC; ++c) sh.x[at * NC + c] = sh.eu[slot * NC + c];
+            sh.touch[at] = 1;
+        }
+        __syncthreads();
+        if (t < U) {
+#pragma unroll
+            for (int c = 0; c < NC; ++c) x[c] = sh.x[t * NC + c];
+        }
+    }
     if (wave * 64 < U) {
         double phi = q.phi;
         if (prologue) {
@@ -1603,26 +1789,26 @@ __global__ __launch_bounds__(kDayBlock) void k_day(Model m, DevState s, DevEvent
                     // phi was already fed by the state before the events of day dp
 #pragma unroll
                     for (int c = 0; c < NC; ++c)
-                        if ((m.imask >> c) & 1u) I += q.x[c];
+                        if ((m.imask >> c) & 1u) I += x[c];
                 } else {
-                    phi = phi_next<NC>(m, q.x, s.alpha[set], s.beta[set * 4 + season((int64_t)m.day0 + dp)], phi, &I);
+                    phi = phi_next<NC>(m, x, s.alpha[set], s.beta[set * 4 + season((int64_t)m.day0 + dp)], phi, &I);
                 }
                 prev = I > 0.0 ? 1 : 0;
                 if (rec >= 0) {
                     const int64_t at = (int64_t)rec * s.n_nodes + s.inst_off[set] + q.nid;
 #pragma unroll
                     for (int c = 0; c < NC; ++c)
-                        if (comp_on<NC>(m, c)) s.snap_u[at * m.nc + c] = q.x[c];
+                        if (comp_on<NC>(m, c)) s.snap_u[at * m.nc + c] = x[c];
                     s.snap_v[at] = phi;
                 }
                 if (__double_as_longlong(phi) != __double_as_longlong(q.phi)) s.phi[base + t] = phi;
             }
             const long long np = wave_sum(prev);
-            if (lane == 0) sh.part[wave][0] = np;
+            if (lane == 0) sh.part[wave * (1 + NC)] = np;
 #pragma unroll
             for (int c = 0; c < NC; ++c) {
-                const long long w = wave_sum(q.x[c]);
-                if (lane == 0) sh.part[wave][1 + c] = w;
+                const long long w = wave_sum(x[c]);
+                if (lane == 0) sh.part[wave * (1 + NC) + 1 + c] = w;
             }
         }
         if (ssa) {
@@ -1630,19 +1816,19 @@ __global__ __launch_bounds__(kDayBlock) void k_day(Model m, DevState s, DevEvent
 #pragma unroll
             for (int i = 0; i < NT; ++i) ch.cphi[i] = active ? ((m.uses_phi >> i) & 1u ? coef[i] * phi : coef[i]) : 0.0;
 #pragma unroll
-            for (int c = 0; c < NC; ++c) {
-                ch.xd[c] = (double)q.x[c];
-                sh.x[c][t] = q.x[c];
+            for (int c = 0; c < NC; ++c) ch.xd[c] = (double)x[c];
+            if (t < U) {
+#pragma unroll
+                for (int c = 0; c < NC; ++c) sh.x[t * NC + c] = x[c];
+                sh.phi[t] = phi;
+                sh.node[t] = q.nid;
             }
-            sh.phi[t] = phi;
-            sh.node[t] = q.nid;
-            sh.touch[t] = 0;
             Rules::rates(m, ch);
             const double gm = s.group_min_attempts;
             int cls = 0;
             if (ch.lam >= gm) {
                 cls = 1 + (ch.lam >= 4.0 * gm) + (ch.lam >= 16.0 * gm) + (ch.lam >= 64.0 * gm) + (ch.lam >= 256.0 * gm);
-                atomicAdd(&sh.in_class[cls], 1);
+                atomicAdd(&cnt.in_class[cls], 1);
             }
             const int kind = !(ch.lam > 0.0) ? -1 : (cls > 0 || ch.lam >= kWaveChain ? 0 : 1);
 #pragma unroll
@@ -1650,17 +1836,17 @@ __global__ __launch_bounds__(kDayBlock) void k_day(Model m, DevState s, DevEvent
                 const unsigned long long in = __ballot(kind == i);
                 if (in == 0ull) continue;
                 int at = 0;
-                if (lane == 0) at = atomicAdd(&sh.n[i], (int)__popcll(in));
+                if (lane == 0) at = atomicAdd(&cnt.n[i], (int)__popcll(in));
                 at = __builtin_amdgcn_readfirstlane(at);
                 if (kind == i)
-                    sh.list[i][at + __popcll(in & ((1ull << lane) - 1ull))] = (uint16_t)(t | (cls << kStageShift));
+                    sh.list[i * U + at + __popcll(in & ((1ull << lane) - 1ull))] = (uint16_t)(t | (cls << kStageShift));
             }
         }
     }
     __syncthreads();
-    if (prologue && t >= (int)blockDim.x - 64 && lane < 1 + NC) {
+    if (prologue && t >= B - 64 && lane < 1 + NC) {
         long long sum = 0;
-        for (int w = 0; w * 64 < U; ++w) sum += sh.part[w][lane];
+        for (int w = 0; w * 64 < U; ++w) sum += sh.part[w * (1 + NC) + lane];
         if (lane == 0) {
             if (sum) atomicAdd(&s.prevalence[(int64_t)(d - 1) * s.n_inst + set], (int32_t)sum);
         } else if (sum && comp_on<NC>(m, lane - 1)) {
@@ -1672,102 +1858,117 @@ __global__ __launch_bounds__(kDayBlock) void k_day(Model m, DevState s, DevEvent
                           (unsigned long long)sum);
         }
     }
-    if (!ssa) return;
-    auto load = [&](int i, typename Rules::State &c) {
-        const double phi = sh.phi[i];
+    if (ssa) {
+        auto load = [&](int i, typename Rules::State &c) {
+            const double phi = sh.phi[i];
 #pragma unroll
-        for (int k2 = 0; k2 < NT; ++k2) c.cphi[k2] = (m.uses_phi >> k2) & 1u ? coef[k2] * phi : coef[k2];
+            for (int k2 = 0; k2 < NT; ++k2) c.cphi[k2] = (m.uses_phi >> k2) & 1u ? coef[k2] * phi : coef[k2];
 #pragma unroll
-        for (int c2 = 0; c2 < NC; ++c2) c.xd[c2] = (double)sh.x[c2][i];
-        c.clock = 0.0;
-        c.fired = 0;
-    };
-    auto store = [&](int i, const typename Rules::State &c) {  // by one lane
-        if (c.fired == 0) return;
+            for (int c2 = 0; c2 < NC; ++c2) c.xd[c2] = (double)sh.x[i * NC + c2];
+            c.clock = 0.0;
+            c.fired = 0;
+        };
+        auto store = [&](int i, const typename Rules::State &c) {  // by one lane
+            if (c.fired == 0) return;
 #pragma unroll
-        for (int c2 = 0; c2 < NC; ++c2) sh.x[c2][i] = (int32_t)c.xd[c2];
-        sh.touch[i] = 1;
-        atomicAdd(&sh.trans, (unsigned long long)c.fired);
-        atomicMax(&sh.most, c.fired);
-    };
-    const int n_long = sh.n[0], n_seg = sh.n[1];
-    int group_class = kLengthClasses, n_group = 0;  // classes from group_class on are the workgroup's
-    for (int b = kLengthClasses - 1; b > 0 && n_group + sh.in_class[b] <= (b >= kFarClass ? 3 : 1); --b) {
-        group_class = b;
-        n_group += sh.in_class[b];
-    }
-    for (int i = 0; n_group > 0 && i < n_long; ++i) {
-        const int entry = sh.list[0][i];
-        if (entry >> kStageShift < group_class) continue;
-        --n_group;
-        // the day's critical chain: its wavefronts issue ahead of the other
-        // waves on their SIMDs while it is walked
-        __builtin_amdgcn_s_setprio(3);
-        const int pos = entry & (kMaxUnit - 1);
-        const uint32_t node = (uint32_t)sh.node[pos];
-        typename Rules::State c;
-        load(pos, c);
-        Rules::rates(m, c);
-        uint32_t kb = 0;
-        if (!walk_group<Rules>(m, c, kb, node, (uint32_t)d, key0, key1, s.status, set) && wave == 0)
-            walk_wave<Rules>(m, c, kb, node, (uint32_t)d, key0, key1, s.status, set, sh.tau[0]);
-        if (t == 0) store(pos, c);
-        __builtin_amdgcn_s_setprio(0);
-        __syncthreads();  // the next chain reuses the walk's LDS
-    }
-    auto take = [&](int which, int k2) {
-        int at = 0;
-        if (lane == 0) at = atomicAdd(&sh.next[which], k2);
-        return __builtin_amdgcn_readfirstlane(at);
-    };
-    for (;;) {
-        const int i = n_long > 0 ? take(0, 1) : 0;
-        if (i >= n_long) break;
-        const int entry = sh.list[0][i];
-        if (entry >> kStageShift >= group_class) continue;
-        const int pos = entry & (kMaxUnit - 1);
-        typename Rules::State c;
-        load(pos, c);
-        Rules::reactants(m, c);
-        walk_wave<Rules>(m, c, 0u, (uint32_t)sh.node[pos], (uint32_t)d, key0, key1, s.status, set, sh.tau[wave]);
-        if (lane == 0) store(pos, c);
-    }
-    if (n_seg > 0)
-        walk_queue<Rules, 16>(m, n_seg, sh.tau[wave], [&](int k2) { return take(1, k2); },
-                              [&](int i, typename Rules::State &c, ChainKey &key) {
-                                  const int pos = sh.list[1][i];
-                                  load(pos, c);
-                                  key = ChainKey{0u, (uint32_t)sh.node[pos], (uint32_t)d, key0, key1, s.status, set};
-                              },
-                              [&](int i, const typename Rules::State &c) { store(sh.list[1][i], c); });
-    __syncthreads();
-    if (t == 0 && sh.trans != 0ull) {
-        const int64_t row = (int64_t)d * s.n_inst + set;
-        atomicAdd((unsigned long long *)&s.transitions[row], sh.trans);
-        atomicMax(&s.max_fired[row], sh.most);
-    }
-    if (m.phi_pre) {
-        // eq:numstep5 as written: phi from the state after the SSA, before the events
-        if (t < U && active) {
-            int32_t y[NC];
-#pragma unroll
-            for (int c = 0; c < NC; ++c) y[c] = sh.x[c][t];
-            double I = 0.0;
-            const double phi = sh.phi[t];
-            const double phi2 = phi_next<NC>(m, y, s.alpha[set], s.beta[set * 4 + season((int64_t)m.day0 + d)], phi, &I);
-            if (__double_as_longlong(phi2) != __double_as_longlong(phi)) s.phi[base + t] = phi2;
+            for (int c2 = 0; c2 < NC; ++c2) sh.x[i * NC + c2] = (int32_t)c.xd[c2];
+            sh.touch[i] = 1;
+            atomicAdd(&cnt.trans, (unsigned long long)c.fired);
+            atomicMax(&cnt.most, c.fired);
+        };
+        const int n_long = cnt.n[0], n_seg = cnt.n[1];
+        if (n_long > 0) {
+            int group_class = kLengthClasses, n_group = 0;  // classes from group_class on are the workgroup's
+            for (int b = kLengthClasses - 1; b > 0 && n_group + cnt.in_class[b] <= (b >= kFarClass ? 3 : 1); --b) {
+                group_class = b;
+                n_group += cnt.in_class[b];
+            }
+            for (int i = 0; n_group > 0 && i < n_long; ++i) {
+                const int entry = sh.list[i];
+                if (entry >> kStageShift < group_class) continue;
+                --n_group;
+                // the day's critical chain: its wavefronts issue ahead of the other
+                // waves on their SIMDs while it is walked
+                __builtin_amdgcn_s_setprio(3);
+                const int pos = entry & (kMaxUnit - 1);
+                const uint32_t node = (uint32_t)sh.node[pos];
+                typename Rules::State c;
+                load(pos, c);
+                Rules::rates(m, c);
+                uint32_t kb = 0;
+                if (!walk_group<Rules>(m, c, kb, node, (uint32_t)d, key0, key1, s.status, set) && wave == 0)
+                    walk_wave<Rules>(m, c, kb, node, (uint32_t)d, key0, key1, s.status, set, sh.tau);
+                if (t == 0) store(pos, c);
+                __builtin_amdgcn_s_setprio(0);
+                __syncthreads();  // the next chain reuses the walk's LDS
+            }
+            for (;;) {
+                int i = 0;
+                if (lane == 0) i = atomicAdd(&cnt.next[0], 1);
+                i = __builtin_amdgcn_readfirstlane(i);
+                if (i >= n_long) break;
+                const int entry = sh.list[i];
+                if (entry >> kStageShift >= group_class) continue;
+                const int pos = entry & (kMaxUnit - 1);
+                typename Rules::State c;
+                load(pos, c);
+                Rules::reactants(m, c);
+                walk_wave<Rules>(m, c, 0u, (uint32_t)sh.node[pos], (uint32_t)d, key0, key1, s.status, set,
+                                 sh.tau + 64 * wave);
+                if (lane == 0) store(pos, c);
+            }
+        }
+        if (n_seg > 0) {
+            auto take = [&](int n) {
+                int at = 0;
+                if (lane == 0) at = atomicAdd(&cnt.next[1], n);
+                return __builtin_amdgcn_readfirstlane(at);
+            };
+            walk_queue<Rules, 16>(m, n_seg, sh.tau + 64 * wave, take,
+                                  [&](int i, typename Rules::State &c, ChainKey &key) {
+                                      const int pos = sh.list[U + i];
+                                      load(pos, c);
+                                      key = ChainKey{0u, (uint32_t)sh.node[pos], (uint32_t)d, key0, key1, s.status, set};
+                                  },
+                                  [&](int i, const typename Rules::State &c) { store(sh.list[U + i], c); });
         }
         __syncthreads();
-    }
-    if (lds) {
-        if (has && !(sh.pe[t].meta & kMetaCont))
-            private_task_lds<NC>(sh.pe, t, npe, sh.x, sh.touch, (int32_t)base, d, key0, key1, set, s.status);
-        __syncthreads();
+        if (t == 0 && cnt.trans != 0ull) {
+            const int64_t row = (int64_t)d * s.n_inst + set;
+            atomicAdd((unsigned long long *)&s.transitions[row], cnt.trans);
+            atomicMax(&s.max_fired[row], cnt.most);
+        }
+        if (m.phi_pre) {
+            // eq:numstep5 as written: phi from the state after the SSA, before the events
+            if (t < U && active) {
+                int32_t y[NC];
+#pragma unroll
+                for (int c = 0; c < NC; ++c) y[c] = sh.x[t * NC + c];
+                double I = 0.0;
+                const double phi = sh.phi[t];
+                const double phi2 = phi_next<NC>(m, y, s.alpha[set], s.beta[set * 4 + season((int64_t)m.day0 + d)], phi, &I);
+                if (__double_as_longlong(phi2) != __double_as_longlong(phi)) s.phi[base + t] = phi2;
+            }
+            __syncthreads();
+        }
+        if (lds && npe > 0) {
+            if (has && !(sh.pe[t].meta & kMetaCont)) {
+                uint64_t pre[kPrivDraws];
+#pragma unroll
+                for (int i = 0; i < kPrivDraws; ++i) pre[i] = sh.pd[i * B + t];
+                private_task_lds<NC>(sh.pe, t, npe, sh.x, sh.touch, (int32_t)base, d, key0, key1, set, s.status, pre);
+            }
+            __syncthreads();
+        }
+    } else if (levels && t < U && sh.touch[t]) {
+        // (the closing launch has not handed its counts over)
+#pragma unroll
+        for (int c = 0; c < NC; ++c) sh.x[t * NC + c] = x[c];
     }
     if (t < U && sh.touch[t]) {
 #pragma unroll
         for (int c = 0; c < NC; ++c)
-            if (comp_on<NC>(m, c)) s.u[(int64_t)c * s.L + base + t] = sh.x[c][t];
+            if (comp_on<NC>(m, c)) s.u[(int64_t)c * s.L + base + t] = sh.x[t * NC + c];
     }
     if (!lds) {
         __syncthreads();
@@ -1776,10 +1977,11 @@ __global__ __launch_bounds__(kDayBlock) void k_day(Model m, DevState s, DevEvent
         fresh_l1();
     }
     if (stage_entry >= 0) {
+        int32_t *stage = ev.stage + (int64_t)(d & 1) * kDaySlotCap * MAXC;
         const int at = stage_entry & (kMaxUnit - 1), slot = stage_entry >> kStageShift;
 #pragma unroll
         for (int c = 0; c < NC; ++c)
-            ev.stage[slot * NC + c] = !comp_on<NC>(m, c) ? 0 : lds ? sh.x[c][at] : load_state(&s.u[(int64_t)c * s.L + base + at]);
+            stage[slot * NC + c] = !comp_on<NC>(m, c) ? 0 : lds ? sh.x[at * NC + c] : load_state(&s.u[(int64_t)c * s.L + base + at]);
     }
 }
 
@@ -2461,180 +2663,6 @@ __global__ __launch_bounds__(kEvBlock) void k_event_levels(Model m, DevState s, 
     }
 }
 
-// A day's levels in LDS (one lane per node): the nodes its level tasks touch
-// are loaded into slots once, every level updates the slots (draws with plain
-// LDS loads and stores, since a node drawn from is alone in its level;
-// additions with LDS atomics, which commute), and the slots are written back
-// once. Same draws and order as the global-memory path.
-template <int NC>
-__device__ __forceinline__ void slot_event(const Model &m, const DevState &s, const DevEvents &ev, uint32_t meta,
-                                           uint32_t smap, int32_t n, uint32_t g, int32_t e, int32_t *xs, int32_t *xd,
-                                           uint32_t key0, uint32_t key1, int32_t set, int32_t d,
-                                           unsigned long long *status, const uint64_t *pre) {
-    const int kind = (int)(meta & kEvKindMask);
-    const uint32_t mask = (meta >> 2) & 0xffu;
-    // A selection of one or two compartments c0 < c1 with its draws computed
-    // ahead (every column of the farm model, every movement of up to six
-    // animals): the running sums of the walk below are 0 before c0, x[c0]
-    // from c0 to c1 and the total from c1 on, so a pick below the count left
-    // in c0 takes from c0 and any other from c1 (the same picks, counts and
-    // write order as the walk over all compartments).
-    const uint32_t rest = mask & (mask - 1u);
-    if (mask != 0u && (rest & (rest - 1u)) == 0u && n <= kPreDraws && (kind != SIM_ENTER || rest == 0u)) {
-        const int c0 = __builtin_ctz(mask);
-        const int c1 = rest ? __builtin_ctz(rest) : c0;
-        if (kind == SIM_ENTER) {
-            __hip_atomic_fetch_add(&xs[c0], n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            return;
-        }
-        const int32_t x0 = xs[c0], x1 = rest ? xs[c1] : 0;
-        const long long tot = (long long)x0 + (long long)x1;
-        if ((long long)n > tot) {
-            atomicMin(status, ((unsigned long long)(uint32_t)ev.gm[e] << 32) | (unsigned long long)(uint32_t)set);
-            return;
-        }
-        if (tot <= 0x7fffffffLL) {
-            int32_t t0 = 0, t1 = 0;
-            uint32_t left0 = (uint32_t)x0;
-#pragma unroll
-            for (int q = 0; q < kPreDraws; ++q) {
-                if (q >= n) break;
-                const uint32_t pick = (uint32_t)__umul64hi(pre[q], (uint64_t)(tot - q));
-                const int in0 = pick < left0 ? 1 : 0;
-                left0 -= (uint32_t)in0;
-                t0 += in0;
-                t1 += 1 - in0;
-            }
-            xs[c0] = x0 - t0;
-            if (rest) xs[c1] = x1 - t1;
-            if (kind == SIM_INTERNAL) {
-                if (t0) xs[shifted(smap, c0)] += t0;
-                if (t1) xs[shifted(smap, c1)] += t1;
-            } else if (kind == SIM_EXTERNAL) {
-                if (t0) __hip_atomic_fetch_add(&xd[shifted(smap, c0)], t0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                if (t1) __hip_atomic_fetch_add(&xd[shifted(smap, c1)], t1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            }
-            return;
-        }
-    }
-    if (kind == SIM_ENTER) {
-#pragma unroll
-        for (int c = 0; c < NC; ++c)
-            if ((mask >> c) & 1u) __hip_atomic_fetch_add(&xs[c], n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        return;
-    }
-    int32_t x[NC];
-    long long tot = 0;
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-        x[c] = ((mask >> c) & 1u) ? xs[c] : 0;
-        tot += x[c];
-    }
-    if ((long long)n > tot) {
-        atomicMin(status, ((unsigned long long)(uint32_t)ev.gm[e] << 32) | (unsigned long long)(uint32_t)set);
-        return;
-    }
-    int32_t take[NC];
-    draw_individuals<NC>(x, take, mask, n, tot, g, d, key0, key1, pre);
-    if (kind == SIM_INTERNAL) {
-#pragma unroll
-        for (int c = 0; c < NC; ++c)
-            if ((mask >> c) & 1u) xs[c] = x[c];
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            if (take[c]) {
-                const int to = shifted(smap, c);
-                xs[to] += take[c];
-            }
-        }
-        return;
-    }
-#pragma unroll
-    for (int c = 0; c < NC; ++c)
-        if ((mask >> c) & 1u) xs[c] = x[c];
-    if (kind == SIM_EXTERNAL) {
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            if (take[c]) {
-                const int to = shifted(smap, c);
-                __hip_atomic_fetch_add(&xd[to], take[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            }
-        }
-    }
-}
-
-// The day's level events are contiguous (e0 .. e0 + ne - 1, by level, then
-// task); the launch carries the day's offsets, and the day kernel has staged
-// the slots' counts in slot order, so that staging is one round trip for the
-// event fields, slot keys, level bounds and counts. Every thread of the
-// workgroup calls it (any workgroup size).
-template <int NC>
-__device__ void event_day_levels(const Model &m, const DevState &s, const DevEvents &ev, const EventDayArgs &a,
-                                 int32_t d, EventDayShared<NC> &sh) {
-    const int nth = (int)blockDim.x;
-    const int32_t nl = a.nl, ns = a.ns, ne = (int32_t)a.ne, s0 = a.s0;
-    const int64_t e0 = a.e0;
-    for (int i = threadIdx.x; i <= nl; i += nth) sh.lv[i] = (int32_t)(ev.lvl_ev_off[a.lv0 + i] - e0);
-    for (int i = threadIdx.x; i < ne; i += nth) {
-        sh.meta[i] = ev.meta[e0 + i];
-        sh.smap[i] = ev.smap[e0 + i];
-        sh.n[i] = ev.n[e0 + i];
-        sh.g[i] = ev.g[e0 + i];
-        sh.ss[i] = (int16_t)ev.slot_src[e0 + i];
-        sh.sd[i] = (int16_t)ev.slot_dst[e0 + i];
-    }
-    // the slots' counts, staged by the day kernel (no wait for slot_pos)
-    for (int i = threadIdx.x; i < ns; i += nth) {
-        sh.k0[i] = ev.slot_key[3 * (s0 + i)];
-        sh.k1[i] = ev.slot_key[3 * (s0 + i) + 1];
-        sh.set[i] = (int32_t)ev.slot_key[3 * (s0 + i) + 2];
-        sh.pos[i] = ev.slot_pos[s0 + i];
-#pragma unroll
-        for (int c = 0; c < NC; ++c) sh.u[i * NC + c] = ev.stage[i * NC + c];
-    }
-    if (!block_ok_once(s.status)) return;  // its barrier also publishes the staged fields
-    // the first draws of every event do not depend on the state: all at once
-    for (int i = threadIdx.x; i < ne * (kPreDraws / 2); i += nth) {
-        const int j = i / (kPreDraws / 2), b = i % (kPreDraws / 2);
-        if ((int)(sh.meta[j] & kEvKindMask) == SIM_ENTER || 2 * b >= sh.n[j]) continue;
-        const int32_t ss = sh.ss[j];
-        const Word4 o = philox4x32_10(Word4{(uint32_t)b, (uint32_t)sh.g[j], (uint32_t)d, 1u}, sh.k0[ss], sh.k1[ss]);
-        sh.pre[j * kPreDraws + 2 * b] = ((uint64_t)o.b << 32) | o.a;
-        sh.pre[j * kPreDraws + 2 * b + 1] = ((uint64_t)o.d << 32) | o.c;
-    }
-    __syncthreads();
-    for (int32_t k = 0; k < nl; ++k) {
-        for (int32_t i = sh.lv[k] + threadIdx.x; i < sh.lv[k + 1]; i += nth) {
-            if (sh.meta[i] & kMetaCont) continue;  // applied with its task's first event
-            const int32_t ss = sh.ss[i];
-            int32_t *xs = &sh.u[ss * NC];
-            int32_t *xd = sh.sd[i] >= 0 ? &sh.u[sh.sd[i] * NC] : xs;
-            // one event, or a run of one node's events in list order
-            int32_t j = i;
-            do {
-                slot_event<NC>(m, s, ev, sh.meta[j], sh.smap[j], sh.n[j], (uint32_t)sh.g[j], (int32_t)(e0 + j), xs, xd,
-                               sh.k0[ss], sh.k1[ss], sh.set[ss], d, s.status, &sh.pre[j * kPreDraws]);
-                ++j;
-            } while (j < sh.lv[k + 1] && (sh.meta[j] & kMetaCont));
-        }
-        __syncthreads();
-    }
-    for (int i = threadIdx.x; i < ns; i += nth) {
-        const int32_t pos = sh.pos[i];
-#pragma unroll
-        for (int c = 0; c < NC; ++c)
-            if (comp_on<NC>(m, c)) s.u[(int64_t)c * s.L + pos] = sh.u[i * NC + c];
-    }
-}
-
-// A day's levels in LDS, launched on its own after the day kernel.
-template <int NC>
-__global__ __launch_bounds__(kEvBlock) void k_event_day(Model m, DevState s, DevEvents ev, int32_t d,
-                                                        EventDayArgs a) {
-    __shared__ EventDayShared<NC> sh;
-    event_day_levels<NC>(m, s, ev, a, d, sh);
-}
-
 // Slot handles: level k of each slot's own day (k = -1: its private tasks, which
 // come before its levels), one grid row per slot of
 // s.run_slots (the slots with a day of events this step). With
@@ -2845,7 +2873,8 @@ __global__ __launch_bounds__(kBlock) void k_persist(Model m, DevState s, DevEven
 
 template <class Rules>
 struct Kernels {
-    static void *day() { return (void *)&k_day<Rules>; }
+    static void *day() { return (void *)&k_day<Rules, false>; }
+    static void *day_levels() { return (void *)&k_day<Rules, true>; }
     static void *tile() { return (void *)&k_day_tile<Rules, false>; }
     static void *tile_slots() { return (void *)&k_day_tile<Rules, true>; }
     static void *far() { return (void *)&k_day_far<Rules, false>; }
@@ -2854,18 +2883,19 @@ struct Kernels {
     static void *levels() { return (void *)&k_event_levels<Rules::NC>; }
     static void *persist() { return (void *)&k_persist<Rules>; }
     static void *slot_events() { return (void *)&k_slot_events<Rules::NC>; }
-    static void *event_day() { return (void *)&k_event_day<Rules::NC>; }
+    static size_t day_lds(int U, int B, bool events) { return DayShared<Rules::NC>().place(nullptr, U, B, events); }
 };
 
 struct Table {
-    void *day, *events, *persist, *levels, *tile, *slot_events, *event_day, *tile_slots, *far, *far_slots;
+    void *day, *day_levels, *events, *persist, *levels, *tile, *slot_events, *tile_slots, *far, *far_slots;
+    size_t (*day_lds)(int U, int B, bool events);
 };
 
 template <class Rules>
 Table table() {
-    return {Kernels<Rules>::day(),    Kernels<Rules>::events(), Kernels<Rules>::persist(),
+    return {Kernels<Rules>::day(),    Kernels<Rules>::day_levels(), Kernels<Rules>::events(), Kernels<Rules>::persist(),
             Kernels<Rules>::levels(), Kernels<Rules>::tile(),   Kernels<Rules>::slot_events(),
-            Kernels<Rules>::event_day(), Kernels<Rules>::tile_slots(), Kernels<Rules>::far(), Kernels<Rules>::far_slots()};
+            Kernels<Rules>::tile_slots(), Kernels<Rules>::far(), Kernels<Rules>::far_slots(), &Kernels<Rules>::day_lds};
 }
 
 Table pick(const Model &m) {
@@ -2903,14 +2933,15 @@ static int launch_tiles(void *tile, void *far, const Model &m, DevState s, const
 }
 
 int launch_day(const Model &m, const DevState &s, const DevEvents &ev, int32_t d, int prologue, int ssa,
-               int layout, void *stream) {
+               const EventDayArgs &levels, int layout, void *stream) {
     if (s.L == 0) return hipSuccess;
     const Table t = pick(m);
     Model mm = m;
     DevState ss = s;
     DevEvents ee = ev;
     int32_t dd = d, pro = prologue, sa = ssa;
-    void *args[] = {&mm, &ss, &ee, &dd, &pro, &sa};
+    EventDayArgs lv = levels;
+    void *args[] = {&mm, &ss, &ee, &dd, &pro, &sa, &lv};
     if (layout == LAYOUT_TILE) {
         if (s.slots) return hipErrorInvalidValue;  // a slot handle's day runs through launch_slot_day
         return launch_tiles(t.tile, t.far, m, s, ev, d, prologue, ssa, s.RL / 64, stream);
@@ -2921,9 +2952,14 @@ int launch_day(const Model &m, const DevState &s, const DevEvents &ev, int32_t d
     // than compute units, fewer a unit let several run side by side (1,990
     // nodes of the synthetic model in units of 4, 60 days: 4.1 ms with 1,024
     // threads a unit, 3.4 with 512).
+    // A day's level events take a thread each, so those runs keep at least kDayEventCap.
     int block = kDayBlock;
-    while (block > 256 && block / 2 >= s.tile_nodes && (int64_t)grid * block > (int64_t)kUnitsWanted * kDayBlock) block /= 2;
-    return (int)hipLaunchKernel(t.day, dim3(grid), dim3((unsigned)block), args, 0, (hipStream_t)stream);
+    const int least = ev.unit_stage_off ? kDayEventCap : 256;
+    while (block > least && block / 2 >= s.tile_nodes && (int64_t)grid * block > (int64_t)kUnitsWanted * kDayBlock) block /= 2;
+    if (lv.ne > kDayEventCap || lv.ns > kDaySlotCap || lv.nl > kDayLevelCap) return hipErrorInvalidValue;
+    const bool staged = ev.unit_stage_off != nullptr;
+    const size_t lds = t.day_lds(s.tile_nodes, block, staged);
+    return (int)hipLaunchKernel(staged ? t.day_levels : t.day, dim3(grid), dim3((unsigned)block), args, lds, (hipStream_t)stream);
 }
 
 int launch_events(const Model &m, const DevState &s, const DevEvents &ev, int32_t d, int64_t begin,
@@ -3002,18 +3038,6 @@ int launch_slot_events(const Model &m, const DevState &s, const DevEvents &ev, i
     int32_t a = step, b = k, c = k_end;
     void *args[] = {&mm, &ss, &ee, &a, &b, &c};
     return (int)hipLaunchKernel(t.slot_events, dim3(gx, (unsigned)n_run), dim3(kEvBlock), args, 0, (hipStream_t)stream);
-}
-
-int launch_event_day(const Model &m, const DevState &s, const DevEvents &ev, int32_t d, const EventDayArgs &a,
-                     void *stream) {
-    const Table t = pick(m);
-    Model mm = m;
-    DevState ss = s;
-    DevEvents ee = ev;
-    int32_t dd = d;
-    EventDayArgs aa = a;
-    void *args[] = {&mm, &ss, &ee, &dd, &aa};
-    return (int)hipLaunchKernel(t.event_day, dim3(1), dim3(kEvBlock), args, 0, (hipStream_t)stream);
 }
 
 int launch_slot_init(const DevState &s, int32_t nc, const int32_t *u0, const double *v0, int32_t slot,

@@ -577,7 +577,7 @@ Layout layout_for(int64_t Np, int64_t n_nodes, int64_t n_inst, int64_t Nc, int64
     l.slot_pos = take(sizeof(int32_t) * n_day_slots);
     l.unit_stage_off = take(sizeof(int32_t) * (D * n_units + 1));
     l.unit_stage = take(sizeof(int32_t) * n_day_slots);
-    l.stage = take(sizeof(int32_t) * kDaySlotCap * MAXC);
+    l.stage = take(sizeof(int32_t) * 2 * kDaySlotCap * MAXC);
     l.slot_key = take(sizeof(uint32_t) * 3 * n_day_slots);
     l.lvl_ev_off = take(sizeof(int64_t) * (n_levels + 1));
     l.ev_slot_src = take(sizeof(int32_t) * n_events);
@@ -1482,8 +1482,12 @@ int sim_run(sim_handle *h, int32_t n_days) {
         });
         if (e != hipSuccess) return h->err = fmt("persistent launch: %s %s", hipGetErrorString(e), why), SIM_EDEVICE;
     } else {
+        EventDayArgs levels{};  // of the day before, if they run in the next launch
         for (int32_t d = d0; d < d1; ++d) {
-            hipError_t e = timed(h, SIM_K_DAY, [&] { return launch_day(h->model, h->st, h->ev, d, d > d0, 1, h->layout, h->stream); });
+            hipError_t e = timed(h, SIM_K_DAY, [&] {
+                return launch_day(h->model, h->st, h->ev, d, d > d0, 1, levels, h->layout, h->stream);
+            });
+            levels = EventDayArgs{};
             if (e != hipSuccess) return h->err = fmt("day kernel: %s", hipGetErrorString(e)), SIM_EDEVICE;
             if (h->layout == LAYOUT_TILE && h->priv_day[d + 1] > h->priv_day[d]) {
                 e = timed(h, SIM_K_EVENTS, [&] {
@@ -1491,20 +1495,18 @@ int sim_run(sim_handle *h, int32_t n_days) {
                 });
                 if (e != hipSuccess) return h->err = fmt("event kernel: %s", hipGetErrorString(e)), SIM_EDEVICE;
             }
-            // a day that fits runs its levels in LDS; otherwise big levels get a
-            // launch of their own and runs of small ones share one workgroup
+            // a day that fits runs its levels in LDS, in the next launch; otherwise
+            // big levels get a launch of their own and runs of small ones share
+            // one workgroup
             int32_t lv = h->lvl_ptr[d];
             const int32_t lv_end = h->lvl_ptr[d + 1];
             if (h->day_slot_off[d + 1] > h->day_slot_off[d]) {
-                EventDayArgs a{};
-                a.lv0 = lv;
-                a.nl = lv_end - lv;
-                a.s0 = h->day_slot_off[d];
-                a.ns = h->day_slot_off[d + 1] - a.s0;
-                a.e0 = h->lvl_ev_off[lv];
-                a.ne = h->lvl_ev_off[lv_end] - a.e0;
-                e = timed(h, SIM_K_EVENTS, [&] { return launch_event_day(h->model, h->st, h->ev, d, a, h->stream); });
-                if (e != hipSuccess) return h->err = fmt("event kernel: %s", hipGetErrorString(e)), SIM_EDEVICE;
+                levels.lv0 = lv;
+                levels.nl = lv_end - lv;
+                levels.s0 = h->day_slot_off[d];
+                levels.ns = h->day_slot_off[d + 1] - levels.s0;
+                levels.e0 = h->lvl_ev_off[lv];
+                levels.ne = h->lvl_ev_off[lv_end] - levels.e0;
                 lv = lv_end;
             }
             while (lv < lv_end) {
@@ -1524,7 +1526,7 @@ int sim_run(sim_handle *h, int32_t n_days) {
                 if (e != hipSuccess) return h->err = fmt("event kernel: %s", hipGetErrorString(e)), SIM_EDEVICE;
             }
         }
-        hipError_t e = timed(h, SIM_K_CLOSE, [&] { return launch_day(h->model, h->st, h->ev, d1, 1, 0, h->layout, h->stream); });
+        hipError_t e = timed(h, SIM_K_CLOSE, [&] { return launch_day(h->model, h->st, h->ev, d1, 1, 0, levels, h->layout, h->stream); });
         if (e != hipSuccess) return h->err = fmt("closing kernel: %s", hipGetErrorString(e)), SIM_EDEVICE;
     }
     h->day = d1;

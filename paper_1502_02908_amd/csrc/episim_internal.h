@@ -128,7 +128,8 @@ struct DevEvents {
     const int32_t *slot_pos;
     const int32_t *unit_stage_off;  // [D * n_units + 1]: slots of day d held by unit u (one lane per node):
     const int32_t *unit_stage;      // local position | slot << kStageShift
-    int32_t *stage;                 // [kDaySlotCap * MAXC]: their counts after the day kernel, [slot][c]
+    int32_t *stage;                 // [2][kDaySlotCap * MAXC], by parity of the day: their counts after the day
+                                    // kernel, [slot][c]
     const uint32_t *slot_key;   // [3 per slot] Philox key (seed, replicate id) and set of the slot's node
     const int64_t *lvl_ev_off;  // event offsets of each level
     const int32_t *slot_src;
@@ -171,8 +172,9 @@ struct EventDayArgs {
     int32_t lv0, nl, s0, ns;
     int64_t e0, ne;
 };
+// (levels: the level events of day d - 1 that run in this launch, ns = 0 if none)
 int launch_day(const Model &m, const DevState &s, const DevEvents &ev, int32_t d, int prologue, int ssa,
-               int layout, void *stream);
+               const EventDayArgs &levels, int layout, void *stream);
 int launch_events(const Model &m, const DevState &s, const DevEvents &ev, int32_t d, int64_t begin,
                   int64_t end, void *stream);
 int launch_event_levels(const Model &m, const DevState &s, const DevEvents &ev, int32_t d, int32_t lv_begin,
@@ -182,12 +184,10 @@ int launch_event_levels(const Model &m, const DevState &s, const DevEvents &ev, 
 constexpr int64_t kSmallLevel = 512;
 // a day with one lane per node, at most kDayEventCap level events in at most
 // kDayLevelCap levels and at most kDaySlotCap distinct nodes touched by them
-// runs its levels in LDS
+// runs its levels in LDS, in the next launch of the day kernel
 constexpr int64_t kDayEventCap = 512;
 constexpr int64_t kDaySlotCap = 768;
 constexpr int64_t kDayLevelCap = 64;
-int launch_event_day(const Model &m, const DevState &s, const DevEvents &ev, int32_t d, const EventDayArgs &a,
-                     void *stream);
 // A slot handle's step: the day kernel over the n_cols columns of s.run_cols,
 // and levels k .. k_end - 1 of the days of the n_run slots of s.run_slots.
 int launch_slot_day(const Model &m, const DevState &s, const DevEvents &ev, int32_t step, int32_t n_cols,

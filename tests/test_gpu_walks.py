@@ -95,3 +95,21 @@ def test_general_models(n_comp, bimolecular, reps):
     say(f"[walks] general n_comp={n_comp} bimolecular={bimolecular} reps={reps}")
     g = check(p)
     assert g["transitions"].sum() > 1000
+
+
+@pytest.mark.parametrize("n_comp,tile_nodes", [(2, 0), (3, 256), (8, 0), (8, 512)])
+def test_level_events_in_the_next_day(n_comp, tile_nodes):
+    # days of up to 512 level events on up to 768 nodes run in the next day's
+    # launch (or the closing one), larger days in launches of their own: the
+    # days here lie on both sides, and the run is cut so that the closing
+    # launch gets either kind
+    p = synth.sis_network(n_nodes=1500, n_days=10, seed=94, p_exit=0.02, p_enter=0.02, p_ext=0.33)
+    if n_comp > 2:
+        p = dataclasses.replace(chain_model(n_comp, 1500, 10, False, 94),
+                                **{k: v for k, v in vars(p).items() if k.startswith("ev_")})
+    p.record_days = np.array([0, 4, 9], np.int32)
+    move = p.ev_dest >= 0
+    n = [len(set(p.ev_node[move & (p.ev_day == d)]) | set(p.ev_dest[move & (p.ev_day == d)])) for d in range(10)]
+    say(f"[walks] level events n_comp={n_comp} tile_nodes={tile_nodes}: {min(n)} to {max(n)} nodes moved between a day")
+    assert min(n) < 768 < max(n)
+    check(p, chunks=[1, 2, 1, 3, 1, 1, 1], tile_nodes=tile_nodes)
