@@ -113,3 +113,17 @@ def test_level_events_in_the_next_day(n_comp, tile_nodes):
     say(f"[walks] level events n_comp={n_comp} tile_nodes={tile_nodes}: {min(n)} to {max(n)} nodes moved between a day")
     assert min(n) < 768 < max(n)
     check(p, chunks=[1, 2, 1, 3, 1, 1, 1], tile_nodes=tile_nodes)
+
+
+@pytest.mark.parametrize("kw", [dict(), dict(tile_nodes=512, heavy_herds=-1), dict(tile_nodes=8, heavy_herds=40)])
+def test_replicate_tiles_with_more_long_chains_than_listed(kw):
+    # 200 herds by 64 replicates, every chain of some 60 attempts: past the
+    # 4,096 of a list of long chains the rest are walked in place; with
+    # heavy_herds=-1 none is listed; chunks swap the lists' counters
+    p = synth.flip_classes(n_nodes=200, S0=10, I0=10, n_days=4)
+    p.u0 = np.ascontiguousarray(p.u0)
+    p.u0[::40, 0] = 900
+    p = p.with_replicates(64, replicate_id=np.arange(64, dtype=np.uint32) + 3)
+    p.record_days = np.array([0, 3], np.int32)
+    say(f"[walks] long chains in tiles {kw}")
+    check(p, chunks=[1, 2, 1], **kw)
