@@ -128,10 +128,8 @@ def chain_probe(P, synth, torch, half=1000, days=40, n_nodes=1, classes=1):
     animals, over the attempts of a day (transitions + 1). classes = 3 runs
     the same dynamics on the SISe3 compartments (S_j = I_j = half / 3 in each
     class), so the chain walks the six-compartment model as the farm
-    networks' herds do. With one node the chain is walked by a wavefront;
-    from 8192 nodes on, the largest herd has a workgroup as on the farm
-    networks (the workgroup walk while the chain expects 128 attempts or
-    more, then a wavefront's)."""
+    networks' herds do. A workgroup walks the chain, as it does the farm
+    networks' largest herds."""
     import numpy as np
 
     def day_us(S0):
@@ -616,7 +614,7 @@ def main():
         if hub_layout:
             short = chain_probe(P, synth, torch, half=1000, n_nodes=8192, classes=classes)
             long_ = chain_probe(P, synth, torch, half=10000, days=20, n_nodes=8192, classes=classes)
-            per_day_us = np.where(most + 1 >= 128, long_["us_per_attempt"], short["us_per_attempt"]) * (most + 1)
+            per_day_us = np.where(most + 1 >= 10000, long_["us_per_attempt"], short["us_per_attempt"]) * (most + 1)
             probes = [short, long_]
         else:
             one = chain_probe(P, synth, torch, classes=classes)
@@ -631,7 +629,7 @@ def main():
                         cycles_per_attempt=[round(q["cycles_per_attempt"], 1) for q in probes],
                         chain_ms_per_step=round(chain_ms, 3), step_ms=round(step_ms, 3),
                         frac=round(chain_ms / step_ms, 4), probe=[q["probe"] for q in probes],
-                        rule="longest chains of 128 attempts or more at the second probe's rate" if hub_layout else "")
+                        rule="longest chains of 10,000 attempts or more at the second probe's rate" if hub_layout else "")
     roofline["binding"] = ("serial SSA chain of the day's largest herd (critical_path.frac of the step), "
                            "not HBM")
     tag = {"sise3-37k": "sq_37k", "sise3-1m": "sq_1m", "sise3-37k-u10": "sq_u10",
