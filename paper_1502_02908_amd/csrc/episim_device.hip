@@ -2679,11 +2679,10 @@ __global__ __launch_bounds__(kEvBlock) void k_slot_events(Model m, DevState s, D
     if (!block_ok_once(status)) return;
     const int32_t W = s.slot_lanes;
     const int32_t lv0 = ev.lvl_ptr[d], lv_day_end = ev.lvl_ptr[d + 1];
-    const int64_t units = s.Np / s.tile_nodes;
     const int64_t stride = (int64_t)gridDim.x * kEvBlock;
     for (int32_t kk = k; kk < k_end && (kk < 0 || lv0 + kk < lv_day_end); ++kk) {
-        const int64_t begin = kk < 0 ? ev.priv_off[d * units] : ev.lvl_off[lv0 + kk];
-        const int64_t end = kk < 0 ? ev.priv_off[(d + 1) * units] : ev.lvl_off[lv0 + kk + 1];
+        const int64_t begin = kk < 0 ? ev.priv_off[d] : ev.lvl_off[lv0 + kk];
+        const int64_t end = kk < 0 ? ev.priv_off[d + 1] : ev.lvl_off[lv0 + kk + 1];
         const int64_t count = (end - begin) * W;
         for (int64_t t = (int64_t)blockIdx.x * kEvBlock + threadIdx.x; t < count; t += stride) {
             const int32_t rr = (int32_t)(t % W);

@@ -401,12 +401,15 @@ int64_t lane_unit(int64_t n_nodes) {
 // pos_node[pos] = node or -1.
 constexpr int64_t kSoloHerds = 128;
 // Replicate tiles: positions of a unit unless tile_nodes names them: a workgroup's
-// share of a launch over all columns (in groups of four, at most kMaxTileUnit).
+// share of a launch over all columns (in groups of four, at most kMaxTileUnit),
+// less what an even split over as many units leaves free.
 constexpr int64_t kMaxTileUnit = 512;
 int64_t tile_unit(int64_t n_nodes, int64_t n_cols) {
     const int64_t wanted = n_nodes * n_cols < kNarrow ? kTileBlocks : kTileBlocksWide;
     const int64_t share = (n_nodes * n_cols + wanted - 1) / wanted;
-    return std::min(kMaxTileUnit, std::max<int64_t>(1, (share + 3) / 4) * 4);
+    const int64_t unit = std::min(kMaxTileUnit, std::max<int64_t>(1, (share + 3) / 4) * 4);
+    const int64_t units = std::max<int64_t>(1, (n_nodes + unit - 1) / unit);
+    return std::max<int64_t>(1, ((n_nodes + units - 1) / units + 3) / 4) * 4;
 }
 
 // With one lane per node and per-day launches, the largest herds of a large
@@ -700,7 +703,8 @@ int build_packed(const sim_problem *const *ps, int32_t n, int32_t events_mode, P
     if (pk->n_events > INT32_MAX) return *err = "too many events", SIM_EINVAL;
     if (pk->layout == LAYOUT_TILE) {
         const int64_t L = pk->Np * pk->RL;
-        pk->far_cap = std::min(L, std::max<int64_t>(L / 8, 4096));
+        // (the same room a column in a slot handle)
+        pk->far_cap = n_slots > 0 ? L / 8 + 4096 : std::min(L, std::max<int64_t>(L / 8, 4096));
     }
     pk->node_id.assign(pk->Np, -1);
     pk->inst.assign(pk->Np, 0);
@@ -828,8 +832,10 @@ int build_packed(const sim_problem *const *ps, int32_t n, int32_t events_mode, P
     // tasks in execution order: level tasks by level, then by first event;
     // then private tasks by day, unit and first event; a task's events stay
     // together in list order. Levels and (day, unit) pairs belong to one day,
-    // so each range counts and places its own tasks.
-    const int64_t U = pk->Np / pk->tile;
+    // so each range counts and places its own tasks. (Replicate tiles with
+    // per-day launches run a day's private tasks in one launch: one unit.)
+    const bool by_day = pk->layout == LAYOUT_TILE && (n_slots > 0 || launch == SIM_LAUNCH_KERNELS);
+    const int64_t U = by_day ? 1 : pk->Np / pk->tile;
     pk->n_units = U;
     big_vec<int64_t> task_glv(n_tasks);
     big_vec<int32_t> task_n(n_tasks), tslot(n_tasks);
@@ -838,7 +844,7 @@ int build_packed(const sim_problem *const *ps, int32_t n, int32_t events_mode, P
     run_ranges(cut, [&](int c, int64_t b, int64_t end) {
         std::fill(task_n.begin() + tcut[c], task_n.begin() + tcut[c + 1], 0);
         for (int64_t e = b; e < end; ++e) {
-            task_glv[task[e]] = priv[task[e]] ? (int64_t)mday[e] * U + mnode[e] / pk->tile
+            task_glv[task[e]] = priv[task[e]] ? (int64_t)mday[e] * U + (by_day ? 0 : mnode[e] / pk->tile)
                                               : pk->lvl_ptr[mday[e]] + level[e] - 1;
             task_n[task[e]]++;
         }

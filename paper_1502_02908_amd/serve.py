@@ -91,7 +91,8 @@ def pick_slot(free, running, per_col):
 def plan_slots(networks, hbm_budget, demand, max_slots=None, slot_lanes=64):
     """Slots per network from an HBM byte budget split in proportion to
     `demand` (expected lane-days per network); at least one column of 64
-    lanes each, whole columns only."""
+    lanes each, whole columns only. Returns the slots and the bytes that a
+    handle of as many takes, per network."""
     per_col = 64 // slot_lanes
     max_slots = 256 * per_col if max_slots is None else max_slots
     per, base = [], []
@@ -104,15 +105,29 @@ def plan_slots(networks, hbm_budget, demand, max_slots=None, slot_lanes=64):
         base.append(one - (two - one))
     w = np.asarray(demand, float)
     w = w / w.sum()
-    out = []
+    out, taken = [], []
     for j, net in enumerate(networks):
-        n = int((hbm_budget * w[j] - base[j]) // per[j])
-        # lane indices stay below 2^31: positions (nodes plus padding and the
-        # units of the largest herds) times the lanes of all slots
-        cap = (2 ** 31 - 1) // (slot_lanes * (net.n_nodes + 512))
+        share = hbm_budget * w[j]
+        n = int((share - base[j]) // per[j])
+        # lane indices stay below 2^31: positions (nodes plus the padding of at
+        # most one unit) times the lanes of all slots
+        cap = min((2 ** 31 - 1) // (slot_lanes * (net.n_nodes + 512)), 65535)
         n = int(min(max(n, per_col), max_slots, cap))
-        out.append(max(per_col, n // per_col * per_col))
-    return out, [int(b + n * p) for b, n, p in zip(base, out, per)]
+        n = max(per_col, n // per_col * per_col)
+        # the columns take nearly the same bytes each: the padding of the
+        # positions and the alignment of the arrays differ with their number
+        nbytes = SlotHandle.workspace_bytes(net, n, slot_lanes)
+        while nbytes > share and n > per_col:
+            n -= per_col
+            nbytes = SlotHandle.workspace_bytes(net, n, slot_lanes)
+        while n + per_col <= min(max_slots, cap):
+            more = SlotHandle.workspace_bytes(net, n + per_col, slot_lanes)
+            if more > share:
+                break
+            n, nbytes = n + per_col, more
+        out.append(n)
+        taken.append(nbytes)
+    return out, taken
 
 
 class Server:
