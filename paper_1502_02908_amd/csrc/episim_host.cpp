@@ -377,6 +377,24 @@ int32_t lane_stride(int32_t R, int layout) {
     return layout == LAYOUT_LANES ? 1 : (int32_t)(((int64_t)R + 63) / 64 * 64);
 }
 
+// Groups that fill whole units: the herds of one instance and region, and each
+// herd that gets a unit to itself.
+struct UnitGroups {
+    std::vector<int64_t> nodes;  // herds of each group
+    int64_t all = 0;             // herds of all groups
+    void add(int64_t n) {
+        if (n > 0) nodes.push_back(n);
+        all += n;
+    }
+    int64_t largest() const { return nodes.empty() ? 0 : *std::max_element(nodes.begin(), nodes.end()); }
+    int64_t units(int64_t u) const {
+        int64_t k = 0;
+        for (int64_t n : nodes) k += (n + u - 1) / u;
+        return k;
+    }
+    int64_t positions(int64_t u) const { return u * units(u); }
+};
+
 // One lane per node: positions of a unit (a workgroup of the day kernel) unless
 // tile_nodes names them: the fewest, as a power of two from 4, that leave at
 // most one unit per compute unit, so that a day's chains spread over as many of
@@ -384,9 +402,16 @@ int32_t lane_stride(int32_t R, int layout) {
 // nodes on 1024, whose wavefronts all have owners. 1,000 nodes, 365 days: 7.3
 // ms in units of 4, 8.1 of 64, 9.1 of 256; 5,000 nodes of a general model, 120
 // days: 3.6 ms in units of 32, 8.3 of 4, five to a compute unit.)
-int64_t lane_unit(int64_t n_nodes) {
+// Where many small groups fill more units than that anyway, a unit grows only
+// while their number falls, and past 256 positions only as long as few of them
+// stay empty, a quarter of the herds' number (5,000 networks of 50 herds, a day in units of 32 / 64 / 256 / 1024:
+// 103 / 75 / 82 / 227 us; 2,000 of 130 in 128 / 256 / 512 / 1024: 73 / 62 / 81 /
+// 122; 300,000 herds in 1,000 regions in 256 / 512 / 1024: 77 / 70 / 91).
+int64_t lane_unit(const UnitGroups &g) {
     int64_t u = 4;
-    while (u < kMaxUnit && (n_nodes + u - 1) / u > kUnitsWanted) u *= 2;
+    while (u < kMaxUnit && g.units(u) > kUnitsWanted && g.units(2 * u) < g.units(u) &&
+           (2 * u <= 256 || g.positions(2 * u) <= std::max(g.all + g.all / 4, g.positions(u))))
+        u *= 2;
     return u;
 }
 
@@ -402,14 +427,21 @@ int64_t lane_unit(int64_t n_nodes) {
 constexpr int64_t kSoloHerds = 128;
 // Replicate tiles: positions of a unit unless tile_nodes names them: a workgroup's
 // share of a launch over all columns (in groups of four, at most kMaxTileUnit),
-// less what an even split over as many units leaves free.
+// less what an even split of the largest group over as many units leaves free,
+// and halved while more positions than herds would stay empty. (Not for fewer:
+// a workgroup closes the records of each region and network that its range
+// meets; 30,000 herds in 1,000 regions by 64 replicates, a day in units of 12 /
+// 48 / 120: 389 / 350 / 345 us.)
 constexpr int64_t kMaxTileUnit = 512;
-int64_t tile_unit(int64_t n_nodes, int64_t n_cols) {
-    const int64_t wanted = n_nodes * n_cols < kNarrow ? kTileBlocks : kTileBlocksWide;
-    const int64_t share = (n_nodes * n_cols + wanted - 1) / wanted;
-    const int64_t unit = std::min(kMaxTileUnit, std::max<int64_t>(1, (share + 3) / 4) * 4);
-    const int64_t units = std::max<int64_t>(1, (n_nodes + unit - 1) / unit);
-    return std::max<int64_t>(1, ((n_nodes + units - 1) / units + 3) / 4) * 4;
+int64_t tile_unit(const UnitGroups &g, int64_t n_cols) {
+    auto fours = [](int64_t n) { return std::max<int64_t>(1, (n + 3) / 4) * 4; };
+    const int64_t wanted = g.all * n_cols < kNarrow ? kTileBlocks : kTileBlocksWide;
+    int64_t unit = std::min(kMaxTileUnit, fours((g.all * n_cols + wanted - 1) / wanted));
+    const int64_t units = std::max<int64_t>(1, (g.largest() + unit - 1) / unit);
+    unit = fours((g.largest() + units - 1) / units);
+    while (unit > 4 && g.positions(unit) > 2 * g.all && g.positions(fours(unit / 2)) < g.positions(unit))
+        unit = fours(unit / 2);
+    return unit;
 }
 
 // With one lane per node and per-day launches, the largest herds of a large
@@ -678,19 +710,30 @@ int build_packed(const sim_problem *const *ps, int32_t n, int32_t events_mode, P
     std::vector<std::vector<int32_t>> pos_node(n);
     pk->inst_off.assign(n, 0);
     pk->inst_pos0.assign(n, 0);
-    int64_t all = 0;
-    for (int32_t k = 0; k < n; ++k) all += ps[k]->n_nodes;
+    auto solo_herds = [&](const sim_problem *p) -> int64_t {  // herds with a unit each
+        return pk->layout == LAYOUT_LANES && launch == SIM_LAUNCH_KERNELS && p->n_nodes >= kGroupMinNodes && group_herds >= 0
+                   ? (group_herds > 0 ? group_herds : kGroupHerds) : 0;
+    };
+    UnitGroups groups;
+    for (int32_t k = 0; k < n; ++k) {
+        const sim_problem *p = ps[k];
+        std::vector<int64_t> in(p->n_regions > 0 ? p->n_regions + 1 : 1, 0);  // herds outside regions, then by region
+        if (p->n_regions > 0)
+            for (int32_t i = 0; i < p->n_nodes; ++i) in[p->region[i] + 1]++;
+        else
+            in[0] = p->n_nodes - solo_herds(p);
+        for (int64_t nodes : in) groups.add(nodes);
+        for (int64_t q = 0; q < solo_herds(p); ++q) groups.add(1);
+    }
     if (pk->layout == LAYOUT_TILE && launch == SIM_LAUNCH_KERNELS && !(o && o->tile_nodes > 0))
-        pk->tile = tile_unit(all, pk->RL / 64);
+        pk->tile = tile_unit(groups, pk->RL / 64);
     if (pk->layout == LAYOUT_LANES) {
-        pk->tile = launch == SIM_LAUNCH_PERSISTENT ? kPersistUnit : o && o->tile_nodes > 0 ? o->tile_nodes : lane_unit(all);
+        pk->tile = launch == SIM_LAUNCH_PERSISTENT ? kPersistUnit : o && o->tile_nodes > 0 ? o->tile_nodes : lane_unit(groups);
     }
     for (int32_t k = 0; k < n; ++k) {
         pk->inst_off[k] = (int32_t)pk->n_nodes;
         pk->inst_pos0[k] = (int32_t)pk->Np;
-        const int64_t group = (pk->layout == LAYOUT_LANES && launch == SIM_LAUNCH_KERNELS &&
-                               ps[k]->n_nodes >= kGroupMinNodes && group_herds >= 0)
-                                  ? (group_herds > 0 ? group_herds : kGroupHerds) : 0;
+        const int64_t group = solo_herds(ps[k]);
         std::vector<int32_t> preg;
         const int64_t np_k = order_nodes(ps[k], pk->layout, pk->layout == LAYOUT_LANES && launch == SIM_LAUNCH_PERSISTENT, pk->tile,
                                           group, &pos_node[k], &preg);
