@@ -1090,7 +1090,7 @@ __device__ __forceinline__ int32_t wave_max(int32_t v) {
 // Sum tallies over the workgroup and add them to the records of one set
 // (every lane of the workgroup belongs to the same trajectory).
 template <int NC>
-__device__ void flush_block(const Model &m, const DevState &s, const Tally<NC> &t, int32_t set, int32_t d_rec,
+__device__ __forceinline__ void flush_block(const Model &m, const DevState &s, const Tally<NC> &t, int32_t set, int32_t d_rec,
                             int32_t d_ssa, int32_t region) {
     __shared__ long long part[kWaves][2 + NC];
     __shared__ int32_t part_most[kWaves];
@@ -1138,7 +1138,7 @@ __device__ void flush_block(const Model &m, const DevState &s, const Tally<NC> &
 // Sum tallies over the wavefronts of a replicate tile (lane = replicate) and
 // add them to the records of the lane's set.
 template <int NC>
-__device__ void flush_tile(const Model &m, const DevState &s, const Tally<NC> &t, int32_t set, int32_t d_rec,
+__device__ __forceinline__ void flush_tile(const Model &m, const DevState &s, const Tally<NC> &t, int32_t set, int32_t d_rec,
                            int32_t d_ssa, int32_t region) {
     __shared__ long long part[kWaves][64][2 + NC];
     __shared__ int32_t part_most[kWaves][64];
