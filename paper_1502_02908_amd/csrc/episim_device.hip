@@ -33,9 +33,8 @@ namespace {
 
 constexpr int kBlock = 256;
 static_assert(kBlock == kPersistUnit, "a workgroup of the persistent kernel's one-lane-per-node layout is one unit");
-constexpr int kDayBlock = 1024;  // workgroup of the one-lane-per-node day kernel
-constexpr int kDayWaves = kDayBlock / 64;
-static_assert(kDayWaves == 16, "the workgroup walk exchanges one value per lane of a row");
+constexpr int kDayWaves = 16;  // wavefronts of a workgroup of the one-lane-per-node day kernel, at most
+static_assert(kDayWaves == 16 && kMaxUnit == 64 * kDayWaves, "the workgroup walk exchanges one value per lane of a row");
 constexpr int kMaxScratchDevices = 64;
 constexpr int kWaves = kBlock / 64;
 constexpr int kEvKindMask = 3;
@@ -162,6 +161,7 @@ struct GenericChain : Chain<NC_, NT_> {
 template <int NC_, int NT_>
 struct GenericRules {
     static constexpr int NC = NC_, NT = NT_;
+    static constexpr int kDayThreads = day_threads(NC, NT, false);
     static constexpr int kTileWaves = 2;  // waves per SIMD the replicate-tile kernel is built for
     using State = GenericChain<NC, NT>;
     __device__ static __forceinline__ double rate(const Model &m, const State &c, int k) {
@@ -246,6 +246,7 @@ struct GenericRules {
 template <int NP>
 struct PairRules {
     static constexpr int NC = 2 * NP, NT = 2 * NP;
+    static constexpr int kDayThreads = day_threads(NC, NT, true);
     // replicate tiles of paired classes are built for three waves per SIMD
     // (at most 168 VGPRs, with a 16-byte spill): the third wave hides the
     // latency of the chains' dependent binary64 arithmetic and of the state
@@ -677,7 +678,7 @@ __device__ bool walk_group(const Model &m, typename Rules::State &c, uint32_t &k
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const unsigned long long below = (1ull << lane) - 1ull;
     int buf = 0;
-    if (round < kDayBlock) {  // the wavefronts that are not there add nothing
+    if (round < 64 * kDayWaves) {  // the wavefronts that are not there add nothing
         if (t < kDayWaves) {
 #pragma unroll
             for (int k = 0; k < kWords; ++k) sh_flow[0][k][t] = sh_flow[1][k][t] = 0;
@@ -1673,7 +1674,7 @@ __device__ __forceinline__ void event_levels_lds(const DevState &s, const DevEve
 // LEVELS: some day of the run has such events (the plain variant keeps the
 // registers for them free).
 template <class Rules, bool LEVELS>
-__global__ __launch_bounds__(kDayBlock) void k_day(Model m, DevState s, DevEvents ev, int32_t d, int32_t prologue,
+__global__ __launch_bounds__(Rules::kDayThreads) void k_day(Model m, DevState s, DevEvents ev, int32_t d, int32_t prologue,
                                                    int32_t ssa, EventDayArgs a) {
     constexpr int NC = Rules::NC, NT = Rules::NT;
     extern __shared__ __align__(16) char day_lds[];
@@ -2888,19 +2889,20 @@ struct Kernels {
 struct Table {
     void *day, *day_levels, *events, *persist, *levels, *tile, *slot_events, *tile_slots, *far, *far_slots;
     size_t (*day_lds)(int U, int B, bool events);
+    int day_threads;
 };
 
 template <class Rules>
 Table table() {
     return {Kernels<Rules>::day(),    Kernels<Rules>::day_levels(), Kernels<Rules>::events(), Kernels<Rules>::persist(),
             Kernels<Rules>::levels(), Kernels<Rules>::tile(),   Kernels<Rules>::slot_events(),
-            Kernels<Rules>::tile_slots(), Kernels<Rules>::far(), Kernels<Rules>::far_slots(), &Kernels<Rules>::day_lds};
+            Kernels<Rules>::tile_slots(), Kernels<Rules>::far(), Kernels<Rules>::far_slots(), &Kernels<Rules>::day_lds, Rules::kDayThreads};
 }
 
 Table pick(const Model &m) {
     if (m.pairs && m.nc == 2) return table<PairRules<1>>();
     if (m.pairs && m.nc == 6) return table<PairRules<3>>();
-    if (m.nc <= 4 && m.nt <= 4) return table<GenericRules<4, 4>>();
+    if (!large_model(m.nc, m.nt, m.pairs != 0)) return table<GenericRules<4, 4>>();
     return table<GenericRules<MAXC, MAXT>>();
 }
 
@@ -2945,16 +2947,16 @@ int launch_day(const Model &m, const DevState &s, const DevEvents &ev, int32_t d
         if (s.slots) return hipErrorInvalidValue;  // a slot handle's day runs through launch_slot_day
         return launch_tiles(t.tile, t.far, m, s, ev, d, prologue, ssa, s.RL / 64, stream);
     }
-    if (s.tile_nodes < 4 || s.tile_nodes > kMaxUnit || s.L % s.tile_nodes != 0) return hipErrorInvalidValue;
+    if (s.tile_nodes < 4 || s.tile_nodes > t.day_threads || s.L % s.tile_nodes != 0) return hipErrorInvalidValue;
     const unsigned grid = (unsigned)(s.L / s.tile_nodes);
-    // Sixteen wavefronts a unit fill a compute unit; where there are more units
+    // As many wavefronts a unit as its registers allow fill a compute unit; where there are more units
     // than compute units, fewer a unit let several run side by side (1,990
     // nodes of the synthetic model in units of 4, 60 days: 4.1 ms with 1,024
     // threads a unit, 3.4 with 512).
     // A day's level events take a thread each, so those runs keep at least kDayEventCap.
-    int block = kDayBlock;
+    int block = t.day_threads;
     const int least = ev.unit_stage_off ? kDayEventCap : 256;
-    while (block > least && block / 2 >= s.tile_nodes && (int64_t)grid * block > (int64_t)kUnitsWanted * kDayBlock) block /= 2;
+    while (block > least && block / 2 >= s.tile_nodes && (int64_t)grid * block > (int64_t)kUnitsWanted * t.day_threads) block /= 2;
     if (lv.ne > kDayEventCap || lv.ns > kDaySlotCap || lv.nl > kDayLevelCap) return hipErrorInvalidValue;
     const bool staged = ev.unit_stage_off != nullptr;
     const size_t lds = t.day_lds(s.tile_nodes, block, staged);

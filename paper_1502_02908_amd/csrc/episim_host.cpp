@@ -365,6 +365,17 @@ int same_model(const sim_problem *a, const sim_problem *b, std::string *err) {
     return SIM_OK;
 }
 
+// Paired S <-> I classes: transition k moves one individual from compartment k to k ^ 1.
+bool paired(const sim_problem *p) {
+    if (p->n_comp != p->n_trans || p->n_comp % 2 != 0) return false;
+    for (int k = 0; k < p->n_trans; ++k) {
+        if (p->reactant[k] != k || (p->reactant2 && p->reactant2[k] >= 0)) return false;
+        for (int c = 0; c < p->n_comp; ++c)
+            if (p->S[(size_t)c * p->n_trans + k] != (c == k ? -1 : (c == (k ^ 1) ? 1 : 0))) return false;
+    }
+    return true;
+}
+
 // One lane per node for a single replicate (the persistent kernel also runs one
 // in tiles where tile_nodes asks for them).
 int choose_layout(int32_t R, int32_t tile_nodes, int32_t launch) {
@@ -407,9 +418,9 @@ struct UnitGroups {
 // stay empty, a quarter of the herds' number (5,000 networks of 50 herds, a day in units of 32 / 64 / 256 / 1024:
 // 103 / 75 / 82 / 227 us; 2,000 of 130 in 128 / 256 / 512 / 1024: 73 / 62 / 81 /
 // 122; 300,000 herds in 1,000 regions in 256 / 512 / 1024: 77 / 70 / 91).
-int64_t lane_unit(const UnitGroups &g) {
+int64_t lane_unit(const UnitGroups &g, int64_t most) {
     int64_t u = 4;
-    while (u < kMaxUnit && g.units(u) > kUnitsWanted && g.units(2 * u) < g.units(u) &&
+    while (u < most && g.units(u) > kUnitsWanted && g.units(2 * u) < g.units(u) &&
            (2 * u <= 256 || g.positions(2 * u) <= std::max(g.all + g.all / 4, g.positions(u))))
         u *= 2;
     return u;
@@ -728,7 +739,8 @@ int build_packed(const sim_problem *const *ps, int32_t n, int32_t events_mode, P
     if (pk->layout == LAYOUT_TILE && launch == SIM_LAUNCH_KERNELS && !(o && o->tile_nodes > 0))
         pk->tile = tile_unit(groups, pk->RL / 64);
     if (pk->layout == LAYOUT_LANES) {
-        pk->tile = launch == SIM_LAUNCH_PERSISTENT ? kPersistUnit : o && o->tile_nodes > 0 ? o->tile_nodes : lane_unit(groups);
+        pk->tile = launch == SIM_LAUNCH_PERSISTENT ? kPersistUnit : o && o->tile_nodes > 0 ? o->tile_nodes
+                   : lane_unit(groups, day_threads(p0->n_comp, p0->n_trans, paired(p0)));
     }
     for (int32_t k = 0; k < n; ++k) {
         pk->inst_off[k] = (int32_t)pk->n_nodes;
@@ -1284,15 +1296,7 @@ int create(const sim_problem *const *ps, int32_t n, const sim_device_opts *o, si
         }
     m.imask = p->phi_I_mask;
     m.nmask = p->phi_N_mask;
-    // paired S <-> I classes: transition k moves one individual from compartment k to k ^ 1
-    m.pairs = (h->Nc == h->Nt && h->Nc % 2 == 0) ? 1 : 0;
-    for (int k = 0; k < h->Nt && m.pairs; ++k) {
-        if (p->reactant[k] != k || m.reactant2[k] >= 0) m.pairs = 0;
-        for (int c = 0; c < h->Nc && m.pairs; ++c) {
-            const int want = c == k ? -1 : (c == (k ^ 1) ? 1 : 0);
-            if (p->S[(size_t)c * h->Nt + k] != want) m.pairs = 0;
-        }
-    }
+    m.pairs = paired(p) ? 1 : 0;
 
     // --- device memory
     h->lay = layout_of(pk, p);

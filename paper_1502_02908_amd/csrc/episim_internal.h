@@ -162,6 +162,16 @@ constexpr double kGroupMinAttempts = 256.0;  // default: a workgroup walks a cha
 constexpr int kMaxUnit = 1024;
 constexpr int kPersistUnit = 256;
 constexpr int64_t kUnitsWanted = 256;  // one a compute unit
+// Threads of a workgroup of the one-lane-per-node day kernel, and with them the
+// most positions of a unit: 1,024 (of 128 registers each), for the general
+// models of more than four compartments or transitions 512 (of 256): with
+// 1,024 their kernel spilled about 500 registers a thread to memory (eight
+// compartments, a day of 20,000 herds: 204 -> 98 us; with short chains 101 ->
+// 56, of 400,000 herds 397 -> 275).
+constexpr bool large_model(int nc, int nt, bool pairs) {
+    return !(pairs && (nc == 2 || nc == 6)) && (nc > 4 || nt > 4);
+}
+constexpr int day_threads(int nc, int nt, bool pairs) { return large_model(nc, nt, pairs) ? 512 : 1024; }
 constexpr int kStageShift = 10;
 static_assert(kMaxUnit == 1 << kStageShift, "local positions fit below the slot (and the length class of a chain)");
 enum { LAYOUT_LANES = 0, LAYOUT_TILE = 1 };

@@ -1,5 +1,6 @@
 """Units of work on the GPU against the oracle, bit for bit: networks packed in
-one handle that fill units of their own sizes."""
+one handle that fill units of their own sizes, and the units of the general
+models of more than four compartments."""
 import numpy as np
 import pytest
 
@@ -7,7 +8,8 @@ from farmnet import synth
 from oracle import oracle as O
 import paper_1502_02908_amd as P
 
-from .gpu_common import assert_parity, say
+from .gpu_common import assert_parity, gpu_run, say
+from .test_gpu_walks import chain_model
 
 pytestmark = pytest.mark.gpu
 
@@ -36,3 +38,13 @@ def test_packed_networks_of_uneven_sizes(sizes, reps):
         one = {k: g[k][:, rows] for k in ("prevalence", "transitions", "totals", "max_transitions")}
         one.update({k: g[k][:, :, herds] for k in ("snap_u", "snap_v")}, u=u[:, herds], v=v[:, herds])
         assert_parity(one, O.run(p, threads=8))
+
+
+@pytest.mark.parametrize("n_comp,n_nodes,kw", [(5, 700, {}), (8, 2100, dict(tile_nodes=512)), (8, 140000, {})])
+def test_large_general_models(n_comp, n_nodes, kw):
+    # units of 4 and of 512 positions, as many as a workgroup of these models
+    # has threads (140,000 herds would fill 1,024 each otherwise)
+    p = chain_model(n_comp, n_nodes, 3, n_comp == 8, 95)
+    p.record_days = np.array([2], np.int32)
+    say(f"[units] general model of {n_comp}, {n_nodes} herds {kw}")
+    assert_parity(gpu_run(p, **kw), O.run(p, threads=8))
