@@ -152,11 +152,24 @@ struct Chain {
 // Besides the counts a chain keeps the reactant counts of every transition,
 // xr[k] = X[reactant[k]] (and xr2[k] of the second reactant of a mass-action
 // rate), which the walks by many lanes update from the picks directly
-// (Model::react). Transitions past the model's have rate constant 0.
+// (ModelTables::react). Transitions past the model's have rate constant 0.
 template <int NC_, int NT_>
 struct GenericChain : Chain<NC_, NT_> {
     double xr[NT_], xr2[NT_];
 };
+
+// The model's tables, read with scalar loads where they are used: kept in
+// registers over a kernel, their values (and the masks of their comparisons)
+// would be spilled and read back lane by lane. (Eight compartments, 512 threads
+// a workgroup: 1,425 scalar and 119 vector registers spilled, now 567 and none; a
+// day of 20,000 herds 98 us, now 70, with short chains 56 and 39. Three
+// compartments 52 us, now 45.)
+using ScalarTables = const __attribute__((address_space(4))) ModelTables;
+__device__ __forceinline__ ScalarTables &model_tables(const Model &m) {
+    uint64_t p = (uint64_t)m.tables;
+    asm volatile("" : "+s"(p));
+    return *(ScalarTables *)p;
+}
 
 template <int NC_, int NT_>
 struct GenericRules {
@@ -164,19 +177,21 @@ struct GenericRules {
     static constexpr int kDayThreads = day_threads(NC, NT, false);
     static constexpr int kTileWaves = 2;  // waves per SIMD the replicate-tile kernel is built for
     using State = GenericChain<NC, NT>;
-    __device__ static __forceinline__ double rate(const Model &m, const State &c, int k) {
+    __device__ static __forceinline__ double rate(ScalarTables &tb, const State &c, int k) {
         const double w = c.cphi[k] * c.xr[k];
         // a mass-action rate is also proportional to its second reactant
-        return m.reactant2[k] >= 0 ? w * c.xr2[k] : w;
+        return tb.reactant2[k] >= 0 ? w * c.xr2[k] : w;
     }
+    __device__ static __forceinline__ double rate(const Model &m, const State &c, int k) { return rate(model_tables(m), c, k); }
     __device__ static __forceinline__ void reactants(const Model &m, State &c) {
+        ScalarTables &tb = model_tables(m);
 #pragma unroll
         for (int k = 0; k < NT; ++k) {
             double a = 0.0, b = 0.0;
 #pragma unroll
             for (int cc = 0; cc < NC; ++cc) {
-                if (m.reactant[k] == cc) a = c.xd[cc];
-                if (m.reactant2[k] == cc) b = c.xd[cc];
+                if (tb.reactant[k] == cc) a = c.xd[cc];
+                if (tb.reactant2[k] == cc) b = c.xd[cc];
             }
             c.xr[k] = a;
             c.xr2[k] = b;
@@ -184,20 +199,22 @@ struct GenericRules {
     }
     __device__ static __forceinline__ void rates(const Model &m, State &c) {
         reactants(m, c);
+        ScalarTables &tb = model_tables(m);
         double lam = 0.0;
 #pragma unroll
         for (int k = 0; k < NT; ++k) {
-            lam = lam + rate(m, c, k);
+            lam = lam + rate(tb, c, k);
             c.cum[k] = lam;
         }
         c.lam = lam;
     }
     __device__ static __forceinline__ void apply(const Model &m, int j, State &c) {
+        ScalarTables &tb = model_tables(m);
 #pragma unroll
         for (int k = 0; k < NT; ++k) {
             if (k == j) {
 #pragma unroll
-                for (int cc = 0; cc < NC; ++cc) c.xd[cc] = c.xd[cc] + (double)m.S[cc][k];
+                for (int cc = 0; cc < NC; ++cc) c.xd[cc] = c.xd[cc] + tb.S[cc][k];
             }
         }
     }
@@ -212,17 +229,18 @@ struct GenericRules {
     // product and sum of counts is an exact integer)
     __device__ static __forceinline__ void cum_after(const Model &m, const State &c, const int (&n)[kFlows],
                                                      double (&cum)[NT]) {
+        ScalarTables &tb = model_tables(m);
         double l = 0.0;
 #pragma unroll
         for (int k = 0; k < NT; ++k) {
             double a = c.xr[k];
 #pragma unroll
-            for (int i = 0; i < NT; ++i) a = __builtin_fma(m.react[k][i], (double)n[i], a);
+            for (int i = 0; i < NT; ++i) a = __builtin_fma(tb.react[k][i], (double)n[i], a);
             double w = c.cphi[k] * a;
-            if (m.reactant2[k] >= 0) {
+            if (tb.reactant2[k] >= 0) {
                 double b = c.xr2[k];
 #pragma unroll
-                for (int i = 0; i < NT; ++i) b = __builtin_fma(m.react2[k][i], (double)n[i], b);
+                for (int i = 0; i < NT; ++i) b = __builtin_fma(tb.react2[k][i], (double)n[i], b);
                 w = w * b;
             }
             l = l + w;
@@ -230,10 +248,11 @@ struct GenericRules {
         }
     }
     __device__ static __forceinline__ void advance(const Model &m, State &c, const int (&n)[kFlows]) {
+        ScalarTables &tb = model_tables(m);
 #pragma unroll
         for (int cc = 0; cc < NC; ++cc) {
 #pragma unroll
-            for (int k = 0; k < NT; ++k) c.xd[cc] = __builtin_fma((double)m.S[cc][k], (double)n[k], c.xd[cc]);
+            for (int k = 0; k < NT; ++k) c.xd[cc] = __builtin_fma(tb.S[cc][k], (double)n[k], c.xd[cc]);
         }
         reactants(m, c);
     }
@@ -667,7 +686,7 @@ constexpr int kGroupPasses = 8;
 constexpr double kGroupRest = 24.0;
 
 template <class Rules>
-__device__ bool walk_group(const Model &m, typename Rules::State &c, uint32_t &kbase, uint32_t node, uint32_t day,
+__device__ __forceinline__ bool walk_group(const Model &m, typename Rules::State &c, uint32_t &kbase, uint32_t node, uint32_t day,
                            uint32_t key0, uint32_t key1, unsigned long long *status, int32_t r) {
     constexpr int NT = Rules::NT, K = Rules::kFlows;
     constexpr int kWords = (K + 2) / 2;  // flows and the moved mark, two to a word
@@ -1544,7 +1563,7 @@ constexpr int kPrivDraws = 2;
 // A run that draws has the node to itself; runs of additions only may share it
 // and add atomically. pre: the first draws of event i.
 template <int NC>
-__device__ void private_task_lds(const PrivEv *pe, int i, int n_ev, int32_t *xs, int32_t *touch, int32_t base,
+__device__ __forceinline__ void private_task_lds(const PrivEv *pe, int i, int n_ev, int32_t *xs, int32_t *touch, int32_t base,
                                  int32_t d, uint32_t key0, uint32_t key1, int32_t set, unsigned long long *status,
                                  const uint64_t (&pre)[kPrivDraws]) {
     const int loc = pe[i].node - base;

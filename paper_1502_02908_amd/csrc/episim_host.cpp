@@ -581,7 +581,7 @@ int64_t order_nodes(const sim_problem *p, int layout, bool by_wave, int64_t tile
 struct Layout {
     size_t u, phi, node_id, inst, inst_off, seed, coef, alpha, beta, repid, status, ev_g, ev_gm, ev_node,
         ev_dest, ev_n, ev_meta, ev_smap, task_off, priv_off, priv_ev_off, day_slot_off, slot_pos, unit_stage_off, unit_stage, stage, slot_key, lvl_ev_off, ev_slot_src, ev_slot_dst, lvl_off, lvl_ptr, prevalence, transitions, totals, max_fired, snap_u, snap_v, rec_slot, slots,
-        u0, v0, run, far_list, far_n, pos_region, regional, goal_ref, goal_part, total;
+        u0, v0, run, tables, far_list, far_n, pos_region, regional, goal_ref, goal_part, total;
 };
 
 size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -648,6 +648,7 @@ Layout layout_for(int64_t Np, int64_t n_nodes, int64_t n_inst, int64_t Nc, int64
     l.u0 = take(n_slots ? sizeof(int32_t) * Nc * Np : 0);
     l.v0 = take(n_slots ? sizeof(double) * Np : 0);
     // slot handles: the step's running slots, then its running columns
+    l.tables = take(sizeof(ModelTables));
     l.run = take(n_slots ? sizeof(int32_t) * (n_slots + RL / 64) : 0);
     l.total = off;
     return l;
@@ -1281,18 +1282,19 @@ int create(const sim_problem *const *ps, int32_t n, const sim_device_opts *o, si
     m.day0 = p->day0;
     m.seed = p->seed;
     m.phi_pre = p->phi_pre_events;
-    for (int k = 0; k < MAXT; ++k) m.reactant2[k] = -1;
     m.uses_phi = 0;
+    ModelTables tables{};
+    for (int k = 0; k < MAXT; ++k) tables.reactant2[k] = -1;
     for (int k = 0; k < h->Nt; ++k) {
         if (p->uses_phi[k]) m.uses_phi |= 1u << k;
-        m.reactant[k] = p->reactant[k];
-        m.reactant2[k] = p->reactant2 ? p->reactant2[k] : -1;
-        for (int c = 0; c < h->Nc; ++c) m.S[c][k] = p->S[(size_t)c * h->Nt + k];
+        tables.reactant[k] = p->reactant[k];
+        if (p->reactant2) tables.reactant2[k] = p->reactant2[k];
+        for (int c = 0; c < h->Nc; ++c) tables.S[c][k] = (double)p->S[(size_t)c * h->Nt + k];
     }
     for (int k = 0; k < h->Nt; ++k)
         for (int i = 0; i < h->Nt; ++i) {
-            m.react[k][i] = (double)m.S[m.reactant[k]][i];
-            m.react2[k][i] = m.reactant2[k] >= 0 ? (double)m.S[m.reactant2[k]][i] : 0.0;
+            tables.react[k][i] = tables.S[tables.reactant[k]][i];
+            tables.react2[k][i] = tables.reactant2[k] >= 0 ? tables.S[tables.reactant2[k]][i] : 0.0;
         }
     m.imask = p->phi_I_mask;
     m.nmask = p->phi_N_mask;
@@ -1352,6 +1354,7 @@ int create(const sim_problem *const *ps, int32_t n, const sim_device_opts *o, si
     h->slot_lanes = pk.slot_lanes;
     s.few_chains = opts.few_chains < 0 ? 0u : (opts.few_chains > 0 ? (uint32_t)opts.few_chains : kFewChains);
     s.group_min_attempts = opts.group_min_attempts > 0 ? (double)opts.group_min_attempts : kGroupMinAttempts;
+    m.tables = at<ModelTables>(h->ws, l.tables);
     s.far_list = at<int32_t>(h->ws, l.far_list);
     s.far_n = at<int32_t>(h->ws, l.far_n);
     s.far_cap = (int32_t)pk.far_cap;
@@ -1421,6 +1424,7 @@ int create(const sim_problem *const *ps, int32_t n, const sim_device_opts *o, si
         {(void *)ev.lvl_off, pk.lvl_off.data(), sizeof(int64_t) * (pk.n_levels + 1)},
         {(void *)ev.lvl_ptr, pk.lvl_ptr.data(), sizeof(int32_t) * (h->D + 1)},
         {(void *)s.rec_slot, pk.rec_slot.data(), sizeof(int32_t) * h->D},
+        {(void *)m.tables, &tables, sizeof tables},
         {(void *)s.pos_region, pk.pos_region.data(), s.n_regions ? sizeof(int32_t) * pk.pos_region.size() : 0},
     };
     for (const Up &up : ups) {

@@ -31,6 +31,14 @@ __host__ __device__ inline uint32_t meta_pack(int kind, uint32_t mask, int shift
 constexpr int MAX_SHIFT_IDS = 63;
 constexpr uint32_t kMetaCont = 1u << 16;
 
+// What the general models (those not in paired classes) read of S and the reactants.
+struct ModelTables {
+    double react[MAXT][MAXT], react2[MAXT][MAXT];  // change of X[reactant[k]], X[reactant2[k]] when transition i fires
+    double S[MAXC][MAXT];                          // S[c][k]
+    int32_t reactant[MAXT];
+    int32_t reactant2[MAXT];                       // second reactant of a mass-action rate, -1 if none
+};
+
 // Model description, passed by value (lands in the kernel-argument segment,
 // read with scalar loads).
 struct Model {
@@ -40,12 +48,8 @@ struct Model {
     uint32_t seed;
     uint32_t uses_phi;          // bit k: rate k proportional to phi
     uint32_t imask, nmask;      // compartments counted in I and in N
-    int32_t reactant[MAXT];
-    int32_t reactant2[MAXT];    // second reactant of a mass-action rate, -1 if none
     int32_t phi_pre;            // 1: phi from the state after the SSA, before the events
-    int32_t S[MAXC][MAXT];      // S[c][k]
-    // change of X[reactant[k]] and X[reactant2[k]] when transition i fires
-    double react[MAXT][MAXT], react2[MAXT][MAXT];
+    const struct ModelTables *tables;  // of the general models, in device memory
 };
 
 // One slot of a slot handle: the handle step at which the slot's day 0 runs
@@ -164,10 +168,10 @@ constexpr int kPersistUnit = 256;
 constexpr int64_t kUnitsWanted = 256;  // one a compute unit
 // Threads of a workgroup of the one-lane-per-node day kernel, and with them the
 // most positions of a unit: 1,024 (of 128 registers each), for the general
-// models of more than four compartments or transitions 512 (of 256): with
-// 1,024 their kernel spilled about 500 registers a thread to memory (eight
-// compartments, a day of 20,000 herds: 204 -> 98 us; with short chains 101 ->
-// 56, of 400,000 herds 397 -> 275).
+// models of more than four compartments or transitions, whose walks take 170
+// registers, 512 (of 256). With 1,024 they spilled about 500 to memory (eight
+// compartments, a day of 20,000 herds: 204 us with 1,024, 98 with 512; with
+// short chains 101 and 56).
 constexpr bool large_model(int nc, int nt, bool pairs) {
     return !(pairs && (nc == 2 || nc == 6)) && (nc > 4 || nt > 4);
 }
