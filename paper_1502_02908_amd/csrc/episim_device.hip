@@ -34,7 +34,7 @@ namespace {
 constexpr int kBlock = 256;
 static_assert(kBlock == kPersistUnit, "a workgroup of the persistent kernel's one-lane-per-node layout is one unit");
 constexpr int kDayWaves = 16;  // wavefronts of a workgroup of the one-lane-per-node day kernel, at most
-static_assert(kDayWaves == 16 && kMaxUnit == 64 * kDayWaves, "the workgroup walk exchanges one value per lane of a row");
+static_assert(kDayWaves == 16 && kMaxUnit <= 64 * kDayWaves, "the workgroup walk exchanges one value per lane of a row");
 constexpr int kMaxScratchDevices = 64;
 constexpr int kWaves = kBlock / 64;
 constexpr int kEvKindMask = 3;
@@ -1577,7 +1577,7 @@ __device__ __forceinline__ void private_task_lds(const PrivEv *pe, int i, int n_
 }
 
 // One lane per node: a workgroup runs one unit of s.tile_nodes positions (4 to
-// 1024), thread t < tile_nodes owning position t. The counts live in LDS for
+// 512), thread t < tile_nodes owning position t. The counts live in LDS for
 // the day: the owners close the previous day and list their node's chain, as
 // long if it expects kWaveChain attempts (lambda) or more; then the whole
 // workgroup walks the longest chains one after another (walk_group), its
@@ -1692,8 +1692,19 @@ __device__ __forceinline__ void event_levels_lds(const DevState &s, const DevEve
 
 // LEVELS: some day of the run has such events (the plain variant keeps the
 // registers for them free).
-template <class Rules, bool LEVELS>
-__global__ __launch_bounds__(Rules::kDayThreads) void k_day(Model m, DevState s, DevEvents ev, int32_t d, int32_t prologue,
+// OWN: where every wavefront has herds of its own (launch_day), the segments of
+// walk_queue are short of nothing but instructions, and 16 lanes for a chain of
+// a few attempts waste them. A wavefront with kOwnFirst short chains or more
+// then walks them where they are listed, each in its owner's lane, until
+// kOwnRest are left; those are listed and start again in a segment. (A day of
+// 1.5 million herds, all infected: SISe3 536 -> 210 us, SIS 376 -> 170; of
+// 100,000 herds with four times the rates 87 -> 67. Without the owners' walk
+// the kernel takes 10 registers less, 0.8 us of 22 a day on 37,000 herds with
+// a tenth infected.)
+constexpr int kOwnFirst = 24, kOwnRest = 8;
+
+template <class Rules, bool LEVELS, bool OWN>
+__global__ __launch_bounds__(OWN ? kMaxUnit : Rules::kDayThreads) void k_day(Model m, DevState s, DevEvents ev, int32_t d, int32_t prologue,
                                                    int32_t ssa, EventDayArgs a) {
     constexpr int NC = Rules::NC, NT = Rules::NT;
     extern __shared__ __align__(16) char day_lds[];
@@ -1850,7 +1861,35 @@ __global__ __launch_bounds__(Rules::kDayThreads) void k_day(Model m, DevState s,
                 cls = 1 + (ch.lam >= 4.0 * gm) + (ch.lam >= 16.0 * gm) + (ch.lam >= 64.0 * gm) + (ch.lam >= 256.0 * gm);
                 atomicAdd(&cnt.in_class[cls], 1);
             }
-            const int kind = !(ch.lam > 0.0) ? -1 : (cls > 0 || ch.lam >= kWaveChain ? 0 : 1);
+            int kind = !(ch.lam > 0.0) ? -1 : (cls > 0 || ch.lam >= kWaveChain ? 0 : 1);
+            if constexpr (OWN) {
+                if (__popcll(__ballot(kind == 1)) >= kOwnFirst) {
+                    ch.clock = 0.0;
+                    ch.fired = 0;
+                    bool live = kind == 1;
+                    for (uint32_t k2 = 0; __popcll(__ballot(live)) > kOwnRest; ++k2) {
+                        if (!live) continue;
+                        const Draw q2 = draw_attempt(k2, (uint32_t)q.nid, (uint32_t)d, key0, key1);
+                        live = chain_step<Rules>(m, ch, q2.E, q2.U, s.status, set);
+                    }
+                    int32_t fired = 0;
+                    if (kind == 1 && !live) {
+                        kind = -1;
+                        fired = ch.fired;
+                        if (fired) {
+#pragma unroll
+                            for (int c = 0; c < NC; ++c) sh.x[t * NC + c] = (int32_t)ch.xd[c];
+                            sh.touch[t] = 1;
+                        }
+                    }
+                    const long long sum = wave_sum(fired);
+                    const int32_t most = wave_max(fired);
+                    if (lane == 0 && sum) {
+                        atomicAdd(&cnt.trans, (unsigned long long)sum);
+                        atomicMax(&cnt.most, most);
+                    }
+                }
+            }
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
                 const unsigned long long in = __ballot(kind == i);
@@ -2892,8 +2931,10 @@ __global__ __launch_bounds__(kBlock) void k_persist(Model m, DevState s, DevEven
 
 template <class Rules>
 struct Kernels {
-    static void *day() { return (void *)&k_day<Rules, false>; }
-    static void *day_levels() { return (void *)&k_day<Rules, true>; }
+    static void *day(bool levels, bool own) {
+        return levels ? (own ? (void *)&k_day<Rules, true, true> : (void *)&k_day<Rules, true, false>)
+                      : (own ? (void *)&k_day<Rules, false, true> : (void *)&k_day<Rules, false, false>);
+    }
     static void *tile() { return (void *)&k_day_tile<Rules, false>; }
     static void *tile_slots() { return (void *)&k_day_tile<Rules, true>; }
     static void *far() { return (void *)&k_day_far<Rules, false>; }
@@ -2906,14 +2947,15 @@ struct Kernels {
 };
 
 struct Table {
-    void *day, *day_levels, *events, *persist, *levels, *tile, *slot_events, *tile_slots, *far, *far_slots;
+    void *(*day)(bool levels, bool own);
+    void *events, *persist, *levels, *tile, *slot_events, *tile_slots, *far, *far_slots;
     size_t (*day_lds)(int U, int B, bool events);
     int day_threads;
 };
 
 template <class Rules>
 Table table() {
-    return {Kernels<Rules>::day(),    Kernels<Rules>::day_levels(), Kernels<Rules>::events(), Kernels<Rules>::persist(),
+    return {&Kernels<Rules>::day,     Kernels<Rules>::events(), Kernels<Rules>::persist(),
             Kernels<Rules>::levels(), Kernels<Rules>::tile(),   Kernels<Rules>::slot_events(),
             Kernels<Rules>::tile_slots(), Kernels<Rules>::far(), Kernels<Rules>::far_slots(), &Kernels<Rules>::day_lds, Rules::kDayThreads};
 }
@@ -2966,7 +3008,7 @@ int launch_day(const Model &m, const DevState &s, const DevEvents &ev, int32_t d
         if (s.slots) return hipErrorInvalidValue;  // a slot handle's day runs through launch_slot_day
         return launch_tiles(t.tile, t.far, m, s, ev, d, prologue, ssa, s.RL / 64, stream);
     }
-    if (s.tile_nodes < 4 || s.tile_nodes > t.day_threads || s.L % s.tile_nodes != 0) return hipErrorInvalidValue;
+    if (s.tile_nodes < 4 || s.tile_nodes > kMaxUnit || s.L % s.tile_nodes != 0) return hipErrorInvalidValue;
     const unsigned grid = (unsigned)(s.L / s.tile_nodes);
     // As many wavefronts a unit as its registers allow fill a compute unit; where there are more units
     // than compute units, fewer a unit let several run side by side (1,990
@@ -2979,7 +3021,9 @@ int launch_day(const Model &m, const DevState &s, const DevEvents &ev, int32_t d
     if (lv.ne > kDayEventCap || lv.ns > kDaySlotCap || lv.nl > kDayLevelCap) return hipErrorInvalidValue;
     const bool staged = ev.unit_stage_off != nullptr;
     const size_t lds = t.day_lds(s.tile_nodes, block, staged);
-    return (int)hipLaunchKernel(staged ? t.day_levels : t.day, dim3(grid), dim3((unsigned)block), args, lds, (hipStream_t)stream);
+    // half the wavefronts or more own herds, and there are several workgroups to a compute unit
+    const bool own = block <= kMaxUnit && 2 * s.tile_nodes >= block;
+    return (int)hipLaunchKernel(t.day(staged, own), dim3(grid), dim3((unsigned)block), args, lds, (hipStream_t)stream);
 }
 
 int launch_events(const Model &m, const DevState &s, const DevEvents &ev, int32_t d, int64_t begin,

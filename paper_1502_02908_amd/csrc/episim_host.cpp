@@ -407,24 +407,30 @@ struct UnitGroups {
 };
 
 // One lane per node: positions of a unit (a workgroup of the day kernel) unless
-// tile_nodes names them: the fewest, as a power of two from 4, that leave at
-// most one unit per compute unit, so that a day's chains spread over as many of
-// them as there are. (37k nodes: 256 positions in 145 units; from 262,144
-// nodes on 1024, whose wavefronts all have owners. 1,000 nodes, 365 days: 7.3
-// ms in units of 4, 8.1 of 64, 9.1 of 256; 5,000 nodes of a general model, 120
-// days: 3.6 ms in units of 32, 8.3 of 4, five to a compute unit.)
+// tile_nodes names them: the fewest, as a power of two from 4 to 256, that leave
+// at most one unit per compute unit, so that a day's chains spread over as many
+// of them as there are. (37k nodes: 256 positions in 145 units. 1,000 nodes, 365
+// days: 7.3 ms in units of 4, 8.1 of 64, 9.1 of 256; 5,000 nodes of a general
+// model, 120 days: 3.6 ms in units of 32, 8.3 of 4, five to a compute unit.)
+// 512 from two units of 256 per compute unit on, for models whose workgroups of
+// 512 threads leave room for another (1.5 million herds, a day in units of 256 /
+// 512: 140 / 124 us with a hundredth of them infected, 206 / 210 with all of them;
+// 100,000 herds 67 / 72; 400,000 herds of eight compartments 169 / 204).
 // Where many small groups fill more units than that anyway, a unit grows only
 // while their number falls, and past 256 positions only as long as few of them
-// stay empty, a quarter of the herds' number (5,000 networks of 50 herds, a day in units of 32 / 64 / 256 / 1024:
-// 103 / 75 / 82 / 227 us; 2,000 of 130 in 128 / 256 / 512 / 1024: 73 / 62 / 81 /
-// 122; 300,000 herds in 1,000 regions in 256 / 512 / 1024: 77 / 70 / 91).
-int64_t lane_unit(const UnitGroups &g, int64_t most) {
+// stay empty, a quarter of the herds' number (5,000 networks of 50 herds, a day
+// in units of 32 / 64 / 256 / 1024: 103 / 75 / 82 / 227 us; 2,000 of 130 in 128 /
+// 256 / 512 / 1024: 73 / 62 / 81 / 122; 300,000 herds in 1,000 regions in 256 /
+// 512 / 1024: 77 / 70 / 91).
+int64_t lane_unit(const UnitGroups &g, bool large) {
     int64_t u = 4;
-    while (u < most && g.units(u) > kUnitsWanted && g.units(2 * u) < g.units(u) &&
-           (2 * u <= 256 || g.positions(2 * u) <= std::max(g.all + g.all / 4, g.positions(u))))
-        u *= 2;
+    while (u < 256 && g.units(u) > kUnitsWanted && g.units(2 * u) < g.units(u)) u *= 2;
+    if (u == 256 && !large && g.units(256) > 2 * kUnitsWanted &&
+        g.positions(512) <= std::max(g.all + g.all / 4, g.positions(256)))
+        u = 512;
     return u;
 }
+static_assert(kMaxUnit == 512, "the largest unit of lane_unit and of tile_nodes");
 
 // Positions of one instance's nodes: herds sorted by size (largest first)
 // are dealt one per unit of work in turn, back and forth (snake order), so the
@@ -741,7 +747,7 @@ int build_packed(const sim_problem *const *ps, int32_t n, int32_t events_mode, P
         pk->tile = tile_unit(groups, pk->RL / 64);
     if (pk->layout == LAYOUT_LANES) {
         pk->tile = launch == SIM_LAUNCH_PERSISTENT ? kPersistUnit : o && o->tile_nodes > 0 ? o->tile_nodes
-                   : lane_unit(groups, day_threads(p0->n_comp, p0->n_trans, paired(p0)));
+                   : lane_unit(groups, large_model(p0->n_comp, p0->n_trans, paired(p0)));
     }
     for (int32_t k = 0; k < n; ++k) {
         pk->inst_off[k] = (int32_t)pk->n_nodes;
