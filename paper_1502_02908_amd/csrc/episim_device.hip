@@ -2398,14 +2398,19 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(Rules::k
 // parameters, about 10 us), so where there are more chains than wavefronts a
 // wavefront takes up to kFarBatch of the shortest class together: a lane each
 // for the loads and stores. d is the day, in a slot handle the step.
+// GROUP: the day waits for its longest chain here, so chains of the longest
+// class get a workgroup each (walk_group) while they leave half the workgroups
+// to the others: a wavefront takes 31 cycles an attempt, a workgroup 10 to 13
+// (37,000 herds, a day with 2 / 8 / 32 / 64 replicates: 243 / 347 / 391 / 417 us
+// with wavefronts, 181 / 241 / 277 / 295 with workgroups).
 constexpr int kFarBatch = 8;
 
-template <class Rules, bool SLOTS>
-__global__ __launch_bounds__(kBlock) void k_day_far(Model m, DevState s, DevEvents, int32_t d) {
+template <class Rules, bool SLOTS, bool GROUP>
+__global__ __launch_bounds__(GROUP ? Rules::kDayThreads : kBlock) void k_day_far(Model m, DevState s, DevEvents, int32_t d) {
     constexpr int NC = Rules::NC, NT = Rules::NT;
-    __shared__ double sh_tau[kWaves][64];
+    constexpr int kBlockWaves = (GROUP ? Rules::kDayThreads : kBlock) / 64;
+    __shared__ double sh_tau[kBlockWaves][64];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int waves = (int)(gridDim.x * kWaves);
     static_assert(kFarLists == 3, "two classes walked singly, one in batches");
     const int32_t *counts = s.far_n + (d & 1) * kFarLists;
     const int n0 = min(counts[0], s.far_cap), n1 = min(counts[1], s.far_cap), n2 = min(counts[2], s.far_cap);
@@ -2414,16 +2419,25 @@ __global__ __launch_bounds__(kBlock) void k_day_far(Model m, DevState s, DevEven
     }
     // the next day's lists start empty (this launch reads the other parity)
     if (blockIdx.x == 0 && threadIdx.x < kFarLists) s.far_n[((d + 1) & 1) * kFarLists + threadIdx.x] = 0;
+    // workgroups 0 .. n_group - 1 walk a chain of the first class each, the
+    // wavefronts of the others what is left: neighbours in a list, which are of
+    // one herd and about as long, in workgroups of sixteen wavefronts apart
+    const int n_group = GROUP && 2 * n0 <= (int)gridDim.x ? n0 : 0;
+    const bool group = (int)blockIdx.x < n_group;
+    const int others = (int)gridDim.x - n_group, waves = others * kBlockWaves, singles = n0 - n_group + n1;
     const int batch = max(1, min(kFarBatch, n2 / waves));
-    const int items = n0 + n1 + (n2 + batch - 1) / batch;
-    for (int w = (int)(blockIdx.x * kWaves) + wave; w < items; w += waves) {
+    const int items = group ? 1 : singles + (n2 + batch - 1) / batch;
+    const int first = GROUP ? (group ? 0 : wave * others + (int)blockIdx.x - n_group) : (int)blockIdx.x * kBlockWaves + wave;
+    for (int w = first; w < items; w += waves) {
         int64_t at = w;
         int count = 1;
-        if (w >= n0 + n1) {
-            at = (int64_t)2 * s.far_cap + (int64_t)(w - n0 - n1) * batch;
-            count = min(batch, n2 - (w - n0 - n1) * batch);
-        } else if (w >= n0) {
-            at = (int64_t)s.far_cap + (w - n0);
+        if (group) {
+            at = blockIdx.x;
+        } else if (w >= singles) {
+            at = (int64_t)2 * s.far_cap + (int64_t)(w - singles) * batch;
+            count = min(batch, n2 - (w - singles) * batch);
+        } else if (w >= n0 - n_group) {
+            at = (int64_t)s.far_cap + (w - (n0 - n_group));
         }
         // lane b < count holds chain b of the batch
         const bool mine = lane < count;
@@ -2462,18 +2476,27 @@ __global__ __launch_bounds__(kBlock) void k_day_far(Model m, DevState s, DevEven
             unsigned long long *stb = (unsigned long long *)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane(
                                                                   (int)(uint32_t)(st >> 32), b) << 32) |
                                                               (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)st, b));
-            walk_wave<Rules>(m, c, 0u, (uint32_t)__builtin_amdgcn_readlane(q.nid, b),
-                             (uint32_t)__builtin_amdgcn_readlane(day, b),
-                             (uint32_t)__builtin_amdgcn_readlane((int)key0, b),
-                             (uint32_t)__builtin_amdgcn_readlane((int)key1, b), stb,
-                             __builtin_amdgcn_readlane(set, b), sh_tau[wave]);
+            const uint32_t node = (uint32_t)__builtin_amdgcn_readlane(q.nid, b), on_day = (uint32_t)__builtin_amdgcn_readlane(day, b),
+                           k0 = (uint32_t)__builtin_amdgcn_readlane((int)key0, b),
+                           k1 = (uint32_t)__builtin_amdgcn_readlane((int)key1, b);
+            const int32_t of = __builtin_amdgcn_readlane(set, b);
+            uint32_t kb = 0;
+            bool done = false;
+            if constexpr (GROUP) {
+                if (group) {
+                    Rules::rates(m, c);
+                    __builtin_amdgcn_s_setprio(3);
+                    done = walk_group<Rules>(m, c, kb, node, on_day, k0, k1, stb, of) || wave != 0;
+                }
+            }
+            if (!done) walk_wave<Rules>(m, c, kb, node, on_day, k0, k1, stb, of, sh_tau[wave]);
             if (lane == b) {
                 fired = c.fired;
 #pragma unroll
                 for (int k = 0; k < NC; ++k) y[k] = (int32_t)c.xd[k];
             }
         }
-        if (mine) {
+        if (mine && !(group && wave != 0)) {
             if (fired) {
                 const int64_t row = (int64_t)day * s.n_inst * s.R + set;
 #pragma unroll
@@ -2937,8 +2960,10 @@ struct Kernels {
     }
     static void *tile() { return (void *)&k_day_tile<Rules, false>; }
     static void *tile_slots() { return (void *)&k_day_tile<Rules, true>; }
-    static void *far() { return (void *)&k_day_far<Rules, false>; }
-    static void *far_slots() { return (void *)&k_day_far<Rules, true>; }
+    static void *far(bool slots, bool group) {
+        return slots ? (group ? (void *)&k_day_far<Rules, true, true> : (void *)&k_day_far<Rules, true, false>)
+                     : (group ? (void *)&k_day_far<Rules, false, true> : (void *)&k_day_far<Rules, false, false>);
+    }
     static void *events() { return (void *)&k_events<Rules::NC>; }
     static void *levels() { return (void *)&k_event_levels<Rules::NC>; }
     static void *persist() { return (void *)&k_persist<Rules>; }
@@ -2948,7 +2973,8 @@ struct Kernels {
 
 struct Table {
     void *(*day)(bool levels, bool own);
-    void *events, *persist, *levels, *tile, *slot_events, *tile_slots, *far, *far_slots;
+    void *events, *persist, *levels, *tile, *slot_events, *tile_slots;
+    void *(*far)(bool slots, bool group);
     size_t (*day_lds)(int U, int B, bool events);
     int day_threads;
 };
@@ -2957,7 +2983,7 @@ template <class Rules>
 Table table() {
     return {&Kernels<Rules>::day,     Kernels<Rules>::events(), Kernels<Rules>::persist(),
             Kernels<Rules>::levels(), Kernels<Rules>::tile(),   Kernels<Rules>::slot_events(),
-            Kernels<Rules>::tile_slots(), Kernels<Rules>::far(), Kernels<Rules>::far_slots(), &Kernels<Rules>::day_lds, Rules::kDayThreads};
+            Kernels<Rules>::tile_slots(), &Kernels<Rules>::far, &Kernels<Rules>::day_lds, Rules::kDayThreads};
 }
 
 Table pick(const Model &m) {
@@ -2974,7 +3000,7 @@ Table pick(const Model &m) {
 // lanes of the tile kernel, so a launch that fills the chip leaves them to it
 // up to kFarWide attempts; in a launch of less than kNarrow positions (times
 // columns) the tile kernel's longest chain is what the day waits for.
-static int launch_tiles(void *tile, void *far, const Model &m, DevState s, const DevEvents &ev, int32_t d, int prologue,
+static int launch_tiles(const Table &t, bool slots, const Model &m, DevState s, const DevEvents &ev, int32_t d, int prologue,
                         int ssa, int64_t n_cols, void *stream) {
     if (s.Np % kWaves != 0) return hipErrorInvalidValue;
     if (s.far_min == 0.0) s.far_min = s.Np * n_cols < kNarrow ? kFarNarrow : kFarWide;
@@ -2987,11 +3013,14 @@ static int launch_tiles(void *tile, void *far, const Model &m, DevState s, const
     const bool by_unit = units * n_cols <= wanted + wanted / 4 && units * n_cols >= wanted / 2;
     const int64_t blocks_x = by_unit ? units : std::min<int64_t>(s.Np / kWaves, wanted / n_cols);
     const unsigned nx = (unsigned)std::max<int64_t>(1, blocks_x);
-    const hipError_t e = hipLaunchKernel(tile, dim3(nx, (unsigned)n_cols), dim3(kBlock), args, 0, (hipStream_t)stream);
+    const hipError_t e = hipLaunchKernel(slots ? t.tile_slots : t.tile, dim3(nx, (unsigned)n_cols), dim3(kBlock), args, 0, (hipStream_t)stream);
     if (e != hipSuccess || !ssa) return (int)e;
     void *far_args[] = {&mm, &s, &ee, &dd};
-    const int64_t blocks = std::max<int64_t>(16, std::min<int64_t>(kFarBlocks, s.Np * n_cols / 4));
-    return (int)hipLaunchKernel(far, dim3((unsigned)blocks), dim3(kBlock), far_args, 0, (hipStream_t)stream);
+    // (from 8,192 positions on, and up to 128 lanes, of which a herd of long chains leaves half the workgroups)
+    const bool group = s.Np * n_cols >= kNarrow / 4 && n_cols <= 2;
+    const int threads = group ? t.day_threads : kBlock;
+    const int64_t blocks = std::max<int64_t>(16, std::min<int64_t>(kFarWaves, s.Np * n_cols) * 64 / threads);
+    return (int)hipLaunchKernel(t.far(slots, group), dim3((unsigned)blocks), dim3((unsigned)threads), far_args, 0, (hipStream_t)stream);
 }
 
 int launch_day(const Model &m, const DevState &s, const DevEvents &ev, int32_t d, int prologue, int ssa,
@@ -3006,7 +3035,7 @@ int launch_day(const Model &m, const DevState &s, const DevEvents &ev, int32_t d
     void *args[] = {&mm, &ss, &ee, &dd, &pro, &sa, &lv};
     if (layout == LAYOUT_TILE) {
         if (s.slots) return hipErrorInvalidValue;  // a slot handle's day runs through launch_slot_day
-        return launch_tiles(t.tile, t.far, m, s, ev, d, prologue, ssa, s.RL / 64, stream);
+        return launch_tiles(t, false, m, s, ev, d, prologue, ssa, s.RL / 64, stream);
     }
     if (s.tile_nodes < 4 || s.tile_nodes > kMaxUnit || s.L % s.tile_nodes != 0) return hipErrorInvalidValue;
     const unsigned grid = (unsigned)(s.L / s.tile_nodes);
@@ -3086,7 +3115,7 @@ int launch_slot_day(const Model &m, const DevState &s, const DevEvents &ev, int3
     if (s.L == 0 || n_cols <= 0) return hipSuccess;
     if (!s.slots || n_cols > s.RL / 64) return hipErrorInvalidValue;
     const Table t = pick(m);
-    return launch_tiles(t.tile_slots, t.far_slots, m, s, ev, step, 1, 1, n_cols, stream);
+    return launch_tiles(t, true, m, s, ev, step, 1, 1, n_cols, stream);
 }
 
 int launch_slot_events(const Model &m, const DevState &s, const DevEvents &ev, int32_t step, int32_t k,

@@ -158,7 +158,7 @@ constexpr int64_t kTileBlocks = 256, kTileBlocksWide = 768;
 // replicates, a day with 24 / 48 / 96: 63 / 82 / 112 us; 37,000 x 256 with 24 / 48 / 96 / 192: 783 / 634 /
 // 574 / 609).
 constexpr double kFarNarrow = 24.0, kFarWide = 96.0;
-constexpr int64_t kFarBlocks = 1024;
+constexpr int64_t kFarWaves = 4096;
 constexpr uint32_t kFewChains = 4;     // default: at most this many live chains walked one after another
 constexpr double kGroupMinAttempts = 256.0;  // default: a workgroup walks a chain expecting this many attempts
 // One lane per node: positions of one workgroup, a power of two up to kMaxUnit

@@ -127,3 +127,56 @@ def test_replicate_tiles_with_more_long_chains_than_listed(kw):
     p.record_days = np.array([0, 3], np.int32)
     say(f"[walks] long chains in tiles {kw}")
     check(p, chunks=[1, 2, 1], **kw)
+
+
+@pytest.mark.parametrize("model,reps,large", [("flip", 2, 3), ("flip3", 64, 2), ("flip3", 64, 3), ("flip", 100, 2),
+                                              ("4", 3, 2), ("8", 3, 2)])
+def test_longest_chains_of_replicate_tiles(model, reps, large):
+    # from 8,192 positions on, chains of 2,048 attempts or more are walked by a
+    # workgroup each while at most 128 of them are listed: 6, 128 and 9 chains,
+    # and 192 and 200 of which each gets a wavefront
+    if model in "48":
+        p = chain_model(int(model), 8300, 2, model == "8", 96)
+        p.u0[:large] = 0
+        p.u0[:large, 2] = [12000, 9000][:large]
+        p.v0[:] = 0.5
+    else:
+        p = (synth.flip_model if model == "flip" else synth.flip_classes)(n_nodes=8300, S0=1, I0=0, n_days=2)
+        p.u0[[100, 4000, 8299][:large], 0] = [3000, 2600, 5000][:large]
+    p = p.with_replicates(reps, replicate_id=np.arange(reps, dtype=np.uint32) + 5)
+    p.record_days = np.array([1], np.int32)
+    say(f"[walks] longest chains of tiles {model} reps={reps}, {large} herds")
+    g = check(p, chunks=[1, 1])
+    assert (g["max_transitions"] > 2048).all()
+
+
+def test_longest_chains_of_slots():
+    # the same in the slots of two requests, the second a step behind
+    net = synth.flip_classes(n_nodes=8300, S0=1, I0=0, n_days=3)
+    net.u0[[100, 8299], 0] = [3000, 2600]
+    out = {}
+    H = P.SlotHandle(net, 2, slot_lanes=32)
+    try:
+        for step in range(5):
+            if step < 2:
+                n = 20 - 13 * step
+                ids = np.arange(n, dtype=np.uint32) + 40 * step
+                H.start(step, 3 - step, np.ones((n, 6)), np.ones(n), np.full((n, 4), 0.1), ids)
+            for slot in H.step():
+                n = 20 - 13 * slot
+                rec = [np.zeros((3 - slot, n), np.int32), np.zeros((3 - slot, n), np.int64), np.zeros((3 - slot, n, 6), np.int64)]
+                H.fetch(slot, *rec)
+                while not H.query(slot):
+                    pass
+                out[slot] = rec, H.state(slot, n)
+    finally:
+        H.close()
+    assert sorted(out) == [0, 1]
+    for slot, (rec, (u, v)) in out.items():
+        n = 20 - 13 * slot
+        p = net.truncated(3 - slot).with_replicates(n, coef=np.ones((n, 6)), alpha=np.ones(n), beta=np.full((n, 4), 0.1),
+                                                    replicate_id=np.arange(n, dtype=np.uint32) + 40 * slot)
+        o = O.run(p, threads=8)
+        for a, k in zip(rec, ("prevalence", "transitions", "totals")):
+            assert np.array_equal(a, o[k]), (slot, k)
+        assert np.array_equal(u, o["u"]) and np.array_equal(v.view(np.int64), o["v"].view(np.int64))
