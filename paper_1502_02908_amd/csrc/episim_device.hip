@@ -1204,17 +1204,9 @@ __device__ __forceinline__ void flush_tile(const Model &m, const DevState &s, co
 // replacement (Sec. 3.2): draw q picks the individual at a uniform position
 // in [0, remaining) of the selected compartments in ascending order, from the
 // Philox block (q / 2, g, d, 1). Removes them from x and counts them in take.
-// pre, when given, holds the first kPreDraws draws (computed ahead in parallel);
-// an event that needs no more than those (every movement of up to five
-// animals) has all its picks multiplied out at once, since draw q picks among
-// tot - q individuals whatever the earlier picks were, and only the walk over
-// the compartments stays serial.
-constexpr int kPreDraws = 6;
-
 template <int NC>
 __device__ __forceinline__ void draw_individuals(int32_t *x, int32_t *take, uint32_t mask, int32_t n, long long tot,
-                                                 uint32_t g, int32_t d, uint32_t key0, uint32_t key1,
-                                                 const uint64_t *pre = nullptr) {
+                                                 uint32_t g, int32_t d, uint32_t key0, uint32_t key1) {
     long long cum[NC];  // running sums of the selected compartments, ascending
     long long run = 0;
 #pragma unroll
@@ -1223,36 +1215,10 @@ __device__ __forceinline__ void draw_individuals(int32_t *x, int32_t *take, uint
         run += ((mask >> c) & 1u) ? x[c] : 0;
         cum[c] = run;
     }
-    if (pre && n <= kPreDraws && tot <= 0x7fffffffLL) {
-        // the running sums and picks fit 32 bits (the same comparisons)
-        uint32_t pick[kPreDraws], cum32[NC];
-#pragma unroll
-        for (int c = 0; c < NC; ++c) cum32[c] = (uint32_t)cum[c];
-#pragma unroll
-        for (int q = 0; q < kPreDraws; ++q)
-            pick[q] = q < n ? (uint32_t)__umul64hi(pre[q], (uint64_t)(tot - q)) : 0u;
-#pragma unroll
-        for (int q = 0; q < kPreDraws; ++q) {
-            if (q >= n) break;
-            int chosen = 0;
-#pragma unroll
-            for (int c = 0; c < NC; ++c) chosen += cum32[c] <= pick[q] ? 1 : 0;
-#pragma unroll
-            for (int c = 0; c < NC; ++c) {
-                const int hit = c == chosen ? 1 : 0;
-                x[c] -= hit;
-                take[c] += hit;
-                cum32[c] -= c >= chosen ? 1u : 0u;
-            }
-        }
-        return;
-    }
     Word4 o{0, 0, 0, 0};
     for (int32_t q = 0; q < n; ++q) {
         uint64_t bits;
-        if (pre && q < kPreDraws) {
-            bits = pre[q];
-        } else if ((q & 1) == 0) {
+        if ((q & 1) == 0) {
             o = philox4x32_10(Word4{(uint32_t)q >> 1, g, (uint32_t)d, 1u}, key0, key1);
             bits = ((uint64_t)o.b << 32) | o.a;
         } else {
@@ -1273,6 +1239,37 @@ __device__ __forceinline__ void draw_individuals(int32_t *x, int32_t *take, uint
             cum[c] -= c >= chosen ? 1 : 0;
         }
         tot -= 1;
+    }
+}
+
+// draw_individuals for an event of at most N draws that were computed ahead
+// (pre), tot below 2^31: draw q picks among tot - q individuals whatever the
+// earlier picks were, and the running sums and picks fit 32 bits (the same
+// comparisons).
+template <int NC, int N>
+__device__ __forceinline__ void draw_ahead(int32_t *x, int32_t *take, uint32_t mask, int32_t n, uint32_t tot,
+                                           const uint64_t (&pre)[N]) {
+    uint32_t cum[NC], run = 0;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        take[c] = 0;
+        run += ((mask >> c) & 1u) ? (uint32_t)x[c] : 0u;
+        cum[c] = run;
+    }
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+        const uint32_t pick = (uint32_t)__umul64hi(pre[q], (uint64_t)tot - q);
+        int chosen = 0;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) chosen += cum[c] <= pick ? 1 : 0;
+        if (q >= n) chosen = NC;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const int hit = c == chosen ? 1 : 0;
+            x[c] -= hit;
+            take[c] += hit;
+            cum[c] -= c >= chosen ? 1u : 0u;
+        }
     }
 }
 
@@ -1520,7 +1517,14 @@ __device__ __forceinline__ void event_lds(uint32_t meta, uint32_t smap, int32_t 
         return;
     }
     int32_t take[NC];
-    draw_individuals<NC>(x, take, mask, n, tot, g, d, key0, key1);
+    // Selections of three compartments or more take the draws computed ahead in
+    // the general models (3,000 herds of three compartments, all selected, a day
+    // 21.2 -> 18.9 us). The farm model's events select one; there the code alone
+    // costs more than it saves (37,000 herds, a day 21.8 -> 22.7 us).
+    if (!exact_size(NC) && ahead && n <= N && tot <= 0x7fffffffLL)
+        draw_ahead<NC>(x, take, mask, n, (uint32_t)tot, pre);
+    else
+        draw_individuals<NC>(x, take, mask, n, tot, g, d, key0, key1);
 #pragma unroll
     for (int c = 0; c < NC; ++c)
         if ((mask >> c) & 1u) xs[c] = x[c];
@@ -1556,7 +1560,8 @@ struct PrivEv {
     uint32_t meta, smap;
     int32_t n, g, gm, node;
 };
-constexpr int kPrivDraws = 2;
+constexpr int kPrivDraws = 2;  // of a private event
+constexpr int kPreDraws = 6;   // of a level event
 
 // One private task (a run of one node's single-node events, i the first)
 // applied to the counts in LDS (position loc's compartment c at xs[loc * NC + c]).
@@ -2020,7 +2025,8 @@ __global__ __launch_bounds__(OWN ? kMaxUnit : Rules::kDayThreads) void k_day(Mod
             __syncthreads();
         }
     } else if (levels && t < U && sh.touch[t]) {
-        // (the closing launch has not handed its counts over)
+        // (the counts that stand there: without this copy the kernel is laid
+        // out otherwise, and every day takes 1 % longer)
 #pragma unroll
         for (int c = 0; c < NC; ++c) sh.x[t * NC + c] = x[c];
     }

@@ -180,3 +180,17 @@ def test_longest_chains_of_slots():
         for a, k in zip(rec, ("prevalence", "transitions", "totals")):
             assert np.array_equal(a, o[k]), (slot, k)
         assert np.array_equal(u, o["u"]) and np.array_equal(v.view(np.int64), o["v"].view(np.int64))
+
+
+@pytest.mark.parametrize("n_comp,reps", [(3, 1), (8, 1), (4, 3)])
+def test_draws_computed_ahead(n_comp, reps):
+    # movements and deaths of 1 to 9 animals from three compartments or more,
+    # around the six (two in a private task) draws computed ahead
+    p = chain_model(n_comp, 400, 6, False, 98)
+    p.u0[:, :] += 60
+    n = np.array([1, 2, 3, 5, 6, 7, 9], np.int32)
+    p.ev_n = np.where(p.ev_kind == 1, p.ev_n, n[np.arange(p.n_events) % 7]).astype(np.int32)
+    p = p.with_replicates(reps)
+    p.record_days = np.array([0, 5], np.int32)
+    say(f"[walks] draws ahead n_comp={n_comp} reps={reps}: {p.n_events} events")
+    check(p, chunks=[1, 3, 2])
