@@ -133,7 +133,7 @@ typedef struct sim_device_opts {
     void *workspace;
     size_t workspace_bytes;
     int32_t events_mode;   /* SIM_EVENTS_* */
-    int32_t block;         /* threads per workgroup for node kernels: 0 or 256 (the kernels are built for 256) */
+    int32_t block;         /* 0 or 256; chooses nothing (each kernel has its own workgroup size) */
     int32_t launch;        /* SIM_LAUNCH_*: how days are issued */
     int32_t group_herds;   /* with one lane per node and per-day launches, the largest herds per instance of
                               at least 8192 nodes that get a workgroup to themselves: 0 = default (4),
@@ -148,9 +148,9 @@ typedef struct sim_device_opts {
     int32_t heavy_herds;   /* replicate tiles with per-day launches: 0 or more (at most 256) = the chains that
                               expect many attempts get a wavefront each, in a launch of their own; negative =
                               every chain is walked with its tile */
-    int32_t few_chains;    /* at most this many live chains of a wavefront, one of them still expecting many
-                              attempts, are walked one after another by the whole wavefront: 0 = default (4),
-                              negative = never, at most 64 */
+    int32_t few_chains;    /* replicate tiles and the persistent launch: at most this many live chains of a
+                              wavefront, one of them still expecting many attempts, are walked one after
+                              another by the whole wavefront: 0 = default (4), negative = never, at most 64 */
     int32_t group_min_attempts; /* one lane per node with per-day launches: a chain that expects this many
                               attempts in the day may be walked by its whole workgroup: 0 = default (256) */
     int32_t slot_lanes;    /* slot handles: replicate lanes per slot, 8, 16, 32 or 64 (0 = 64); n_slots times

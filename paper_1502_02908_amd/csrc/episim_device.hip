@@ -3020,7 +3020,7 @@ static int launch_tiles(const Table &t, bool slots, const Model &m, DevState s, 
     const int64_t blocks_x = by_unit ? units : std::min<int64_t>(s.Np / kWaves, wanted / n_cols);
     const unsigned nx = (unsigned)std::max<int64_t>(1, blocks_x);
     const hipError_t e = hipLaunchKernel(slots ? t.tile_slots : t.tile, dim3(nx, (unsigned)n_cols), dim3(kBlock), args, 0, (hipStream_t)stream);
-    if (e != hipSuccess || !ssa) return (int)e;
+    if (e != hipSuccess || !ssa || std::isnan(s.far_min)) return (int)e;
     void *far_args[] = {&mm, &s, &ee, &dd};
     // (from 8,192 positions on, and up to 128 lanes, of which a herd of long chains leaves half the workgroups)
     const bool group = s.Np * n_cols >= kNarrow / 4 && n_cols <= 2;

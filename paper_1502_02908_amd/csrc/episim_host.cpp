@@ -1364,7 +1364,7 @@ int create(const sim_problem *const *ps, int32_t n, const sim_device_opts *o, si
     s.far_list = at<int32_t>(h->ws, l.far_list);
     s.far_n = at<int32_t>(h->ws, l.far_n);
     s.far_cap = (int32_t)pk.far_cap;
-    s.far_min = opts.heavy_herds < 0 ? 1e300 : 0.0;
+    s.far_min = opts.heavy_herds < 0 ? std::nan("") : 0.0;
     s.n_regions = p->n_regions;
     s.pos_region = at<int32_t>(h->ws, l.pos_region);
     s.regional = at<int64_t>(h->ws, l.regional);

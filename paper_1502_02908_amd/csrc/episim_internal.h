@@ -88,17 +88,17 @@ struct DevState {
     // step's launches cover only these (grid y = their count)
     const int32_t *run_slots;   // [RL / slot_lanes]
     const int32_t *run_cols;    // [RL / 64]
-    int32_t tile_nodes;         // positions of one unit: a replicate tile (a power of two, 4 .. 512), or
-                                // a workgroup's nodes with one lane per node (4 .. kMaxUnit)
+    int32_t tile_nodes;         // positions of one unit: a replicate tile's (a multiple of 4 up to 512), or a
+                                // workgroup's with one lane per node (a power of two, 4 .. kMaxUnit)
     int32_t slot_lanes;         // slot handles: replicate lanes of one slot (8, 16, 32 or 64)
-    uint32_t few_chains;        // at most this many live chains of a wavefront are walked one after another
+    uint32_t few_chains;        // tiles, persistent launch: at most this many live chains of a wavefront are walked one after another
     double group_min_attempts;  // one lane per node: a workgroup walks a chain that expects this many attempts
     // replicate tiles: the lanes whose chains expect far_min attempts or more
     // today, by length class (a chain that finds its list full is walked in place)
     int32_t *far_list;          // [kFarLists][far_cap]
     int32_t *far_n;             // [2][kFarLists], by parity of the day (of the step in a slot handle)
     int32_t far_cap;
-    double far_min;             // 0: chosen by the launcher
+    double far_min;             // 0: chosen by the launcher; NaN: no chain is a far one
     // daily records
     int32_t *prevalence;        // [D][sets]
     int64_t *transitions;       // [D][sets]

@@ -14,8 +14,6 @@ the schedule of the workload at hand (candidates_for):
   launch             per-day kernels, or one cooperative kernel for the whole run;
   small_level        up to which size event levels run several per launch in
                      one workgroup (0: default 512);
-  few_chains         how many live chains of a wavefront may be walked one after
-                     another by the whole wavefront (0: default 4, negative: never);
 one lane per node (one trajectory per instance):
   group_herds        how many of the largest herds of a large instance get a
                      workgroup to themselves (0: default 4, negative: none);
@@ -27,7 +25,9 @@ replicate tiles (several replicates per instance):
                      size and the replicates);
   heavy_herds        whether chains of many attempts get a wavefront each in a
                      launch of their own (0 or more) or stay with their tile
-                     (negative).
+                     (negative);
+  few_chains         how many live chains of a wavefront may be walked one after
+                     another by the whole wavefront (0: default 4, negative: never).
 """
 from __future__ import annotations
 
@@ -46,8 +46,6 @@ LANE_CANDIDATES = (
     dict(group_min_attempts=16384),
     dict(small_level=128),
     dict(small_level=4096),
-    dict(few_chains=1),
-    dict(few_chains=8),
     dict(launch=LAUNCH_PERSISTENT),
     dict(tile_nodes=4),
     dict(tile_nodes=16),
@@ -57,8 +55,6 @@ TILE_CANDIDATES = (
     dict(tile_nodes=64),
     dict(tile_nodes=256),
     dict(heavy_herds=-1),
-    dict(heavy_herds=32),
-    dict(heavy_herds=128),
     dict(few_chains=1),
     dict(few_chains=-1),
     dict(small_level=4096),

@@ -73,3 +73,14 @@ def test_many_small_networks_with_replicates_are_accepted():
     # 20 herds the lanes would pass 2^31
     p = dataclasses.replace(synth.flip_model(n_nodes=20, S0=1, I0=1, n_days=1)).with_replicates(256)
     assert packed_bytes([p] * 16500) > 0
+
+
+def test_tuner_times_no_schedule_twice():
+    # heavy_herds has a sign only, and few_chains is read by replicate tiles
+    # (and the persistent launch) only
+    from paper_1502_02908_amd.tune import LANE_CANDIDATES, TILE_CANDIDATES
+    lanes = [{k: v for k, v in c.items() if k not in ("few_chains", "heavy_herds")} for c in LANE_CANDIDATES]
+    tiles = [{k: -1 if k == "heavy_herds" else v for k, v in c.items() if not (k == "heavy_herds" and v >= 0)}
+             for c in TILE_CANDIDATES]
+    for candidates in (lanes, tiles):
+        assert all(c not in candidates[:j] for j, c in enumerate(candidates))
