@@ -194,3 +194,67 @@ def test_draws_computed_ahead(n_comp, reps):
     p.record_days = np.array([0, 5], np.int32)
     say(f"[walks] draws ahead n_comp={n_comp} reps={reps}: {p.n_events} events")
     check(p, chunks=[1, 3, 2])
+
+
+@pytest.mark.parametrize("n_nodes,tile,density,pre", [(512, 512, 2.1, 0), (512, 512, 2.6, 1), (77000, 256, 2.3, 0)])
+def test_private_events_past_the_workgroup_size(n_nodes, tile, density, pre):
+    # units of 512 and 256 herds with up to about 1,100, 1,300 and 600 private
+    # events a day: past the 1,024 threads of a workgroup (512 in the third,
+    # of 301 units) the tasks run on global memory, below them in LDS
+    p = synth.sise3_network(n_nodes=n_nodes, n_days=6 if n_nodes > 1000 else 12, seed=99, age_days=(1, 3), median=400.0,
+                            e1_per_node_day=density)
+    p.phi_pre_events = pre
+    p.record_days = np.array([0, p.n_days - 1], np.int32)
+    threads = 512 if n_nodes > 1000 else 1024
+    move = p.ev_dest >= 0
+    a_day = np.bincount(p.ev_day[~move], minlength=p.n_days) / (n_nodes / tile)
+    say(f"[walks] private events {n_nodes} herds: {a_day.min():.0f} to {a_day.max():.0f} a unit and day")
+    assert a_day.min() < threads < a_day.max()
+    check(p, tile_nodes=tile)
+
+
+@pytest.mark.parametrize("n_nodes,classes", [(16, 1), (4800, 3), (9600, 1)])
+@pytest.mark.parametrize("large", [3, 4])
+def test_several_workgroup_chains_in_a_unit(n_nodes, classes, large):
+    # units of 16 herds, three of them with 1,100 to 6,000 attempts a day: the
+    # workgroup walks one after another (of 1,024, 512 and 256 threads); of
+    # four, each gets a wavefront
+    p = (synth.flip_model if classes == 1 else synth.flip_classes)(n_nodes=n_nodes, S0=1, I0=0, n_days=2)
+    big = np.random.default_rng(3).integers(1100, 6000, large * (n_nodes // 16))
+    p.u0[np.random.default_rng(4).permutation(n_nodes)[:len(big)], 0] = big
+    p.record_days = np.array([1], np.int32)
+    say(f"[walks] {large} long chains in each of {n_nodes // 16} units")
+    check(p, tile_nodes=16, group_min_attempts=64, group_herds=-1)
+
+
+@pytest.mark.parametrize("least", [8, 4096])
+def test_threshold_of_the_workgroup_walk(least):
+    p = synth.sise3_network(n_nodes=9000, n_days=30, seed=100, u=10.0, age_days=(10, 20))
+    p.record_days = np.array([29], np.int32)
+    say(f"[walks] group_min_attempts={least}")
+    check(p, group_min_attempts=least)
+
+
+@pytest.mark.parametrize("n_nodes,reps", [(1, 1), (1, 2), (8200, 2)])
+def test_too_many_transitions_in_a_day(n_nodes, reps):
+    # a herd whose chain passes 2^24 transitions, walked by a workgroup of the
+    # day kernel, a wavefront and a workgroup of the long chains' launch: the
+    # run reports it, and the handle goes on from another state
+    p = synth.flip_model(n_nodes=n_nodes, S0=3, I0=3, n_days=2).with_replicates(reps)
+    u = np.broadcast_to(p.u0, (reps,) + p.u0.shape).copy()
+    v = np.zeros((reps, n_nodes))
+    over = u.copy()
+    over[reps - 1, 0] = 12_000_000
+    say(f"[walks] past the limit of transitions n_nodes={n_nodes} reps={reps}")
+    with P.Simulator(p) as sim:
+        sim.set_state(over, v, 0)
+        sim.run(2)
+        with pytest.raises(P.SimError) as e:
+            sim.sync()
+        assert e.value.code == P.SIM_ELIMIT and f"replicate {reps - 1}" in str(e.value)
+        sim.set_state(u, v, 0)
+        sim.run(2)
+        g = sim.trajectory()
+    o = O.run(p, threads=8)
+    for k in ("transitions", "totals", "prevalence", "max_transitions"):
+        assert np.array_equal(g[k], o[k]), k
