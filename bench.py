@@ -120,16 +120,16 @@ VALU_PEAK_OPS = 256 * 4 * 16 * CLOCK_GHZ * 1e9
 OPS_PER_ATTEMPT = 98 + 10 + 50 + 10 + 2 + 1 + 12 + 2 + 11
 
 
-def chain_probe(P, synth, torch, half=1000, days=40, n_nodes=1, classes=1):
+def chain_probe(P, synth, torch, half=1000, days=40, n_nodes=1, classes=1, equal=1, tile_nodes=0):
     """Time per attempt of one long chain (the serial critical path of a
-    plain step): the synthetic model of Sec. 4.2 with one node of S = I =
-    half (lambda = 2 half per day, no events) among n_nodes - 1 empty ones,
-    its day kernel's duration less that of the same network with no
-    animals, over the attempts of a day (transitions + 1). classes = 3 runs
-    the same dynamics on the SISe3 compartments (S_j = I_j = half / 3 in each
-    class), so the chain walks the six-compartment model as the farm
-    networks' herds do. A workgroup walks the chain, as it does the farm
-    networks' largest herds."""
+    plain step): the synthetic model of Sec. 4.2 with `equal` nodes of S = I =
+    half (lambda = 2 half per day, no events) among n_nodes - equal empty
+    ones, its day kernel's duration less that of the same network with no
+    animals, over a node's attempts of a day (transitions + 1). classes = 3
+    runs the same dynamics on the SISe3 compartments (S_j = I_j = half / 3 in
+    each class), so the chain walks the six-compartment model as the farm
+    networks' herds do. A workgroup walks one such chain, as it does the farm
+    networks' largest herds; several in one unit get a wavefront each."""
     import numpy as np
 
     def day_us(S0):
@@ -140,8 +140,8 @@ def chain_probe(P, synth, torch, half=1000, days=40, n_nodes=1, classes=1):
             p = synth.flip_model(n_nodes=n_nodes, S0=0, I0=0, n_days=days)
             row = [S0, S0]
         p.u0 = np.ascontiguousarray(p.u0)
-        p.u0[0] = row
-        with P.Simulator(p) as sim:
+        p.u0[:equal] = row
+        with P.Simulator(p, tile_nodes=tile_nodes) as sim:
             sim.run(0)
             sim.sync()
             sim.set_state(p.u0[None], p.v0[None], 0)
@@ -151,11 +151,11 @@ def chain_probe(P, synth, torch, half=1000, days=40, n_nodes=1, classes=1):
             kt = sim.kernel_times(0)
             trans = int(sim.trajectory()["transitions"].sum())
         ms, n = kt["day"]
-        return ms * 1e3 / n, trans / days
+        return ms * 1e3 / n, trans / days / equal
     t_big, per_day = day_us(half)
     t_empty, _ = day_us(0)
     us = (t_big - t_empty) / (per_day + 1.0)
-    where = "one node" if n_nodes == 1 else f"one node of {n_nodes}"
+    where = "one node" if n_nodes == 1 else f"one node of {n_nodes}" if equal == 1 else f"{equal} equal nodes in one unit"
     model = ("the synthetic S<->I model" if classes == 1 else
              "the synthetic S<->I dynamics on the six SISe3 compartments")
     size = f"S = I = {half}" if classes == 1 else f"S_j = I_j = {half // 3}"
@@ -600,10 +600,11 @@ def main():
                         for k, v in kt.items() if v[1]}
     sim.close()
 
-    # the serial critical path: each day's longest SSA chain at the
-    # per-attempt time of a long chain walked as the day kernel walks the
-    # largest herd (from 8192 nodes with one lane per node: its own workgroup,
-    # the workgroup walk for chains of 128 expected attempts or more)
+    # the serial critical path: each day's longest SSA chain at the time of a
+    # chain walked as the day kernel walks the largest herd (from 8192 nodes
+    # with one lane per node it has a unit to itself, whose workgroup walks it
+    # from 256 expected attempts on): a first round, whose code the day fetches
+    # anew, and a rate per attempt past it, from chains of two lengths
     hub_layout = p.n_nodes >= 8192 and p.n_rep == 1 and not best.get("tile_nodes")
     # the probe walks the workload's own rules: three S<->I classes on the
     # six-compartment networks, one on the synthetic model (its launches are
@@ -614,12 +615,20 @@ def main():
         if hub_layout:
             short = chain_probe(P, synth, torch, half=1000, n_nodes=8192, classes=classes)
             long_ = chain_probe(P, synth, torch, half=10000, days=20, n_nodes=8192, classes=classes)
-            per_day_us = np.where(most + 1 >= 10000, long_["us_per_attempt"], short["us_per_attempt"]) * (most + 1)
+            n = [q["attempts_per_day"] for q in (short, long_)]
+            t = [q["day_kernel_us"] - q["empty_day_kernel_us"] for q in (short, long_)]
+            rate = (t[1] - t[0]) / (n[1] - n[0])
+            per_day_us = max(0.0, t[0] - rate * n[0]) + rate * (most + 1)
             probes = [short, long_]
+            rule = (f"{max(0.0, t[0] - rate * n[0]):.1f} us for the day's longest chain and {rate * 1e3:.2f} ns an "
+                    "attempt, from the two probes")
         else:
-            one = chain_probe(P, synth, torch, classes=classes)
+            # in the synthetic model every node of a unit has such a chain
+            unit = (best.get("tile_nodes") or 4) if args.workload == "synthetic-1k" else 1
+            one = chain_probe(P, synth, torch, classes=classes, n_nodes=unit, equal=unit, tile_nodes=best.get("tile_nodes") or 0)
             per_day_us = one["us_per_attempt"] * (most + 1)
             probes = [one]
+            rule = "the probe's time per attempt"
         chain_ms = float(per_day_us.sum()) / 1e3
         step_ms = total / args.steps * 1e3
         critical = dict(longest_chain_attempts_per_step=int((most + 1).sum()),
@@ -629,7 +638,7 @@ def main():
                         cycles_per_attempt=[round(q["cycles_per_attempt"], 1) for q in probes],
                         chain_ms_per_step=round(chain_ms, 3), step_ms=round(step_ms, 3),
                         frac=round(chain_ms / step_ms, 4), probe=[q["probe"] for q in probes],
-                        rule="longest chains of 10,000 attempts or more at the second probe's rate" if hub_layout else "")
+                        rule=rule)
     roofline["binding"] = ("serial SSA chain of the day's largest herd (critical_path.frac of the step), "
                            "not HBM")
     tag = {"sise3-37k": "sq_37k", "sise3-1m": "sq_1m", "sise3-37k-u10": "sq_u10",
