@@ -1,12 +1,17 @@
 // gfx950 kernels of the per-day step (Bauer, Engblom & Widgren,
 // arXiv:1502.02908, Sec. 3.1-3.3 and Algorithm 1):
-//   k_day      for every lane (node, replicate): the continuous-state update
-//              closing the previous day (eq:numstep5 with eq:siminfpressure)
-//              and that day's record, then the direct-method SSA over the
-//              window [d, d+1) with phi frozen (eq:numstep3, eq:sampling,
-//              eq:sampling2);
-//   k_events   one conflict-free level of day d's external events
-//              (eq:numstep4, Sec. 3.2): a thread per (event, replicate);
+//   k_day      one replicate: closes the previous day of every node (the level
+//              events of its day where few nodes take part, the continuous-state
+//              update eq:numstep5 with eq:siminfpressure, the day's record), then
+//              the direct-method SSA over the window [d, d+1) with phi frozen
+//              (eq:numstep3, eq:sampling, eq:sampling2) and the events of single
+//              nodes that come first in the day;
+//   k_day_tile, k_day_far
+//              the same for many replicates, 64 a column, and for slots of
+//              requests; the longest chains in a launch of their own;
+//   k_events, k_event_levels, k_slot_events
+//              conflict-free levels of day d's external events (eq:numstep4,
+//              Sec. 3.2): a thread per (event, replicate);
 //   k_persist  the same phases for a run of days in one cooperative launch,
 //              with grid barriers between phases.
 // All binary64 arithmetic is written in a fixed order with contraction off,
@@ -1590,11 +1595,12 @@ __device__ __forceinline__ void private_task_lds(const PrivEv *pe, int i, int n_
 // walked side by side by segments of a wavefront (walk_queue); at last the
 // unit's private tasks run on the counts, and each touched node is stored
 // once. What binds a day is the latency of the walks' dependent arithmetic, so
-// the chains of a few nodes are spread over many wavefronts: sixteen a unit,
-// and units small enough for every compute unit to have one (lane_unit on the
-// host); with more units than that, fewer. With four wavefronts a unit of 256 nodes, each walking its 64 nodes'
-// chains attempt by attempt in their own lanes, a day's SSA took about 18 us
-// whatever its chains' lengths.
+// the chains of a few nodes are spread over many wavefronts: sixteen a unit
+// (eight for large general models), and units small enough for every compute
+// unit to have one (lane_unit on the host); with more units than that, fewer.
+// With four wavefronts a unit of 256 nodes, each walking its 64 nodes' chains
+// attempt by attempt in their own lanes, a day's SSA took about 18 us whatever
+// its chains' lengths.
 // The longest chains: those of group_min_attempts and more, in classes of a
 // factor of 4, the highest classes that hold one chain together (three from
 // class kFarClass on). A workgroup walks a chain of 2,000 attempts in about

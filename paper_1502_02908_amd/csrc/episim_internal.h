@@ -142,10 +142,12 @@ struct DevEvents {
     const int32_t *lvl_ptr;     // [D+1]: levels of day d are lvl_ptr[d] .. lvl_ptr[d+1]-1
 };
 
-// Layouts of the day phase: one lane per node with workgroup sums (R == 1),
-// or tiles of kTileNodes nodes x 64 replicate lanes per workgroup (R > 1,
-// lane stride RL a multiple of 64). A private task (a level-1 run of one node's
-// single-node events) runs in its node's unit right after the SSA.
+// Layouts of the day phase: one lane per node, a workgroup a unit of positions
+// (R == 1), or replicate tiles of positions x 64 replicate lanes (R > 1, lane
+// stride RL a multiple of 64). A private task (a level-1 run of one node's
+// single-node events) runs right after the SSA: in its node's unit with one
+// lane per node and in the persistent kernel, in a launch over the day's
+// private tasks in tiles.
 constexpr int kTileNodes = 128;       // positions of a replicate tile of the persistent kernel by default
 constexpr int kFarLists = 3;
 // Workgroups of a tile launch: three of four wavefronts fit a compute unit, so one round of 768 fills
