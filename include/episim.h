@@ -143,7 +143,7 @@ typedef struct sim_device_opts {
     int32_t tile_nodes;    /* replicate tiles (R > 1): node positions per unit of 64 replicate lanes: 0 = chosen by
                               the network's size and the replicates, else a power of two in [4, 512]. With one
                               replicate (R = 1) and per-day launches, the nodes of one workgroup: 0 = chosen by
-                              the network's size (4 to 512), else a power of two in [4, 512]; the persistent
+                              the network's size (4 to 1024), else a power of two in [4, 512]; the persistent
                               launch runs one replicate in tiles if it is nonzero */
     int32_t heavy_herds;   /* replicate tiles with per-day launches: 0 or more (at most 256) = the chains that
                               expect many attempts get a wavefront each, in a launch of their own; negative =

@@ -1587,7 +1587,7 @@ __device__ __forceinline__ void private_task_lds(const PrivEv *pe, int i, int n_
 }
 
 // One lane per node: a workgroup runs one unit of s.tile_nodes positions (4 to
-// 512), thread t < tile_nodes owning position t. The counts live in LDS for
+// 1024), thread t < tile_nodes owning position t. The counts live in LDS for
 // the day: the owners close the previous day and list their node's chain, as
 // long if it expects kWaveChain attempts (lambda) or more; then the whole
 // workgroup walks the longest chains one after another (walk_group), its
@@ -1708,14 +1708,14 @@ __device__ __forceinline__ void event_levels_lds(const DevState &s, const DevEve
 // a few attempts waste them. A wavefront with kOwnFirst short chains or more
 // then walks them where they are listed, each in its owner's lane, until
 // kOwnRest are left; those are listed and start again in a segment. (A day of
-// 1.5 million herds, all infected: SISe3 536 -> 210 us, SIS 376 -> 170; of
-// 100,000 herds with four times the rates 87 -> 67. Without the owners' walk
-// the kernel takes 10 registers less, 0.8 us of 22 a day on 37,000 herds with
-// a tenth infected.)
+// 1.5 million herds, all infected: SISe3 536 -> 232 us, SIS 376 -> 177; of
+// 100,000 herds with four times the rates 86 -> 72. The code alone costs 0.8 us
+// of 22 a day on 37,000 herds with a tenth infected, where a quarter of the
+// wavefronts own herds.)
 constexpr int kOwnFirst = 24, kOwnRest = 8;
 
 template <class Rules, bool LEVELS, bool OWN>
-__global__ __launch_bounds__(OWN ? kMaxUnit : Rules::kDayThreads) void k_day(Model m, DevState s, DevEvents ev, int32_t d, int32_t prologue,
+__global__ __launch_bounds__(Rules::kDayThreads) void k_day(Model m, DevState s, DevEvents ev, int32_t d, int32_t prologue,
                                                    int32_t ssa, EventDayArgs a) {
     constexpr int NC = Rules::NC, NT = Rules::NT;
     extern __shared__ __align__(16) char day_lds[];
@@ -3062,8 +3062,8 @@ int launch_day(const Model &m, const DevState &s, const DevEvents &ev, int32_t d
     if (lv.ne > kDayEventCap || lv.ns > kDaySlotCap || lv.nl > kDayLevelCap) return hipErrorInvalidValue;
     const bool staged = ev.unit_stage_off != nullptr;
     const size_t lds = t.day_lds(s.tile_nodes, block, staged);
-    // half the wavefronts or more own herds, and there are several workgroups to a compute unit
-    const bool own = block <= kMaxUnit && 2 * s.tile_nodes >= block;
+    // half the wavefronts or more own herds
+    const bool own = 2 * s.tile_nodes >= block;
     return (int)hipLaunchKernel(t.day(staged, own), dim3(grid), dim3((unsigned)block), args, lds, (hipStream_t)stream);
 }
 

@@ -407,15 +407,17 @@ struct UnitGroups {
 };
 
 // One lane per node: positions of a unit (a workgroup of the day kernel) unless
-// tile_nodes names them: the fewest, as a power of two from 4 to 256, that leave
-// at most one unit per compute unit, so that a day's chains spread over as many
-// of them as there are. (37k nodes: 256 positions in 145 units. 1,000 nodes, 365
-// days: 7.3 ms in units of 4, 8.1 of 64, 9.1 of 256; 5,000 nodes of a general
-// model, 120 days: 3.6 ms in units of 32, 8.3 of 4, five to a compute unit.)
-// 512 from two units of 256 per compute unit on, for models whose workgroups of
-// 512 threads leave room for another (1.5 million herds, a day in units of 256 /
-// 512: 140 / 124 us with a hundredth of them infected, 206 / 210 with all of them;
-// 100,000 herds 67 / 72; 400,000 herds of eight compartments 169 / 204).
+// tile_nodes names them: the fewest, as a power of two from 4, that leave at
+// most one unit per compute unit, so that a day's chains spread over as many of
+// them as there are. (37k nodes: 256 positions in 145 units; from 262,144
+// nodes on 1024, whose wavefronts all have owners. 1,000 nodes, 365 days: 7.3
+// ms in units of 4, 8.1 of 64, 9.1 of 256; 5,000 nodes of a general model, 120
+// days: 3.6 ms in units of 32, 8.3 of 4, five to a compute unit.) Large general
+// models, of 512 threads a workgroup, end at 256 (400,000 herds of eight
+// compartments, a day in units of 256 / 512: 169 / 204 us); the others do not,
+// as the largest herd's chain is walked by its unit's workgroup (a million
+// herds, hub of 249,000 attempts a day, 60 days in units of 512, whose workgroups
+// have 512 threads, / 1024: 81 / 67 ms; 1.5 million, all infected, a day 209 / 232 us).
 // Where many small groups fill more units than that anyway, a unit grows only
 // while their number falls, and past 256 positions only as long as few of them
 // stay empty, a quarter of the herds' number (5,000 networks of 50 herds, a day
@@ -424,14 +426,11 @@ struct UnitGroups {
 // 512 / 1024: 77 / 70 / 91).
 int64_t lane_unit(const UnitGroups &g, bool large) {
     int64_t u = 4;
-    while (u < 256 && g.units(u) > kUnitsWanted && g.units(2 * u) < g.units(u)) u *= 2;
-    if (u == 256 && !large && g.units(256) > 2 * kUnitsWanted &&
-        g.positions(512) <= std::max(g.all + g.all / 4, g.positions(256)))
-        u = 512;
+    while (u < (large ? 256 : kMaxUnit) && g.units(u) > kUnitsWanted && g.units(2 * u) < g.units(u) &&
+           (2 * u <= 256 || g.positions(2 * u) <= std::max(g.all + g.all / 4, g.positions(u))))
+        u *= 2;
     return u;
 }
-static_assert(kMaxUnit == 512, "the largest unit of lane_unit and of tile_nodes");
-
 // Positions of one instance's nodes: herds sorted by size (largest first)
 // are dealt one per unit of work in turn, back and forth (snake order), so the
 // longest SSA chains of a day run in different units, start first, and share

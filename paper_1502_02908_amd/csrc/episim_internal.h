@@ -165,7 +165,7 @@ constexpr uint32_t kFewChains = 4;     // default: at most this many live chains
 constexpr double kGroupMinAttempts = 256.0;  // default: a workgroup walks a chain expecting this many attempts
 // One lane per node: positions of one workgroup, a power of two up to kMaxUnit
 // (the persistent kernel's workgroups take kPersistUnit).
-constexpr int kMaxUnit = 512;
+constexpr int kMaxUnit = 1024;
 constexpr int kPersistUnit = 256;
 constexpr int64_t kUnitsWanted = 256;  // one a compute unit
 // Threads of a workgroup of the one-lane-per-node day kernel, at most: 1,024 (of
@@ -177,7 +177,7 @@ constexpr bool large_model(int nc, int nt, bool pairs) {
     return !(pairs && (nc == 2 || nc == 6)) && (nc > 4 || nt > 4);
 }
 constexpr int day_threads(int nc, int nt, bool pairs) { return large_model(nc, nt, pairs) ? 512 : 1024; }
-constexpr int kStageShift = 9;
+constexpr int kStageShift = 10;
 static_assert(kMaxUnit == 1 << kStageShift, "local positions fit below the slot (and the length class of a chain)");
 enum { LAYOUT_LANES = 0, LAYOUT_TILE = 1 };
 

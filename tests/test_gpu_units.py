@@ -71,15 +71,16 @@ def widespread(model, n_nodes, n_days, frac, seed):
 
 
 @pytest.mark.parametrize("frac", [0.375, 1.0])
-@pytest.mark.parametrize("model,n_nodes", [("sis", 66000), ("sis", 132001), ("sise3", 66000), ("sise3 levels", 66000),
-                                           ("sise3 pre", 132001), ("3", 66000), ("8", 66000)])
-def test_herds_walked_by_their_owners(model, n_nodes, frac):
-    # more units of 256 and of 512 positions than fill the chip with workgroups
-    # of 1,024 threads: wavefronts of 64 herds hold 24 chains on average, on
-    # both sides of the number that they walk themselves, and 64, of which
-    # the last eight and the longest start again in segments
+@pytest.mark.parametrize("model,n_nodes,tile", [("sis", 66000, 0), ("sis", 132001, 0), ("sise3", 66000, 0), ("sise3", 66100, 256),
+                                                ("sise3 levels", 66000, 0), ("sise3 pre", 132001, 0), ("3", 66000, 0),
+                                                ("8", 66000, 0)])
+def test_herds_walked_by_their_owners(model, n_nodes, tile, frac):
+    # units of 512 and 1024 positions in workgroups of 1,024 threads, and more
+    # units of 256 than fill the chip with those: wavefronts of 64 herds hold 24
+    # chains on average, on both sides of the number that they walk themselves,
+    # and 64, of which the last eight and the longest start again in segments
     p = widespread(model, n_nodes, 3, frac, 97)
     say(f"[units] owners {model} {n_nodes} herds, {frac} of them with a chain")
-    g = gpu_run(p)
+    g = gpu_run(p, tile_nodes=tile)
     assert_parity(g, O.run(p, threads=8))
     assert g["transitions"][0].sum() > 0.1 * frac * n_nodes
